@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "rve_internal.h"
+#include "rve_wave.h"
 
 namespace rve {
 
@@ -16,14 +17,6 @@ namespace {
 
 constexpr int kOrientThreads = 256;
 constexpr int ST_NONFINITE = 2, ST_BAD_F = 3;
-
-template <typename T>
-__device__ __forceinline__ T wave_sum64(T v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 __global__ __launch_bounds__(kOrientThreads) void orientation_kernel(OrientArgs A)
 {
@@ -67,7 +60,7 @@ __global__ __launch_bounds__(kOrientThreads) void orientation_kernel(OrientArgs 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
-        const double w = wave_sum64(s[q]);
+        const double w = wave_sum(s[q]);
         if (lane == 0) part[q][wave] = w;
     }
     __syncthreads();

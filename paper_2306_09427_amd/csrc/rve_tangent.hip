@@ -38,6 +38,7 @@
 #include <stdint.h>
 
 #include "rve_internal.h"
+#include "rve_wave.h"
 
 namespace rve {
 
@@ -183,14 +184,6 @@ __global__ __launch_bounds__(kOpsThreads) void fiber_ops_kernel(TangentArgs A)
 }
 
 // ------------------------------------------------------------------ wave helpers
-template <typename T>
-__device__ __forceinline__ T wsum(T v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // Values the whole wavefront shares (loaded through vector memory) moved to
 // scalar registers.
 __device__ __forceinline__ int64_t uni64(int64_t x)
@@ -429,29 +422,50 @@ struct CgRed {
     double s[2][3][16];   // per-wavefront partial sums, alternating buffers
 };
 
+// Totals of N <= 3 values over the workgroup, in every thread: wave sums, then
+// the waves in order.  One barrier; the buffers alternate with `parity`.
+template <int NW, int N>
+__device__ __forceinline__ void block_sums(CgRed& red, int parity, double (&v)[N])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] = wave_sum(v[q]);
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) red.s[parity][q][wave] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        double x = 0.0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) x += red.s[parity][q][i];
+        v[q] = uniformd(x);
+    }
+}
 template <int NW>
 __device__ __forceinline__ void block_sum3(CgRed& red, int parity, double& a, double& b, double& c)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    a = wsum(a);
-    b = wsum(b);
-    c = wsum(c);
-    if (lane == 0) {
-        red.s[parity][0][wave] = a;
-        red.s[parity][1][wave] = b;
-        red.s[parity][2][wave] = c;
-    }
-    __syncthreads();
-    double x = 0.0, y = 0.0, z = 0.0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        x += red.s[parity][0][i];
-        y += red.s[parity][1][i];
-        z += red.s[parity][2][i];
-    }
-    a = uniformd(x);
-    b = uniformd(y);
-    c = uniformd(z);
+    double v[3] = {a, b, c};
+    block_sums<NW, 3>(red, parity, v);
+    a = v[0];
+    b = v[1];
+    c = v[2];
+}
+template <int NW>
+__device__ __forceinline__ void block_sum2(CgRed& red, int parity, double& a, double& b)
+{
+    double v[2] = {a, b};
+    block_sums<NW, 2>(red, parity, v);
+    a = v[0];
+    b = v[1];
+}
+template <int NW>
+__device__ __forceinline__ void block_sum1(CgRed& red, int parity, double& a)
+{
+    double v[1] = {a};
+    block_sums<NW, 1>(red, parity, v);
+    a = v[0];
 }
 
 // ------------------------------------------------------------------ streamed tasks
@@ -468,13 +482,20 @@ __device__ void cg_stream_task(const TangentArgs& A, int r, int col, CgRed& red)
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int parity = 0;
     // sums over the workgroup (every thread gets the same totals)
+    auto sum1 = [&](double& x) __attribute__((always_inline)) {
+        if (T == 64) {
+            x = uniformd(wave_sum(x));
+        } else {
+            block_sum1<NW>(red, parity, x);
+            parity ^= 1;
+        }
+    };
     auto sum2 = [&](double& x, double& y) __attribute__((always_inline)) {
         if (T == 64) {
-            x = uniformd(wsum(x));
-            y = uniformd(wsum(y));
+            x = uniformd(wave_sum(x));
+            y = uniformd(wave_sum(y));
         } else {
-            double z = 0.0;
-            block_sum3<NW>(red, parity, x, y, z);
+            block_sum2<NW>(red, parity, x, y);
             parity ^= 1;
         }
     };
@@ -520,10 +541,7 @@ __device__ void cg_stream_task(const TangentArgs& A, int r, int col, CgRed& red)
             bb += b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
         }
     }
-    {
-        double u = 0.0;
-        sum2(bb, u);
-    }
+    sum1(bb);
     __syncthreads();
 
     int status = ST_CONVERGED;
@@ -599,10 +617,7 @@ __device__ void cg_stream_task(const TangentArgs& A, int r, int col, CgRed& red)
                     pq += (double)pa.x * qx + (double)pa.y * qy + (double)pa.z * qz;
                 }
             }
-            {
-                double u = 0.0;
-                sum2(pq, u);
-            }
+            sum1(pq);
             if (!(pq > 0.0)) {
                 status = ST_CG_INDEFINITE;
                 done = true;
@@ -659,7 +674,7 @@ __device__ void cg_stream_task(const TangentArgs& A, int r, int col, CgRed& red)
     assembly_partial<TAN>(A, c, r, kk, ll, x64, tid, T, acc);
     if (T == 64) {
 #pragma unroll
-        for (int p = 0; p < 9; ++p) acc[p] = wsum(acc[p]);
+        for (int p = 0; p < 9; ++p) acc[p] = wave_sum(acc[p]);
     } else {
 #pragma unroll
         for (int p = 0; p < 9; p += 3) {
@@ -765,8 +780,7 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
         if (tid < 3) x64[3 * nf + tid] = 0.0;
     }
     {
-        double u0 = 0.0, u1 = 0.0;
-        block_sum3<NW>(red, parity, bb, u0, u1);
+        block_sum1<NW>(red, parity, bb);
         parity ^= 1;
     }
 
@@ -832,8 +846,7 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
             }
         }
         {
-            double u0 = 0.0;
-            block_sum3<NW>(red, parity, rr, rz, u0);
+            block_sum2<NW>(red, parity, rr, rz);
             parity ^= 1;
         }
         if (rr <= tol2 * bb) {
@@ -890,8 +903,7 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
                 pq += (double)pk.x * sx + (double)pk.y * sy + (double)pk.z * sz;
             }
             {
-                double u0 = 0.0, u1 = 0.0;
-                block_sum3<NW>(red, parity, pq, u0, u1);
+                block_sum1<NW>(red, parity, pq);
                 parity ^= 1;
             }
             if (!(pq > 0.0)) {
@@ -929,8 +941,7 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
                 rzn += (double)R[k][0] * z.x + (double)R[k][1] * z.y + (double)R[k][2] * z.z;
             }
             {
-                double u0 = 0.0;
-                block_sum3<NW>(red, parity, rn, rzn, u0);
+                block_sum2<NW>(red, parity, rn, rzn);
                 parity ^= 1;
             }
             if (rn <= 1e-6 * rr0 || rn <= 0.25 * tol2 * bb) break;
@@ -1030,7 +1041,7 @@ __device__ __forceinline__ void block_sum_n(BlkRed& red, int parity, double (&v)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const double w = wsum(v[i]);
+        const double w = wave_sum(v[i]);
         if (lane == 0) red.s[parity][i][wave] = w;
     }
     __syncthreads();

@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include "rve_internal.h"
+#include "rve_wave.h"
 
 namespace rve {
 
@@ -194,20 +195,6 @@ __device__ __forceinline__ void t_two_sum(double a, double b, double& s, double&
     e = (a - (s - z)) + (b - z);
 }
 
-template <typename T>
-__device__ inline T t_wave_sum(T v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-__device__ inline double t_wave_max(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
 // Shared scalars of a team workgroup.
 struct TeamShared {
     double w[16][6];    // per-wave partials: gmax, |f_free|^2, |cMv|^2, |f_bnd|^2, KE
@@ -224,11 +211,11 @@ __device__ __forceinline__ void wg_partials(TeamShared& S, int tid, double g, do
                                             double ke)
 {
     const int lane = tid & 63, wave = tid >> 6;
-    g = t_wave_max(g);
-    r2 = t_wave_sum(r2);
-    d2 = t_wave_sum(d2);
-    b2 = t_wave_sum(b2);
-    ke = t_wave_sum(ke);
+    g = wave_max(g);
+    r2 = wave_sum(r2);
+    d2 = wave_sum(d2);
+    b2 = wave_sum(b2);
+    ke = wave_sum(ke);
     if (lane == 0) {
         S.w[wave][0] = g; S.w[wave][1] = r2; S.w[wave][2] = d2; S.w[wave][3] = b2; S.w[wave][4] = ke;
     }

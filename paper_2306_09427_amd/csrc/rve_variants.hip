@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include "rve_internal.h"
+#include "rve_wave.h"
 
 namespace rve {
 
@@ -31,20 +32,6 @@ constexpr int LAW_EXP = 1, MASS_SCALED = 1, INIT_WARM = 2;
 constexpr int DAMP_KINETIC = 1, DAMP_ADAPTIVE = 2;
 constexpr int kNodeDoubles = 17;   // h 3, v 3, a 3, f 3, h_start 3, M, G
 constexpr int kFibDoubles = 5;     // force vector 3, Gershgorin term, stored energy
-
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
-}
 
 // Sums of N values over the workgroup (value k of every thread), and one
 // maximum, in a fixed order: wave sums, then the waves in order.  Every
