@@ -87,7 +87,7 @@ struct rve_batch {
     bool have_state = false;
     // [kinetic][fp64][variant]: the build uses private (scratch) memory and is never launched
     bool variant_spills[2][2][kNumResident] = {};
-    bool streamed_private[2][2][2] = {};            // [kinetic][fp64][1024 threads]: same for the streamed builds
+    bool streamed_private[2][2][3] = {};             // [kinetic][fp64][256, 1024, 512 threads]: same for the streamed builds
     bool tangent_private[2][kNumTanRes] = {};        // [vjp][variant]: same for the resident tangent builds
     bool tangent_blk_private[kNumTanBlk] = {};       // same for the blocked tangent builds
     // tangent / vjp workspace
@@ -186,33 +186,32 @@ static bool spills(const rve_batch* b, int v, bool fp64)
     return b->variant_spills[kinetic_mode(b->opts) ? 1 : 0][fp64 ? 1 : 0][v];
 }
 
-// Size tiers: distinct (fiber, node) capacities of the resident variants, ascending.
-static std::vector<std::pair<int64_t, int64_t>> tier_caps()
+// Size tiers: distinct (fiber, node) capacities of the resident variants of a
+// precision, ascending.
+static std::vector<std::pair<int64_t, int64_t>> tier_caps(bool fp64)
 {
     std::vector<std::pair<int64_t, int64_t>> caps;
     for (int v = 0; v < kNumResident; ++v)
-        caps.push_back({(int64_t)kResident[v].threads * kResident[v].sf, (int64_t)kResident[v].threads * kResident[v].sn});
+        if (resident_fixed(v, fp64)) caps.push_back({resident_fibers(v, fp64), resident_nodes(v, fp64)});
     std::sort(caps.begin(), caps.end());
     caps.erase(std::unique(caps.begin(), caps.end()), caps.end());
     return caps;
 }
 
-// Tier of an RVE (index into tier_caps) or -1 when only the streamed kernel can take it.
+// Tier of an RVE (index into tier_caps) or -1 when no resident variant holds it.
 static int tier_of(const rve_batch* b, int64_t r, bool fp64)
 {
-    size_t lds_cap = 160 * 1024 - 4096;
-    if (b->nfib_of[r] >= kResMaxFibers || resident_lds_bytes(fp64, b->nf_of[r], b->nfib_of[r], 0) > lds_cap) return -1;
-    auto caps = tier_caps();
+    const auto caps = tier_caps(fp64);
     for (size_t t = 0; t < caps.size(); ++t)
         if (b->nfib_of[r] <= caps[t].first && b->nf_of[r] <= caps[t].second) return (int)t;
     return -1;
 }
 
-static bool variant_fits_tier(int v, int tier)
+static bool variant_fits_tier(int v, int tier, bool fp64)
 {
-    auto caps = tier_caps();
-    return (int64_t)kResident[v].threads * kResident[v].sf >= caps[tier].first &&
-           (int64_t)kResident[v].threads * kResident[v].sn >= caps[tier].second;
+    const auto caps = tier_caps(fp64);
+    return resident_fixed(v, fp64) && resident_fibers(v, fp64) >= caps[tier].first &&
+           resident_nodes(v, fp64) >= caps[tier].second;
 }
 
 static int ensure_events(rve_batch* b, int n)
@@ -988,44 +987,45 @@ static int check_indexing(const rve_net_desc* net, bool fp64, int plant)
             if (seen[q] != 1) return bad(r, "fiber " + std::to_string(q / 2) + " end " + std::to_string(q % 2) + " listed " +
                                                 std::to_string(seen[q]) + " times");
         // register-resident builds that hold this RVE
-        const int64_t h_entries = nf + 1 - (plant == 1 ? 1 : 0);
-        const int64_t fv_entries = nfib + 1;
         for (int v = 0; v < kNumResident; ++v) {
+            if (!resident_fixed(v, fp64) || nfib > resident_fibers(v, fp64) || nf > resident_nodes(v, fp64)) continue;
             const ResidentVariant& rv = kResident[v];
-            if (nfib > (int64_t)rv.threads * rv.sf || nf > (int64_t)rv.threads * rv.sn) continue;
-            if (nfib >= kResMaxFibers) continue;   // such RVEs only run streamed (tier_of)
-            const size_t dyn = resident_lds_bytes(fp64, nf, nfib, rv.threads);
-            if (dyn > 160 * 1024 - 4096) continue;   // tier_of sends these to the streamed engine
-            if (dyn + kResStaticLds > 160 * 1024) return bad(r, "LDS of a resident workgroup exceeds 160 KB");
-            for (int tid = 0; tid < rv.threads; ++tid) {
-                for (int sl = 0; sl < rv.sf; ++sl) {
-                    const int64_t k = (int64_t)sl * rv.threads + tid;
-                    if (k >= nfib) continue;
-                    const uint32_t E = res_pack_ends(P.ends[f0 + k], (uint32_t)nf);
-                    if ((int64_t)res_end_i(E) >= h_entries || (int64_t)res_end_j(E) >= h_entries)
-                        return bad(r, "build " + std::to_string(v) + ": fiber " + std::to_string(k) +
-                                          " reads a position outside the LDS array");
-                }
-                for (int sl = 0; sl < rv.sn; ++sl) {
-                    const int64_t a = (int64_t)sl * rv.threads + tid;
-                    if (a >= nf) continue;   // lanes past nf only read the zero slot (padding codes)
-                    const int64_t e0 = P.inc_off[a0 + a], deg = P.inc_off[a0 + a + 1] - e0;
-                    for (int q = 0; q < kResIncRegs; ++q) {
-                        const uint32_t code = q < deg ? res_inc_code(P.inc[e0 + q]) : (uint32_t)nfib;
-                        if ((int64_t)res_code_fiber(code) >= fv_entries)
-                            return bad(r, "build " + std::to_string(v) + ": node " + std::to_string(a) +
-                                              " reads a force outside the LDS array");
-                        if (q < deg && res_code_neg(code) != ((P.inc[e0 + q] >> 31) != 0))
-                            return bad(r, "incidence code loses the end sign");
-                        if (q < deg && (int64_t)res_code_fiber(code) != (int64_t)(P.inc[e0 + q] & 0x7fffffffu))
-                            return bad(r, "incidence code loses fiber id bits");
-                    }
-                    for (int64_t e = e0 + kResIncRegs; e < e0 + deg; ++e)
-                        if ((int64_t)(P.inc[e] & 0x7fffffffu) >= fv_entries)
-                            return bad(r, "overflow incidence reads a force outside the LDS array");
+            const ResLayout L = res_layout(fp64, rv.threads, rv.sf, rv.sn);
+            const std::string build = "build " + std::to_string(v) + ": ";
+            const int64_t h_bytes = (int64_t)L.unit * (L.NP + 1 - (plant == 1 ? 1 : 0)), f_bytes = (int64_t)L.unit * L.NF;
+            if (res_lds_total(fp64, rv.threads, rv.sf, rv.sn) > 160 * 1024) return bad(r, build + "LDS exceeds 160 KB");
+            // whole waves take part in a slot: its lanes past the last fiber or
+            // node write neutral values to their own LDS slots
+            if (((nfib + 63) & ~int64_t(63)) > L.NF || ((nf + 63) & ~int64_t(63)) > L.NP)
+                return bad(r, build + "a wave's slot reaches past the LDS array");
+            if (nfib >= L.NF) return bad(r, build + "no zero force slot");
+            for (int64_t k = 0; k < nfib; ++k) {
+                const uint32_t E = chip_ends(P.ends[f0 + k], (uint32_t)nf, L);
+                if ((int64_t)(E & 0xffffu) + L.unit > h_bytes || (int64_t)(E >> 16) + L.unit > h_bytes)
+                    return bad(r, build + "fiber " + std::to_string(k) + " reads a position outside the LDS array");
+                for (int end = 0; end < 2; ++end) {
+                    const int64_t id = end ? P.ends[f0 + k] >> 16 : P.ends[f0 + k] & 0xffffu;
+                    if ((int64_t)(end ? E >> 16 : E & 0xffffu) != (id < nf ? id : L.NP) * L.unit)
+                        return bad(r, build + "a fiber end's offset names another node");
                 }
             }
-            if (nfib > 0x7fff) return bad(r, "the zero force slot does not fit the 15-bit code");
+            for (int64_t a = 0; a < nf; ++a) {
+                const int64_t e0 = P.inc_off[a0 + a], deg = P.inc_off[a0 + a + 1] - e0;
+                for (int64_t q = 0; q < std::max<int64_t>(deg, kResIncRegs); ++q) {
+                    // two incidences per word, beside a neighbour that sets every bit it may
+                    const uint32_t w = q < deg ? P.inc[e0 + q] : (uint32_t)nfib;
+                    const int half = (int)(q & 1);
+                    const uint32_t in = half ? chip_codes((uint32_t)L.NF - 1, 1, w & 0x7fffffffu, w >> 31, L)
+                                             : chip_codes(w & 0x7fffffffu, w >> 31, (uint32_t)L.NF - 1, 1, L);
+                    const int64_t o = chip_offset(in, half, L);
+                    if (o + L.unit > f_bytes)
+                        return bad(r, build + "node " + std::to_string(a) + " reads a force outside the LDS array");
+                    if (chip_sign(in, half, L) != (w & 0x80000000u)) return bad(r, build + "incidence code loses the end sign");
+                    if (o != (int64_t)(w & 0x7fffffffu) * L.unit) return bad(r, build + "incidence code loses fiber id bits");
+                }
+                if (a > 0 && deg <= kResIncRegs && P.inc_off[a0 + a] - P.inc_off[a0 + a - 1] > kResIncRegs)
+                    return bad(r, "nodes of degree above 4 are not the last free nodes");
+            }
         }
         // streamed engine: workspace entries [NF + R] per fiber array, [NFREE + R] positions
         if (f0 + r + nfib >= NF + R) return bad(r, "streamed fiber zero slot outside the workspace");
@@ -1187,17 +1187,28 @@ static int default_variant(const rve_batch* b, int tier, bool fp64)
 {
     const int T = b->opts.threads_per_rve;
     const bool kin = kinetic_mode(b->opts);
-    const auto caps = tier_caps();
-    const size_t lds = resident_lds_bytes(fp64, caps[tier].second, caps[tier].first, 0);
+    // A batch of no more RVEs than CUs runs one RVE per CU whatever the build,
+    // and its time is that of one iteration: the build with the most threads,
+    // except that the smallest RVEs, whose barriers then cost more than the
+    // slots they save, take 512.  us per iteration, one RVE: 60 seeds 1.33 with
+    // 256 threads, 1.17 with 512, 1.25 with 1024; 100 seeds 1.97, 1.42, 1.44;
+    // 300 seeds 2.66 with 512, 2.24 with 1024; FP64, 100 seeds, 2.66 with 256,
+    // 2.36 with 512.  More RVEs than CUs: the most workgroups per CU (1024 RVEs
+    // of 300 seeds 7.2 us with 512 threads, two per CU, 9.2 with 1024).
+    if (b->R <= b->n_cu && !T) {
+        const int pref[2][3] = {{1, 4, 5}, {1, 3, 6}};   // [fp64]
+        for (int v : pref[fp64 ? 1 : 0])
+            if (!spills(b, v, fp64) && variant_fits_tier(v, tier, fp64) && (v != 1 || tier == 0 || fp64)) return v;
+    }
     int chosen = -1, best_blocks = 0;
     int64_t best = 0;
     for (int v = 0; v < kNumResident; ++v) {
         const ResidentVariant& rv = kResident[v];
         if (T && rv.threads != T) continue;
         if (spills(b, v, fp64)) continue;   // never launched
-        if (!variant_fits_tier(v, tier)) continue;
+        if (!variant_fits_tier(v, tier, fp64)) continue;
         int per_cu = 0;
-        if (max_resident_blocks(v, fp64, kin, lds, &per_cu) != hipSuccess || per_cu < 1) continue;
+        if (max_resident_blocks(v, fp64, kin, 0, &per_cu) != hipSuccess || per_cu < 1) continue;
         const int64_t key = (int64_t)rv.threads * rv.sf * 4096 - rv.threads;
         if (chosen < 0 || per_cu > best_blocks || (per_cu == best_blocks && key < best)) {
             chosen = v;
@@ -1289,7 +1300,6 @@ static void assign_groups(rve_batch* b)
         size_t lds = 0;
         int team = 0, code = kStreamedGroup;
         if (v < (size_t)kNumResident) {
-            for (int32_t r : members) lds = std::max(lds, resident_lds_bytes(fp64, b->nf_of[r], b->nfib_of[r], 0));
             code = (int)v;
         } else if (v == (size_t)inc_slot) {
             for (int32_t r : members) lds = std::max(lds, incidence_lds_bytes(b->nf_of[r]));
@@ -1343,11 +1353,14 @@ static int streamed_blocks_per_cu(int threads, int64_t lds_nodes, bool fp64)
 
 // Workgroup size of the streamed engine: 1024 threads unless 256 are asked
 // for or the 1024-thread build of this precision and damping uses private
-// memory (the FP64 builds do); 0 when neither build may be launched.
+// memory (the FP64 builds do, and take 512 threads, else 256: one RVE of 550
+// seeds 22.7 us per iteration against 28.2 with 256 threads, 1024 of them 196
+// against 215 us); 0 when no build may be launched.
 static int streamed_threads(const rve_batch* b, bool fp64)
 {
     const int k = kinetic_mode(b->opts) ? 1 : 0, p = fp64 ? 1 : 0;
     if (b->opts.threads_per_rve != 256 && !b->streamed_private[k][p][1]) return 1024;
+    if (b->opts.threads_per_rve != 256 && fp64 && !b->streamed_private[k][p][2]) return 512;
     return b->streamed_private[k][p][0] ? 0 : 256;
 }
 
@@ -1499,9 +1512,10 @@ int rve_batch_create(const rve_net_desc* net, const rve_opts* opts, rve_batch** 
                 if (resident_scratch_bytes(v, p == 1, k == 1, &sb) != hipSuccess) sb = 1;
                 b->variant_spills[k][p][v] = sb > 0;
             }
-            for (int w = 0; w < 2; ++w) {
+            for (int w = 0; w < 3; ++w) {
+                const int threads[3] = {256, 1024, 512};
                 size_t sb = 1;
-                if (streamed_scratch_bytes(p == 1, k == 1, w ? 1024 : 256, &sb) != hipSuccess) sb = 1;
+                if (streamed_scratch_bytes(p == 1, k == 1, threads[w], &sb) != hipSuccess) sb = 1;
                 b->streamed_private[k][p][w] = sb > 0;
             }
         }
@@ -1820,6 +1834,10 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
             rest.push_back({-w, g});
         }
     std::sort(rest.begin(), rest.end());
+    if (b->R <= b->n_cu)   // the largest RVEs first
+        std::stable_sort(rest.begin(), rest.end(), [&](const std::pair<int64_t, size_t>& x, const std::pair<int64_t, size_t>& y) {
+            return b->nfib_of[b->groups[x.second][0]] > b->nfib_of[b->groups[y.second][0]];
+        });
     for (auto& pr : rest) order.push_back(pr.second);
     const bool fork = concurrent && rest.size() > 1;
     if (fork) {
@@ -1829,6 +1847,28 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
         }
         if (!b->fork_ev) HIP_TRY(hipEventCreateWithFlags(&b->fork_ev, hipEventDisableTiming));
     }
+    // A batch of fewer RVEs than CUs leaves CUs idle: each workgroup of the
+    // resident launches asks for more than half of a CU's LDS, so that none
+    // shares a CU with another launch's (8 RVEs of 100 to 400 seeds in three
+    // launches: 31.6 ms where two shared a CU, 18.2 ms apart).  Only where each
+    // XCD has a CU for its share of every launch (workgroups go to the 8 XCDs
+    // in turn, launch by launch), or some would wait for one.
+    int64_t per_xcd = 0;
+    for (const auto& g : b->groups) per_xcd += ((int64_t)g.size() + 7) / 8;
+    const bool own_cu = b->R <= b->n_cu, apart = 8 * per_xcd <= b->n_cu;
+    // Four launches run at once (the batch's stream and three more); a further
+    // one goes behind the launch that is expected to end first: the one of
+    // least work, or, with a CU for every RVE, of the smallest RVEs.
+    std::vector<int> lane_of(order.size(), 0);
+    {
+        double load[4] = {0, 0, 0, 0};
+        for (size_t q = 0; q < rest.size(); ++q) {
+            const std::vector<int32_t>& g = b->groups[order[n_team + q]];
+            const double w = own_cu ? (double)b->nfib_of[g[0]] : -(double)rest[q].first;
+            lane_of[q] = (int)(std::min_element(load, load + 4) - load);
+            load[lane_of[q]] += w;
+        }
+    }
     for (size_t oi = 0; oi < order.size(); ++oi) {
         const size_t g = order[oi];
         hipStream_t gs_ = s;
@@ -1836,7 +1876,7 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
             HIP_TRY(hipEventRecord(b->fork_ev, s));
             for (int q = 0; q < 3; ++q) HIP_TRY(hipStreamWaitEvent(b->aux[q], b->fork_ev, 0));
         }
-        if (fork && oi > n_team) gs_ = b->aux[(oi - n_team - 1) % 3];
+        if (fork && oi >= n_team && lane_of[oi - n_team] > 0) gs_ = b->aux[lane_of[oi - n_team] - 1];
         a.list = b->dlist + b->group_first[g];
         a.n_list = (int32_t)b->groups[g].size();
         a.queue = queues + 2 * g;
@@ -1844,10 +1884,12 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
         if (profile) HIP_TRY(hipEventRecord(b->ev[2 * g], gs_));
         if (v >= 0) {
             int per_cu = 1;
-            HIP_TRY(max_resident_blocks(v, fp64, a.kinetic != 0, b->group_lds[g], &per_cu));
+            HIP_TRY(max_resident_blocks(v, fp64, a.kinetic != 0, 0, &per_cu));
             if (per_cu < 1) return fail(RVE_EDEVICE, "resident kernel variant does not fit a CU");
             int grid = std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list);
-            HIP_TRY(launch_resident(v, fp64, a, b->group_lds[g], grid, gs_));
+            const ResidentVariant& rv = kResident[v];
+            const size_t own = (size_t)res_lds_total(fp64, rv.threads, rv.sf, rv.sn), want = 84 * 1024;
+            HIP_TRY(launch_resident(v, fp64, a, apart && own < want ? want - own : 0, grid, gs_));
         } else if (v == kIncGroup) {
             const int iv = inc_variant(b);
             if (iv < 0) return fail(RVE_EDEVICE, "internal: no incidence build for these options");
@@ -2113,7 +2155,7 @@ int rve_batch_autotune(rve_batch* b, const double* F, int32_t ptr_kind, int32_t 
     if (rc) return rc;
     int rc_ev = ensure_events(b, 2);
     if (rc_ev) return rc_ev;
-    auto caps = tier_caps();
+    const auto caps = tier_caps(fp64);
     for (size_t t = 0; t < caps.size(); ++t) {
         std::vector<int32_t> members;
         for (int64_t r = 0; r < b->R; ++r)
@@ -2123,11 +2165,7 @@ int rve_batch_autotune(rve_batch* b, const double* F, int32_t ptr_kind, int32_t 
                          [&](int32_t x, int32_t y) { return b->nfib_of[x] > b->nfib_of[y]; });
         members.resize(std::min<size_t>(members.size(), (size_t)b->n_cu * 2));
         double fibs = 0.0;
-        size_t lds = 0;
-        for (int32_t r : members) {
-            fibs += (double)b->nfib_of[r];
-            lds = std::max(lds, resident_lds_bytes(fp64, b->nf_of[r], b->nfib_of[r], 0));
-        }
+        for (int32_t r : members) fibs += (double)b->nfib_of[r];
         HIP_TRY(hipMemcpy(b->dtune_list, members.data(), 4 * members.size(), hipMemcpyHostToDevice));
         SolveArgs a;
         fill_solve_args(b, a);
@@ -2148,12 +2186,12 @@ int rve_batch_autotune(rve_batch* b, const double* F, int32_t ptr_kind, int32_t 
             // edit changed its spill code, and a later build of it faulted.
             // Each remaining candidate's final states must also stay close to
             // those of the streamed kernel (timed first) on the tuning RVEs.
-            if (v >= 0 && (!variant_fits_tier(v, (int)t) || spills(b, v, fp64))) continue;
+            if (v >= 0 && (!variant_fits_tier(v, (int)t, fp64) || spills(b, v, fp64))) continue;
             if (v < 0 && !streamed_threads(b, fp64)) continue;
             int grid = 0;
             if (v >= 0) {
                 int per_cu = 0;
-                if (max_resident_blocks(v, fp64, a.kinetic != 0, lds, &per_cu) != hipSuccess || per_cu < 1) continue;
+                if (max_resident_blocks(v, fp64, a.kinetic != 0, 0, &per_cu) != hipSuccess || per_cu < 1) continue;
                 grid = (int)std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list);
             } else {
                 a.lds_h_nodes = streamed_lds_nodes(b, members.data(), members.size(), fp64);
@@ -2165,7 +2203,7 @@ int rve_batch_autotune(rve_batch* b, const double* F, int32_t ptr_kind, int32_t 
                 HIP_TRY(launch_reset(a.queue, 1, s));
                 HIP_TRY(hipEventRecord(b->ev[0], s));
                 if (v >= 0)
-                    HIP_TRY(launch_resident(v, fp64, a, lds, grid, s));
+                    HIP_TRY(launch_resident(v, fp64, a, 0, grid, s));
                 else
                     HIP_TRY(launch_streamed(fp64, a, grid, streamed_threads(b, fp64), s));
                 HIP_TRY(hipEventRecord(b->ev[1], s));

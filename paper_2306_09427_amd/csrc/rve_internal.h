@@ -151,10 +151,11 @@ struct VariantArgs {
 hipError_t launch_variant(const VariantArgs& a, int64_t n_rve, hipStream_t s);
 size_t variant_ws_bytes(int64_t n_free, int64_t n_fib);
 
-// Index arithmetic of the register-resident engine, shared by the kernels
-// and the host replay that bounds every index (rve_check_indexing).
-// Fiber ends: two 16-bit local node ids, free-first numbering; a boundary
-// end (id >= nf) reads the zero position slot nf.
+// Index arithmetic shared by the on-chip kernels and the host replay that
+// bounds every index (rve_check_indexing).  The team engine and the FP64
+// resident builds without the fixed LDS layout use 16-bit ids: fiber ends as
+// two 16-bit local node ids, free-first numbering; a boundary end (id >= nf)
+// reads the zero position slot nf.
 __host__ __device__ inline uint32_t res_pack_ends(uint32_t ends, uint32_t nf)
 {
     uint32_t i = ends & 0xffffu, j = ends >> 16;
@@ -172,6 +173,67 @@ __host__ __device__ inline uint32_t res_code_fiber(uint32_t code) { return code 
 __host__ __device__ inline bool res_code_neg(uint32_t code) { return (code & 0x8000u) != 0; }
 constexpr int kResIncRegs = 4;          // incidences per node held in registers (two codes per word)
 constexpr int kResMaxFibers = 0x7fff;   // fiber ids and the zero slot fit the 15-bit code
+
+// Fixed LDS layout of a resident workgroup (rve_resident.hip): every array
+// starts at a compile-time offset, so an access is one VGPR address plus an
+// instruction offset.  Positions: NP slots and the zero slot NP that every
+// boundary end reads.  Fiber forces: NF slots, of which slot nfib stays zero
+// (the padding of short incidence lists), so an RVE has at most NF - 1 fibers.
+// One access unit is 16 bytes in FP32 (float4 records) and 8 in FP64
+// (structure of arrays).  The largest FP64 build holds fewer slots than its
+// threads could, because its arrays fill the 160 KB.
+struct ResLayout {
+    int NF, NP, unit;
+    bool ids;   // incidence codes hold ids (the byte offsets of NF slots pass 16 bits)
+};
+__host__ __device__ constexpr bool res_lds_full(bool fp64, int threads, int sf) { return fp64 && threads * sf == 4096; }
+__host__ __device__ constexpr ResLayout res_layout(bool fp64, int threads, int sf, int sn)
+{
+    return {res_lds_full(fp64, threads, sf) ? 3968 : threads * sf, res_lds_full(fp64, threads, sf) ? 1920 : threads * sn,
+            fp64 ? 8 : 16, !fp64 && threads * sf > 4096};
+}
+// Bytes of the positions, of both arrays, and the table sizes behind them:
+// boundary fibers and the incidences of nodes of degree above 4 (16 bits each).
+__host__ __device__ constexpr int res_pos_bytes(bool fp64, const ResLayout& L) { return (fp64 ? 24 : 16) * (L.NP + 1); }
+__host__ __device__ constexpr int res_arr_bytes(bool fp64, const ResLayout& L)
+{
+    return res_pos_bytes(fp64, L) + (fp64 ? 28 : 16) * L.NF;
+}
+__host__ __device__ constexpr int res_bcap(int threads) { return threads; }
+__host__ __device__ constexpr int res_xcap(int threads) { return 2 * threads; }
+__host__ __device__ constexpr int res_lds_total(bool fp64, int threads, int sf, int sn)
+{
+    return res_arr_bytes(fp64, res_layout(fp64, threads, sf, sn)) + 2 * (res_bcap(threads) + res_xcap(threads)) + 1024;
+}
+// Fiber ends as two 16-bit byte offsets into the positions.
+__host__ __device__ inline uint32_t chip_ends(uint32_t ends, uint32_t nf, const ResLayout& L)
+{
+    uint32_t i = ends & 0xffffu, j = ends >> 16;
+    i = i < nf ? i : (uint32_t)L.NP;
+    j = j < nf ? j : (uint32_t)L.NP;
+    return i * (uint32_t)L.unit | (j * (uint32_t)L.unit) << 16;
+}
+// Two incidences in one word, fiber ids k0 and k1, n set when the node is the
+// fiber's end i (its force enters with a minus sign).  Byte form: the force
+// offsets in the two halves (multiples of 8 or 16), both signs in the two lowest
+// bits, so the high offset is one shift away, the low one one AND, and the low
+// sign one shift-or away from a factor of +-1.  Id form: 13-bit ids, the sign
+// in the top bit of each half.
+__host__ __device__ constexpr uint32_t chip_codes(uint32_t k0, uint32_t n0, uint32_t k1, uint32_t n1, const ResLayout& L)
+{
+    return L.ids ? (k0 | n0 << 15 | k1 << 16 | n1 << 31)
+                 : (k0 * (uint32_t)L.unit | n0 | n1 << 1 | (k1 * (uint32_t)L.unit) << 16);
+}
+__host__ __device__ constexpr uint32_t chip_offset(uint32_t w, int half, const ResLayout& L)
+{
+    return L.ids ? (half ? w >> 12 & 0x1fff0u : (w & 0x1fffu) << 4)
+                 : (half ? w >> 16 : w & (0x10000u - (uint32_t)L.unit));
+}
+// the sign of a half as bit 31
+__host__ __device__ constexpr uint32_t chip_sign(uint32_t w, int half, const ResLayout& L)
+{
+    return L.ids ? (half ? w & 0x80000000u : w << 16 & 0x80000000u) : (half ? w << 30 & 0x80000000u : w << 31);
+}
 
 // Reduction slots of a relaxation workgroup (static LDS of the resident and
 // streamed kernels): per-wave partial sums of |f_free|^2, |c M v|^2,
@@ -287,13 +349,24 @@ struct ResidentVariant {
     int threads, sf, sn;
 };
 
-constexpr int kNumResident = 6;
+constexpr int kNumResident = 7;
 extern const ResidentVariant kResident[kNumResident];
 
-// LDS bytes a resident variant needs for an RVE of nf free nodes and nfib fibers.
-size_t resident_lds_bytes(bool fp64, int64_t nf, int64_t nfib, int threads);
+// Whether a variant exists with the fixed LDS layout in this precision (the
+// others are FP64 builds that exceed their register budget and are never
+// launched), and the largest RVE it holds.
+inline bool resident_fixed(int v, bool fp64) { return fp64 ? v == 0 || v == 1 || v == 3 || v == 6 : v < 6; }
+inline int resident_fibers(int v, bool fp64)
+{
+    return res_layout(fp64, kResident[v].threads, kResident[v].sf, kResident[v].sn).NF - 1;
+}
+inline int resident_nodes(int v, bool fp64)
+{
+    return res_layout(fp64, kResident[v].threads, kResident[v].sf, kResident[v].sn).NP;
+}
 
-hipError_t launch_resident(int variant, bool fp64, const SolveArgs& a, size_t lds_bytes, int grid,
+// lds_pad: dynamic LDS on top of the build's own (to keep other workgroups off its CU).
+hipError_t launch_resident(int variant, bool fp64, const SolveArgs& a, size_t lds_pad, int grid,
                            hipStream_t s);
 hipError_t launch_streamed(bool fp64, const SolveArgs& a, int grid, int threads, hipStream_t s);
 size_t streamed_lds_cap();   // bytes of LDS the streamed engine may use for h
@@ -329,9 +402,10 @@ hipError_t launch_tangent_res(int variant, const TangentArgs& a, int grid, hipSt
 hipError_t launch_tangent_stream(const TangentArgs& a, int threads, int grid, hipStream_t s);
 hipError_t tangent_res_blocks(int variant, bool vjp, int* blocks_per_cu);
 // kin: the kinetic-damping build of the variant (launch_resident reads a.kinetic).
-hipError_t max_resident_blocks(int variant, bool fp64, bool kin, size_t lds_bytes, int* blocks_per_cu);
+hipError_t max_resident_blocks(int variant, bool fp64, bool kin, size_t lds_pad, int* blocks_per_cu);
 // Private (spill) bytes per lane of a resident variant; > 0 means it spills.
 hipError_t resident_scratch_bytes(int variant, bool fp64, bool kin, size_t* bytes);
+hipError_t resident_wide_scratch_bytes(int variant, bool fp64, bool kin, size_t* bytes);
 // Same for a streamed build (256 or 1024 threads) and a resident tangent build.
 hipError_t streamed_scratch_bytes(bool fp64, bool kin, int threads, size_t* bytes);
 hipError_t tangent_res_scratch_bytes(int variant, bool vjp, size_t* bytes);

@@ -32,38 +32,14 @@
 #include <stdint.h>
 
 #include "rve_internal.h"
+#include "rve_relax.h"
+#include "rve_wave.h"
 
 namespace rve {
 
 const ResidentVariant kResident[kNumResident] = {
-    {256, 4, 2}, {512, 4, 2}, {768, 4, 2}, {512, 6, 3}, {1024, 4, 2}, {1024, 6, 3},
+    {256, 4, 2}, {512, 4, 2}, {768, 4, 2}, {512, 6, 3}, {1024, 4, 2}, {1024, 6, 3}, {512, 8, 4},
 };
-
-constexpr int kLawLinear = 0;
-constexpr int kMassScaled = 1;
-constexpr int kInitWarm = 2;
-
-constexpr int ST_CONVERGED = 0, ST_MAXITER = 1, ST_NONFINITE = 2, ST_BAD_F = 3, ST_STAGNATED = 8;
-
-// Stagnation stop, evaluated at a convergence test that did not converge
-// (floor_tol_rel > 0): Rref is the residual of the start, replaced by R
-// whenever R falls below half of it, and stall counts the tests since (it
-// saturates at stall_checks).  The run stops once stall_checks tests have
-// passed without a halving while R and the damping-force norm D are both
-// within floor_tol_rel |f_bnd|.
-__device__ __forceinline__ bool stagnated(const SolveArgs& A, double R, double D, double B, double& Rref,
-                                          int& stall)
-{
-    if (!(A.floor_tol_rel > 0.0)) return false;
-    if (R < 0.5 * Rref) {
-        Rref = R;
-        stall = 0;
-        return false;
-    }
-    if (stall < A.stall_checks) ++stall;
-    const double ftol = A.floor_tol_rel * B;
-    return stall >= A.stall_checks && R <= ftol && D <= ftol;
-}
 
 // ------------------------------------------------------------------ helpers
 template <typename Real>
@@ -176,71 +152,6 @@ __device__ __forceinline__ FiberOut<double> fiber_eval_exact(int law, double EA,
     return o;
 }
 
-// The thread id as a value the compiler cannot see through: indices derived
-// from it are recomputed where used instead of being hoisted and kept live.
-__device__ __forceinline__ int opaque_tid()
-{
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    return t;
-}
-
-// Broadcast helpers: values every lane holds identically (read back from LDS
-// after a barrier) are moved to scalar registers.
-__device__ __forceinline__ double uniform(double x)
-{
-    int lo = __builtin_amdgcn_readfirstlane(__double2loint(x));
-    int hi = __builtin_amdgcn_readfirstlane(__double2hiint(x));
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ float uniform(float x)
-{
-    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
-}
-__device__ __forceinline__ int uniform32(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ int64_t uniform64(int64_t x)
-{
-    const int lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-    const int hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-template <typename T>
-__device__ inline T wave_sum(T v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-__device__ inline double wave_max(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-// Maximum over the 64 lanes of a non-negative float (bit patterns of
-// non-negative floats order like unsigned integers), by DPP butterflies
-// inside each row of 16 lanes and row broadcasts across rows; the result of
-// lane 63 is returned in a scalar register.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ unsigned dpp_max_step(unsigned v)
-{
-    unsigned o = (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROW_MASK, 0xf, false);
-    return o > v ? o : v;
-}
-__device__ __forceinline__ float wave_max_nonneg(float x)
-{
-    unsigned v = __float_as_uint(x);
-    v = dpp_max_step<0xb1, 0xf>(v);    // quad_perm [1,0,3,2]
-    v = dpp_max_step<0x4e, 0xf>(v);    // quad_perm [2,3,0,1]
-    v = dpp_max_step<0x141, 0xf>(v);   // row_half_mirror
-    v = dpp_max_step<0x140, 0xf>(v);   // row_mirror
-    v = dpp_max_step<0x142, 0xa>(v);   // row_bcast:15
-    v = dpp_max_step<0x143, 0xc>(v);   // row_bcast:31
-    return __uint_as_float(__builtin_amdgcn_readlane(v, 63));
-}
-
 // Neumaier-compensated accumulation (sum, compensation).
 __device__ inline void neumaier_add(double& s, double& c, double x)
 {
@@ -250,12 +161,6 @@ __device__ inline void neumaier_add(double& s, double& c, double x)
     else
         c += (x - t) + s;
     s = t;
-}
-
-__device__ inline double det3(const double* F)
-{
-    return F[0] * (F[4] * F[8] - F[5] * F[7]) - F[1] * (F[3] * F[8] - F[5] * F[6]) +
-           F[2] * (F[3] * F[7] - F[4] * F[6]);
 }
 
 // ------------------------------------------------------------------ LDS layouts
@@ -334,11 +239,6 @@ struct Lds<double> {
     }
 };
 
-size_t resident_lds_bytes(bool fp64, int64_t nf, int64_t nfib, int /*threads*/)
-{
-    return fp64 ? Lds<double>::bytes(nf, nfib) : Lds<float>::bytes(nf, nfib);
-}
-
 // Reduction slots of a workgroup: per-wave partial sums of |f_free|^2,
 // |c M v|^2, |f_bnd|^2 and (kinetic damping) the kinetic energy, and two
 // alternating slots for the time-step maximum (LDS atomic max on the bit
@@ -352,22 +252,6 @@ __device__ __forceinline__ void reset_gslots(RedSlots& red)
     }
 }
 
-__device__ __forceinline__ double readlane_d(double x, int l)
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
-    return __hiloint2double(hi, lo);
-}
-
-// Error-free sum of two doubles: s + e == a + b exactly (Knuth's two-sum;
-// symmetric in a and b).
-__device__ __forceinline__ void two_sum(double a, double b, double& s, double& e)
-{
-    s = a + b;
-    const double z = s - a;
-    e = (a - (s - z)) + (b - z);
-}
-
 // Workgroup reduction: max of gpart (>= 0) every call, and the three norms
 // when `full` (the kinetic energy too in the kinetic builds).  Inside a wave
 // the partials are added pairwise; across waves the sums are compensated:
@@ -377,15 +261,29 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
 // barrier; the max slot alternates with `parity`, the other slot is cleared
 // for the next call (at least two barriers separate a clear from the next
 // atomic on that slot).
+// The 1024-thread FP64 builds, which exceed their 128 VGPRs and are never
+// launched, keep the ds_bpermute sums.
+template <bool LDS>
+__device__ __forceinline__ double wave_sum_by(double v)
+{
+    if constexpr (LDS) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        return v;
+    } else {
+        return wave_sum(v);
+    }
+}
 template <typename Real, int NW, bool KE = false>
 __device__ __forceinline__ void block_reduce(RedSlots& red, int tid, int parity, Real gpart, double r2, double d2,
                                              double b2, bool full, double& gmax_o, double& r2_o, double& d2_o,
                                              double& b2_o, double ke = 0.0, double* ke_o = nullptr)
 {
     static_assert(NW <= 16, "at most 16 waves per workgroup");
+    constexpr bool BP = sizeof(Real) == 8 && NW == 16;
     const int lane = tid & 63, wave = tid >> 6;
     if constexpr (KE) {
-        ke = wave_sum(ke);
+        ke = wave_sum_by<BP>(ke);
         if (lane == 0) red.v[3][wave] = ke;
     }
     if constexpr (sizeof(Real) == 4) {
@@ -396,9 +294,9 @@ __device__ __forceinline__ void block_reduce(RedSlots& red, int tid, int parity,
         if (lane == 0) atomicMax(&red.g64[parity], (unsigned long long)__double_as_longlong(g));
     }
     if (full) {
-        r2 = wave_sum(r2);
-        d2 = wave_sum(d2);
-        b2 = wave_sum(b2);
+        r2 = wave_sum_by<BP>(r2);
+        d2 = wave_sum_by<BP>(d2);
+        b2 = wave_sum_by<BP>(b2);
         if (lane == 0) {
             red.v[0][wave] = r2;
             red.v[1][wave] = d2;
@@ -418,13 +316,22 @@ __device__ __forceinline__ void block_reduce(RedSlots& red, int tid, int parity,
         const int p = lane >> 4, w = lane & 15;
         const bool use = w < NW && (p == 3 ? KE : full);
         double s = use ? red.v[p][w] : 0.0, c = 0.0;
+        // (the pairs of a row's butterfly hold equal values after each stage,
+        // so the rotations of dpp_mov apply)
+        if constexpr (BP) {
 #pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-            const double so = __shfl_xor(s, off, 16), co = __shfl_xor(c, off, 16);
-            double t, e;
-            two_sum(s, so, t, e);
-            s = t;
-            c = (c + co) + e;
+            for (int off = 8; off > 0; off >>= 1) {
+                const double so = __shfl_xor(s, off, 16), co = __shfl_xor(c, off, 16);
+                double t, e;
+                two_sum(s, so, t, e);
+                s = t;
+                c = (c + co) + e;
+            }
+        } else {
+            combine_pairs<kDppRor8>(s, c);
+            combine_pairs<kDppRor4>(s, c);
+            combine_pairs<kDppXor2>(s, c);
+            combine_pairs<kDppXor1>(s, c);
         }
         const double tot = s + c;
         if (full) {
@@ -876,14 +783,16 @@ __device__ __forceinline__ void resident_solve(const SolveArgs& A, int r, char* 
                 status = ST_NONFINITE;
                 break;
             }
-            const double Rn = sqrt(R2), Dn = sqrt(D2), Bn = sqrt(B2);
-            const double tol = fmax(A.tol_abs, A.tol_rel * Bn);
-            if (Rn <= tol && Dn <= tol) break;
-            if (stagnated(A, Rn, Dn, Bn, Rref, stall)) {
-                status = ST_STAGNATED;
-                break;
+            if (test_in_reach(A, R2, B2)) {
+                const double Rn = sqrt(R2), Dn = sqrt(D2), Bn = sqrt(B2);
+                const double tol = fmax(A.tol_abs, A.tol_rel * Bn);
+                if (Rn <= tol && Dn <= tol) break;
+                if (stagnated(A, Rn, Dn, Bn, Rref, stall)) {
+                    status = ST_STAGNATED;
+                    break;
+                }
+                Rref = uniform(Rref);
             }
-            Rref = uniform(Rref);
         }
         if (!(gmax > 0.0) || !isfinite(gmax)) {
             status = ST_NONFINITE;
@@ -1660,14 +1569,16 @@ __device__ __forceinline__ void incidence_solve(const SolveArgs& A, const IncArg
                 status = ST_NONFINITE;
                 break;
             }
-            const double Rn = sqrt(R2), Dn = sqrt(D2), Bn = sqrt(B2);
-            const double tol = fmax(A.tol_abs, A.tol_rel * Bn);
-            if (Rn <= tol && Dn <= tol) break;
-            if (stagnated(A, Rn, Dn, Bn, Rref, stall)) {
-                status = ST_STAGNATED;
-                break;
+            if (test_in_reach(A, R2, B2)) {
+                const double Rn = sqrt(R2), Dn = sqrt(D2), Bn = sqrt(B2);
+                const double tol = fmax(A.tol_abs, A.tol_rel * Bn);
+                if (Rn <= tol && Dn <= tol) break;
+                if (stagnated(A, Rn, Dn, Bn, Rref, stall)) {
+                    status = ST_STAGNATED;
+                    break;
+                }
+                Rref = uniform(Rref);
             }
-            Rref = uniform(Rref);
         }
         if (!(gmax > 0.0) || !isfinite(gmax)) {
             status = ST_NONFINITE;
@@ -1993,14 +1904,16 @@ __device__ __forceinline__ void incidence_global_solve(const SolveArgs& A, const
                 status = ST_NONFINITE;
                 break;
             }
-            const double Rn = sqrt(R2), Dn = sqrt(D2), Bn = sqrt(B2);
-            const double tol = fmax(A.tol_abs, A.tol_rel * Bn);
-            if (Rn <= tol && Dn <= tol) break;
-            if (stagnated(A, Rn, Dn, Bn, Rref, stall)) {
-                status = ST_STAGNATED;
-                break;
+            if (test_in_reach(A, R2, B2)) {
+                const double Rn = sqrt(R2), Dn = sqrt(D2), Bn = sqrt(B2);
+                const double tol = fmax(A.tol_abs, A.tol_rel * Bn);
+                if (Rn <= tol && Dn <= tol) break;
+                if (stagnated(A, Rn, Dn, Bn, Rref, stall)) {
+                    status = ST_STAGNATED;
+                    break;
+                }
+                Rref = uniform(Rref);
             }
-            Rref = uniform(Rref);
         }
         if (!(gmax > 0.0) || !isfinite(gmax)) {
             status = ST_NONFINITE;
@@ -2218,63 +2131,22 @@ hipError_t launch_stress(const SolveArgs& a, int n_rve, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ launch helpers
-template <typename Real, int T, int SF, int SN, bool KIN>
-static hipError_t launch_res(const SolveArgs& a, size_t lds, int grid, hipStream_t s)
+// Private bytes of the FP64 resident builds of 768 and 1024 threads with the
+// state of dr_resident_kernel: their state does not fit the 168 or 128 VGPRs,
+// so the host finds a private segment and never launches them.
+hipError_t resident_wide_scratch_bytes(int variant, bool fp64, bool kin, size_t* bytes)
 {
-    auto k = dr_resident_kernel<Real, T, SF, SN, KIN>;
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(T), lds, s, a);
-    return hipGetLastError();
-}
-
-template <typename Real, int T, int SF, int SN, bool KIN>
-static hipError_t spill_res(size_t* bytes)
-{
-    hipFuncAttributes at;
-    hipError_t e = hipFuncGetAttributes(&at, (const void*)dr_resident_kernel<Real, T, SF, SN, KIN>);
-    *bytes = at.localSizeBytes;
-    return e;
-}
-
-template <typename Real, int T, int SF, int SN, bool KIN>
-static hipError_t occ_res(size_t lds, int* blocks)
-{
-    auto k = dr_resident_kernel<Real, T, SF, SN, KIN>;
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, (const void*)k, T, lds);
-}
-
-// precision x damping (viscous or kinetic) for one resident variant
-#define RVE_RES_PK(FN, T, SF, SN, ...)                                                                \
-    (kin ? (fp64 ? FN<double, T, SF, SN, true>(__VA_ARGS__) : FN<float, T, SF, SN, true>(__VA_ARGS__))  \
-         : (fp64 ? FN<double, T, SF, SN, false>(__VA_ARGS__) : FN<float, T, SF, SN, false>(__VA_ARGS__)))
-#define RVE_RES_DISPATCH(FN, ...)                                                                     \
-    switch (variant) {                                                                                \
-    case 0: return RVE_RES_PK(FN, 256, 4, 2, __VA_ARGS__);                                            \
-    case 1: return RVE_RES_PK(FN, 512, 4, 2, __VA_ARGS__);                                            \
-    case 2: return RVE_RES_PK(FN, 768, 4, 2, __VA_ARGS__);                                            \
-    case 3: return RVE_RES_PK(FN, 512, 6, 3, __VA_ARGS__);                                            \
-    case 4: return RVE_RES_PK(FN, 1024, 4, 2, __VA_ARGS__);                                           \
-    case 5: return RVE_RES_PK(FN, 1024, 6, 3, __VA_ARGS__);                                           \
-    default: return hipErrorInvalidValue;                                                             \
+    if (!fp64) return hipErrorInvalidValue;
+#define RVE_WIDE(T, SF, SN)                                             \
+    max_private_bytes({kin ? (const void*)dr_resident_kernel<double, T, SF, SN, true>  \
+                           : (const void*)dr_resident_kernel<double, T, SF, SN, false>}, bytes)
+    switch (variant) {
+    case 2: return RVE_WIDE(768, 4, 2);
+    case 4: return RVE_WIDE(1024, 4, 2);
+    case 5: return RVE_WIDE(1024, 6, 3);
+    default: return hipErrorInvalidValue;
     }
-
-hipError_t launch_resident(int variant, bool fp64, const SolveArgs& a, size_t lds, int grid, hipStream_t s)
-{
-    const bool kin = a.kinetic != 0;
-    RVE_RES_DISPATCH(launch_res, a, lds, grid, s)
-}
-
-hipError_t max_resident_blocks(int variant, bool fp64, bool kin, size_t lds, int* blocks)
-{
-    RVE_RES_DISPATCH(occ_res, lds, blocks)
-}
-
-hipError_t resident_scratch_bytes(int variant, bool fp64, bool kin, size_t* bytes)
-{
-    RVE_RES_DISPATCH(spill_res, bytes)
+#undef RVE_WIDE
 }
 
 template <typename Real, int T>
@@ -2293,6 +2165,7 @@ static hipError_t launch_streamed_t(const SolveArgs& a, int grid, hipStream_t s)
 hipError_t launch_streamed(bool fp64, const SolveArgs& a, int grid, int threads, hipStream_t s)
 {
     if (threads == 256) return fp64 ? launch_streamed_t<double, 256>(a, grid, s) : launch_streamed_t<float, 256>(a, grid, s);
+    if (threads == 512) return fp64 ? launch_streamed_t<double, 512>(a, grid, s) : hipErrorInvalidValue;
     return fp64 ? launch_streamed_t<double, 1024>(a, grid, s) : launch_streamed_t<float, 1024>(a, grid, s);
 }
 
@@ -2308,6 +2181,7 @@ static hipError_t streamed_private_t(bool kin, size_t* bytes)
 hipError_t streamed_scratch_bytes(bool fp64, bool kin, int threads, size_t* bytes)
 {
     if (threads == 256) return fp64 ? streamed_private_t<double, 256>(kin, bytes) : streamed_private_t<float, 256>(kin, bytes);
+    if (threads == 512 && fp64) return streamed_private_t<double, 512>(kin, bytes);
     if (threads == 1024)
         return fp64 ? streamed_private_t<double, 1024>(kin, bytes) : streamed_private_t<float, 1024>(kin, bytes);
     return hipErrorInvalidValue;
