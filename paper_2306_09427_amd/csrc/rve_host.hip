@@ -214,6 +214,18 @@ static bool variant_fits_tier(int v, int tier, bool fp64)
            resident_nodes(v, fp64) >= caps[tier].second;
 }
 
+// Streams and events of launches that run at once (forked from the batch's
+// stream and joined back to it).
+static int ensure_aux(rve_batch* b)
+{
+    for (int q = 0; q < 3; ++q) {
+        if (!b->aux[q]) HIP_TRY(hipStreamCreateWithFlags(&b->aux[q], hipStreamNonBlocking));
+        if (!b->join_ev[q]) HIP_TRY(hipEventCreateWithFlags(&b->join_ev[q], hipEventDisableTiming));
+    }
+    if (!b->fork_ev) HIP_TRY(hipEventCreateWithFlags(&b->fork_ev, hipEventDisableTiming));
+    return RVE_OK;
+}
+
 static int ensure_events(rve_batch* b, int n)
 {
     while ((int)b->ev.size() < n) {
@@ -1841,11 +1853,8 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
     for (auto& pr : rest) order.push_back(pr.second);
     const bool fork = concurrent && rest.size() > 1;
     if (fork) {
-        for (int q = 0; q < 3; ++q) {
-            if (!b->aux[q]) HIP_TRY(hipStreamCreateWithFlags(&b->aux[q], hipStreamNonBlocking));
-            if (!b->join_ev[q]) HIP_TRY(hipEventCreateWithFlags(&b->join_ev[q], hipEventDisableTiming));
-        }
-        if (!b->fork_ev) HIP_TRY(hipEventCreateWithFlags(&b->fork_ev, hipEventDisableTiming));
+        const int rc = ensure_aux(b);
+        if (rc) return rc;
     }
     // A batch of fewer RVEs than CUs leaves CUs idle: each workgroup of the
     // resident launches asks for more than half of a CU's LDS, so that none
@@ -2656,7 +2665,7 @@ static int ensure_tangent_ws(rve_batch* b, size_t slot_bytes)
 // the blocked one keeps three columns' q and d in global memory and waits
 // for its slowest column).
 static int tangent_plan(rve_batch* b, int mode, int engine, int rhs_opt, std::vector<int64_t>& gf, int* grid,
-                        int64_t* S, bool* blk, size_t* slot_bytes)
+                        int64_t* S, bool* blk, size_t* slot_off, size_t* slot_bytes)
 {
     tangent_groups(b);
     const int per = mode == 0 ? 9 : 1;
@@ -2674,6 +2683,8 @@ static int tangent_plan(rve_batch* b, int mode, int engine, int rhs_opt, std::ve
         const int64_t tasks = (gf[v + 1] - gf[v]) * per;
         grid[v] = 0;
         S[v] = 1;
+        slot_off[v] = *slot_bytes;
+        size_t bytes = 0;
         if (tasks == 0) continue;
         if (v < kNumTanRes && blk[v]) {
             int bpc = 0;
@@ -2682,21 +2693,22 @@ static int tangent_plan(rve_batch* b, int mode, int engine, int rhs_opt, std::ve
             const int64_t btasks = (gf[v + 1] - gf[v]) * (9 / kTanBlkRhs);
             grid[v] = (int)std::min<int64_t>((int64_t)bpc * b->n_cu, btasks);
             S[v] = (int64_t)kTanRes[v].threads * kTanRes[v].sn + 1;
-            *slot_bytes = std::max(*slot_bytes, 80 * (size_t)kTanBlkRhs * (size_t)S[v] * (size_t)grid[v]);
+            bytes = 80 * (size_t)kTanBlkRhs * (size_t)S[v] * (size_t)grid[v];
         } else if (v < kNumTanRes) {
             int bpc = 0;
             HIP_TRY(tangent_res_blocks(v, mode != 0, &bpc));
             if (bpc < 1) return fail(RVE_EDEVICE, "tangent kernel does not fit a compute unit");
             grid[v] = (int)std::min<int64_t>((int64_t)bpc * b->n_cu, tasks);
             S[v] = (int64_t)kTanRes[v].threads * kTanRes[v].sn + 1;
-            *slot_bytes = std::max(*slot_bytes, 64 * (size_t)S[v] * (size_t)grid[v]);
+            bytes = 64 * (size_t)S[v] * (size_t)grid[v];
         } else {
             // streamed: one 1024-thread workgroup per CU for the RVEs too large
             // for LDS, or one wavefront per task (8 per CU) on the STREAMED engine
             grid[v] = (int)std::min<int64_t>((int64_t)b->n_cu * (stream_threads == 64 ? 8 : 1), tasks);
             for (int64_t r = 0; r < b->R; ++r) S[v] = std::max<int64_t>(S[v], b->nf_of[r] + 1);
-            *slot_bytes = std::max(*slot_bytes, 128 * (size_t)S[v] * (size_t)grid[v]);
+            bytes = 128 * (size_t)S[v] * (size_t)grid[v];
         }
+        *slot_bytes += (bytes + 255) & ~size_t(255);   // the launches run at once: slots of their own
     }
     return RVE_OK;
 }
@@ -2724,7 +2736,8 @@ static int ws_layout(rve_batch* b, WsLayout& L)
             size_t sb = 0;
             for (int rhs : {0, 3}) {
                 bool blk[kNumTanRes + 1];
-                int rc = tangent_plan(b, mode, engine, rhs, gf, grid, S, blk, &sb);
+                size_t slot_off[kNumTanRes + 1];
+                int rc = tangent_plan(b, mode, engine, rhs, gf, grid, S, blk, slot_off, &sb);
                 if (rc) return rc;
                 L.slots = std::max(L.slots, sb);
             }
@@ -2845,7 +2858,8 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
     int64_t S[kNumTanRes + 1];
     size_t slot_bytes = 0;
     bool blk[kNumTanRes + 1];
-    rc = tangent_plan(b, mode, b->opts.engine, b->opts.tangent_rhs, gf, grid, S, blk, &slot_bytes);
+    size_t slot_off[kNumTanRes + 1];
+    rc = tangent_plan(b, mode, b->opts.engine, b->opts.tangent_rhs, gf, grid, S, blk, slot_off, &slot_bytes);
     if (rc) return rc;
     // largest free-node count of each launch's RVEs
     b->t_max_nf.assign(kNumTanRes + 1, 0);
@@ -2868,7 +2882,6 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
     a.out = b->t_out;
     a.status = b->t_status;
     a.iters = reinterpret_cast<unsigned long long*>(b->t_iters);
-    a.queue = b->dqueue + 60;
     a.mode = mode;
     a.law = b->opts.law;
     a.EA = b->opts.EA;
@@ -2884,29 +2897,59 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
     a.recB = b->t_recB;
     a.precond = b->t_precond;
     a.par64 = b->t_par64;
-    a.slot_ws64 = reinterpret_cast<double*>(b->t_slots);
     a.build_static = b->t_static_built ? 0 : 1;
     HIP_TRY(launch_tangent_prep(a, s));
     b->t_static_built = true;
+    HIP_TRY(launch_reset(b->dqueue, kNumTanRes + 1, s));
+    // The launches run at once on up to four streams, the most work first, so
+    // that the tail of one (its last tasks on few CUs) overlaps the others; a
+    // launch beyond four goes behind the one of least work.
+    std::vector<std::pair<int64_t, int>> order;
+    int total = 0;
     for (int v = 0; v <= kNumTanRes; ++v) {
         if (grid[v] == 0) continue;
+        int64_t w = 0;
+        for (int64_t q = gf[v]; q < gf[v + 1]; ++q) w += b->nf_of[b->t_order_host[q]];
+        order.push_back({-w, v});
+        total += (grid[v] + 7) / 8 * 8;   // workgroups go to the 8 XCDs in turn
+    }
+    std::sort(order.begin(), order.end());
+    const bool fork = order.size() > 1;
+    if (fork) {
+        rc = ensure_aux(b);
+        if (rc) return rc;
+        HIP_TRY(hipEventRecord(b->fork_ev, s));
+        for (int q = 0; q < 3; ++q) HIP_TRY(hipStreamWaitEvent(b->aux[q], b->fork_ev, 0));
+    }
+    double load[4] = {0, 0, 0, 0};
+    for (const auto& pr : order) {
+        const int v = pr.second;
+        const int lane = (int)(std::min_element(load, load + 4) - load);
+        load[lane] -= (double)pr.first;
+        hipStream_t ls = lane == 0 ? s : b->aux[lane - 1];
         // every RVE of the launch must fit its slot (and, resident, its LDS)
         const size_t need =
             (v < kNumTanRes ? (blk[v] ? 80 * (size_t)kTanBlkRhs : 64) : 128) * (size_t)S[v] * (size_t)grid[v];
-        if (need > b->t_slot_bytes || b->t_max_nf[v] >= S[v])
+        if (slot_off[v] + need > b->t_slot_bytes || b->t_max_nf[v] >= S[v])
             return fail(RVE_EINVAL, "internal: tangent slot smaller than an RVE of its group");
         a.order = b->t_order + gf[v];
         a.n_order = gf[v + 1] - gf[v];
+        a.queue = b->dqueue + v;
         a.slot_nodes = S[v];
-        a.slot_ws32 = reinterpret_cast<float4*>(b->t_slots + 48 * (size_t)S[v] * (size_t)grid[v]);
-        HIP_TRY(launch_reset(a.queue, 1, s));
+        a.slot_ws64 = reinterpret_cast<double*>(b->t_slots + slot_off[v]);
+        a.slot_ws32 = reinterpret_cast<float4*>(b->t_slots + slot_off[v] + 48 * (size_t)S[v] * (size_t)grid[v]);
         if (v < kNumTanRes && blk[v])
-            HIP_TRY(launch_tangent_blk(v, a, grid[v], s));
+            HIP_TRY(launch_tangent_blk(v, a, grid[v], ls));
         else if (v < kNumTanRes)
-            HIP_TRY(launch_tangent_res(v, a, grid[v], s));
+            HIP_TRY(launch_tangent_res(v, a, grid[v], total <= b->n_cu, ls));
         else
-            HIP_TRY(launch_tangent_stream(a, stream_threads, grid[v], s));
+            HIP_TRY(launch_tangent_stream(a, stream_threads, grid[v], ls));
     }
+    if (fork)
+        for (int q = 0; q < 3; ++q) {
+            HIP_TRY(hipEventRecord(b->join_ev[q], b->aux[q]));
+            HIP_TRY(hipStreamWaitEvent(s, b->join_ev[q], 0));
+        }
     HIP_TRY(hipMemcpyAsync(out, b->t_out, (mode == 0 ? 648 : 72) * b->R, out_kind, s));
     HIP_TRY(hipMemcpyAsync(status, b->t_status, 4 * b->R, out_kind, s));
     if (ptr_kind == RVE_PTR_HOST) HIP_TRY(hipStreamSynchronize(s));

@@ -398,7 +398,8 @@ struct TangentVariant {
 constexpr int kNumTanRes = 5;
 extern const TangentVariant kTanRes[kNumTanRes];
 hipError_t launch_tangent_prep(const TangentArgs& a, hipStream_t s);
-hipError_t launch_tangent_res(int variant, const TangentArgs& a, int grid, hipStream_t s);
+// own_cu: no two workgroups on one CU.
+hipError_t launch_tangent_res(int variant, const TangentArgs& a, int grid, bool own_cu, hipStream_t s);
 hipError_t launch_tangent_stream(const TangentArgs& a, int threads, int grid, hipStream_t s);
 hipError_t tangent_res_blocks(int variant, bool vjp, int* blocks_per_cu);
 // kin: the kinetic-damping build of the variant (launch_resident reads a.kinetic).

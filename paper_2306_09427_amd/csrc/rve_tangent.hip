@@ -38,28 +38,26 @@
 #include <stdint.h>
 
 #include "rve_internal.h"
+#include "rve_relax.h"
 #include "rve_wave.h"
 
 namespace rve {
 
 namespace {
 
-constexpr int ST_CONVERGED = 0, ST_NO_STATE = 4, ST_CG_MAXITER = 5, ST_CG_INDEFINITE = 6;
+typedef KernArgsT<TangentArgs> TanArgs;
+typedef float f32x3 __attribute__((ext_vector_type(3)));
+constexpr int ST_NO_STATE = 4, ST_CG_MAXITER = 5, ST_CG_INDEFINITE = 6;
 constexpr int kOpsThreads = 256;
-
-__device__ inline double det3(const double* F)
-{
-    return F[0] * (F[4] * F[8] - F[5] * F[7]) - F[1] * (F[3] * F[8] - F[5] * F[6]) +
-           F[2] * (F[3] * F[7] - F[4] * F[6]);
-}
 
 // ------------------------------------------------------------------ static records
 // Fills (fiber, other end) of every ELL record of RVE blockIdx.x from the CSR
 // incidence; padding records are (-1, nf).
-__global__ __launch_bounds__(kOpsThreads) void ell_build_kernel(TangentArgs A)
+__global__ __launch_bounds__(kOpsThreads) void ell_build_kernel(TangentArgs)
 {
+    TanArgs& A = *kernel_args<TangentArgs>();
     const int r = blockIdx.x;
-    const DevNet& net = A.net;
+    auto& net = A.net;
     const int64_t f0 = net.fib_off[r];
     const int64_t a0 = net.free_off[r], nf = net.free_off[r + 1] - a0;
     const int64_t cf = A.chunk_first[r], nch = A.chunk_first[r + 1] - cf;
@@ -87,11 +85,12 @@ __global__ __launch_bounds__(kOpsThreads) void ell_build_kernel(TangentArgs A)
 // One workgroup per RVE: n, a = k_t/L0, g = T/l and T of every fiber at the
 // last solve's state (FP64), then the FP32 record operators and the inverse
 // diagonal blocks of K_ff.
-__global__ __launch_bounds__(kOpsThreads) void fiber_ops_kernel(TangentArgs A)
+__global__ __launch_bounds__(kOpsThreads) void fiber_ops_kernel(TangentArgs)
 {
+    TanArgs& A = *kernel_args<TangentArgs>();
     const int r = blockIdx.x;
     if (A.solve_status[r] != 0) return;
-    const DevNet& net = A.net;
+    auto& net = A.net;
     const int64_t f0 = net.fib_off[r], nfib = net.fib_off[r + 1] - f0;
     const int64_t a0 = net.free_off[r], nf = net.free_off[r + 1] - a0;
     double F[9];
@@ -231,9 +230,9 @@ struct Ctx {
     const uint32_t* ends;
 };
 
-__device__ __forceinline__ Ctx make_ctx(const TangentArgs& A, int r)
+__device__ __forceinline__ Ctx make_ctx(TanArgs& A, int r)
 {
-    const DevNet& net = A.net;
+    auto& net = A.net;
     Ctx c;
     c.f0 = uni64(net.fib_off[r]);
     c.nfib = uni64(net.fib_off[r + 1]) - c.f0;
@@ -250,9 +249,13 @@ __device__ __forceinline__ Ctx make_ctx(const TangentArgs& A, int r)
 // thread id (opaque in the persistent kernels); the NaN is produced at the
 // store so that no constant is kept live across tasks.
 template <bool TAN>
-__device__ void no_state(const TangentArgs& A, int r, int col, int tid)
+__device__ void no_state(TanArgs& A, int r, int col, int tid)
 {
-    if (tid == 0) atomicMax(&A.status[r], ST_NO_STATE);
+    if (tid == 0) {
+        int code = ST_NO_STATE;
+        asm volatile("" : "+v"(code));
+        atomicMax(&A.status[r], code);
+    }
     if (tid < 9) {
         double nanv = NAN;
         asm volatile("" : "+v"(nanv));
@@ -266,10 +269,10 @@ __device__ void no_state(const TangentArgs& A, int r, int col, int tid)
 // Right-hand side at free node a (FP64).  Tangent: -sum s B_f (e_k d0_l),
 // s = +1 at end j, -1 at end i.  VJP: (K u)_a with u = -G x_b on fixed ends.
 template <bool TAN>
-__device__ __forceinline__ void rhs_node(const TangentArgs& A, const Ctx& c, int64_t a, int kk, int ll,
+__device__ __forceinline__ void rhs_node(TanArgs& A, const Ctx& c, int64_t a, int kk, int ll,
                                          const double* F, const double* G, double* b)
 {
-    const DevNet& net = A.net;
+    auto& net = A.net;
     b[0] = b[1] = b[2] = 0.0;
 #pragma unroll 1
     for (int64_t e = c.incoff[a]; e < c.incoff[a + 1]; ++e) {
@@ -298,7 +301,7 @@ __device__ __forceinline__ void rhs_node(const TangentArgs& A, const Ctx& c, int
 }
 
 // FP64 residual b - K x at free node a; x64 holds the solution (entry nf = 0).
-__device__ __forceinline__ void residual_node(const TangentArgs& A, const Ctx& c, int64_t a, const double* x64,
+__device__ __forceinline__ void residual_node(TanArgs& A, const Ctx& c, int64_t a, const double* x64,
                                               const double* b64, bool first, double* ra)
 {
     for (int p = 0; p < 3; ++p) ra[p] = b64[3 * a + p];
@@ -321,16 +324,18 @@ __device__ __forceinline__ void residual_node(const TangentArgs& A, const Ctx& c
 // fixed end (FP64).  acc[3p + c] collects sum_b df_b,p x_b,c + f_b,p (E Xm_b)_c
 // (tangent) or sum_b (z_b + G^T f_b)_p Xm_b,c (VJP).
 template <bool TAN>
-__device__ __forceinline__ void assembly_partial(const TangentArgs& A, const Ctx& c, int r, int kk, int ll,
+__device__ __forceinline__ void assembly_partial(TanArgs& A, const Ctx& c, int r, int kk, int ll,
                                                  const double* x64, int64_t k0, int stride, double* acc)
 {
-    const DevNet& net = A.net;
+    auto& net = A.net;
     double F[9], G[9];
     for (int k = 0; k < 9; ++k) F[k] = A.F[9 * r + k];
     if (!TAN)
         for (int k = 0; k < 9; ++k) G[k] = A.gsigma[9 * r + k];
+    double z0 = 0.0;   // opaque: no zeros are held in registers for it
+    asm volatile("" : "+v"(z0));
 #pragma unroll
-    for (int p = 0; p < 9; ++p) acc[p] = 0.0;
+    for (int p = 0; p < 9; ++p) acc[p] = z0;
 #pragma unroll 1
     for (int64_t k = k0; k < c.nfib; k += stride) {
         const uint32_t en = c.ends[k];
@@ -386,7 +391,7 @@ __device__ __forceinline__ void assembly_partial(const TangentArgs& A, const Ctx
 
 // Final outputs of a task from the summed assembly (one thread).
 template <bool TAN>
-__device__ void assembly_write(const TangentArgs& A, int r, int col, const double* acc, int status, int64_t iters)
+__device__ void assembly_write(TanArgs& A, int r, int col, const double* acc, int status, int64_t iters)
 {
     double F[9];
     for (int k = 0; k < 9; ++k) F[k] = A.F[9 * r + k];
@@ -474,7 +479,7 @@ __device__ __forceinline__ void block_sum1(CgRed& red, int parity, double& a)
 // takes ELL chunks w, w + T/64, ... and lane = node within its chunk.
 // Solver vectors live in the workgroup's global slot (any RVE size).
 template <bool TAN, int T>
-__device__ void cg_stream_task(const TangentArgs& A, int r, int col, CgRed& red)
+__device__ void cg_stream_task(TanArgs& A, int r, int col, CgRed& red)
 {
     constexpr int NW = T / 64;
     int tid = threadIdx.x;
@@ -687,8 +692,9 @@ __device__ void cg_stream_task(const TangentArgs& A, int r, int col, CgRed& red)
 }
 
 template <bool TAN, int T>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_stream_kernel(TangentArgs A)
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_stream_kernel(TangentArgs)
 {
+    TanArgs& A = *kernel_args<TangentArgs>();
     __shared__ CgRed red;
     __shared__ int task;
     constexpr int per = TAN ? 9 : 1;
@@ -703,11 +709,388 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_
     }
 }
 
+// ------------------------------------------------------------------ on-chip tasks
+// Tasks of RVEs of at most 2048 free nodes: nothing but the workgroup's sums
+// and one vector leaves the registers during the inner solve.  Thread tid owns
+// free nodes tid + T k (k < SN); each node slot keeps its first four records
+// (the chunks of nodes of degree <= 4 hold no more), its inverse block and its
+// p, r, q and d in VGPRs; p is exchanged through LDS, where the records beyond
+// four of the nodes x4 .. nf (the packing puts the degrees above 4 last) are
+// held too.  Reading the records from L2 in every iteration (24 bytes each,
+// about 250 iterations) took three quarters of an iteration.
+//
+// An iteration is bound by its serial chain: three barriers, two FP64 sums over
+// the workgroup and two FP64 quotients.  The sums of r.r and r.z share one
+// butterfly (the halves of the wave), see half_sums.  Microseconds per iteration
+// of one RVE alone, records from L2 -> here: 2.43 -> 1.64 at 183 free nodes,
+// 3.78 -> 2.42 at 790, 6.16 -> 3.95 at 1720; the 9216 columns of 1024 RVEs of 60
+// seeds: 51.9 -> 30.5 ms.
+//
+// The arithmetic, its rounding and the order of every sum are those of
+// cg_res_task.
+template <int T>
+struct ChipExtra {
+    static constexpr int XN = T / 4;   // rows of nodes: 4 records each
+    float4 A[4 * XN];                  // (n, k_t/L0 - T/l)
+    int2 B[4 * XN];                    // (LDS byte offset of the other end, bits of T/l)
+    int x4, xd;
+};
+
+// s += B_f (p - po) of one record; c = k_t/L0 - T/l
+__device__ __forceinline__ void add_record(float nx, float ny, float nz, float c, float g, const float* p, f32x3 po,
+                                           float* s)
+{
+#pragma clang fp contract(off)
+    const float dx = p[0] - po.x, dy = p[1] - po.y, dz = p[2] - po.z;
+    const float cn = c * fmaf(nz, dz, fmaf(nx, dx, ny * dy));
+    s[0] += fmaf(g, dx, cn * nx);
+    s[1] += fmaf(g, dy, cn * ny);
+    s[2] += fmaf(g, dz, cn * nz);
+}
+// z = P r, P = (00, 01, 02, 11, 12, 22)
+__device__ __forceinline__ void apply_block(const float* P, const float* r, float* z)
+{
+#pragma clang fp contract(off)
+    z[0] = fmaf(P[2], r[2], fmaf(P[1], r[1], P[0] * r[0]));
+    z[1] = fmaf(P[4], r[2], fmaf(P[3], r[1], P[1] * r[0]));
+    z[2] = fmaf(P[5], r[2], fmaf(P[2], r[0], P[4] * r[1]));
+}
+
+// Totals of a and b over the workgroup, in every thread, with one butterfly:
+// after the exchange of stage 32 the lower half of the wave holds a's sums and
+// the upper half b's; the additions are those of block_sum2.
+template <int NW>
+__device__ __forceinline__ void half_sums(CgRed& red, int parity, int tid, double& a, double& b)
+{
+    const int lane = tid & 63, wave = tid >> 6;
+    double v = halves_xor32(a, b);
+    v = add_xor16(v);
+    v += dpp_mov<kDppRor8>(v);
+    v += dpp_mov<kDppRor4>(v);
+    v += dpp_mov<kDppXor2>(v);
+    v += dpp_mov<kDppXor1>(v);
+    if ((lane & 31) == 0) red.s[parity][lane >> 5][wave] = v;
+    __syncthreads();
+    double x = 0.0;
+    const double* q = red.s[parity][lane >> 5];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) x += q[i];
+    a = readlane_d(x, 0);
+    b = readlane_d(x, 32);
+}
+
+template <bool TAN, int T, int SN>
+__device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T>& X, CgRed& red)
+{
+    constexpr int NW = T / 64;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (__builtin_amdgcn_readfirstlane(A.solve_status[r]) != 0) {
+        no_state<TAN>(A, r, col, tid);
+        return;
+    }
+    const Ctx c = make_ctx(A, r);
+    const int nf = (int)c.nf;
+    const int kk = col / 3, ll = col % 3;
+    const int64_t cf = uni64(A.chunk_first[r]);
+    const int64_t S = A.slot_nodes;
+    double* x64 = A.slot_ws64 + (int64_t)blockIdx.x * 8 * S;   // x, b (3 S each)
+    double* b64 = x64 + 3 * S;
+    const int64_t rec0 = uni64(A.chunk_rec[cf]);
+    const float4* recA = A.recA + rec0;
+    const int2* recB = A.recB + rec0;
+    int parity = 0;
+    if (tid == 0) {
+        int xd = 4;
+        asm volatile("" : "+v"(xd));
+        X.x4 = nf;
+        X.xd = xd;
+    }
+    __syncthreads();
+
+    // opaque zeros: no zero vectors are held in registers across tasks
+    double bb = 0.0;
+    float zf = 0.f;
+    asm volatile("" : "+v"(bb), "+v"(zf));
+    // right-hand side (FP64)
+    {
+        double F[9], G[9];
+        for (int k = 0; k < 9; ++k) F[k] = A.F[9 * r + k];
+        if (!TAN)
+            for (int k = 0; k < 9; ++k) G[k] = A.gsigma[9 * r + k];
+#pragma unroll 1
+        for (int k = 0; k < SN; ++k) {
+            const int a = tid + T * k;
+            if (a < nf) {
+                double b[3];
+                rhs_node<TAN>(A, c, a, kk, ll, F, G, b);
+                double zx = 0.0;
+                asm volatile("" : "+v"(zx));
+                for (int p = 0; p < 3; ++p) {
+                    b64[3 * a + p] = b[p];
+                    x64[3 * a + p] = zx;
+                }
+                bb += b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+                const int deg = (int)(c.incoff[a + 1] - c.incoff[a]);
+                if (deg > 4) {
+                    atomicMin(&X.x4, a);
+                    atomicMax(&X.xd, deg);
+                }
+            }
+        }
+        double zx = 0.0;
+        asm volatile("" : "+v"(zx));
+        if (tid < 3) x64[3 * nf + tid] = zx;
+    }
+    block_sum1<NW>(red, parity, bb);
+    parity ^= 1;
+
+    // records, blocks and extra records on chip (read once per task)
+    const int x4 = __builtin_amdgcn_readfirstlane(X.x4), nx = nf - x4;
+    const int xrows = (__builtin_amdgcn_readfirstlane(X.xd) - 1) / 4;
+    const bool xtab = xrows * nx <= ChipExtra<T>::XN;
+    float rx[SN][4], ry[SN][4], rz_[SN][4], rc[SN][4], rg[SN][4];
+    uint32_t ro[SN][2];   // LDS byte offsets of the other ends, two per word
+    float Pb[SN][6];
+    int rb[SN], wd[SN];   // first record and width of the slot's chunk (scalar width; 0 past the last node)
+#pragma unroll
+    for (int k = 0; k < SN; ++k) {
+        const int ch = wave + NW * k, a = tid + T * k;
+        rb[k] = 0;
+        wd[k] = 0;
+        float4 p0 = make_float4(zf, zf, zf, zf), p1 = p0;
+        uint32_t o4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            rx[k][u] = ry[k][u] = rz_[k][u] = rc[k][u] = rg[k][u] = zf;
+            o4[u] = 16u * (uint32_t)(T * SN);
+        }
+        if (64 * ch < nf) {
+            const int64_t c0 = uni64(A.chunk_rec[cf + ch]);
+            wd[k] = (int)((uni64(A.chunk_rec[cf + ch + 1]) - c0) >> 6);
+            rb[k] = (int)(c0 - rec0) + (tid & 63);
+            if (a < nf) {
+                p0 = A.precond[2 * (c.a0 + a)];
+                p1 = A.precond[2 * (c.a0 + a) + 1];
+            }
+            if (wd[k] > 0) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float4 ra = recA[rb[k] + 64 * u];
+                    const int2 ob = recB[rb[k] + 64 * u];
+                    rx[k][u] = ra.x; ry[k][u] = ra.y; rz_[k][u] = ra.z;
+                    rg[k][u] = __int_as_float(ob.y);
+                    rc[k][u] = ra.w - rg[k][u];
+                    o4[u] = 16u * (uint32_t)(ob.x < nf ? ob.x : T * SN);
+                }
+            }
+            if (xtab && a >= x4 && a < nf) {
+#pragma unroll 1
+                for (int j = 0; j < 4 * xrows; ++j) {
+                    float4 ra = make_float4(zf, zf, zf, zf);
+                    int2 ob = make_int2(nf, 0);
+                    if (4 + j < wd[k]) {
+                        ra = recA[rb[k] + 64 * (4 + j)];
+                        ob = recB[rb[k] + 64 * (4 + j)];
+                    }
+                    ra.w -= __int_as_float(ob.y);
+                    ob.x = 16 * (ob.x < nf ? ob.x : T * SN);
+                    X.A[j * nx + (a - x4)] = ra;
+                    X.B[j * nx + (a - x4)] = ob;
+                }
+            }
+        }
+        ro[k][0] = o4[0] | o4[1] << 16;
+        ro[k][1] = o4[2] | o4[3] << 16;
+        Pb[k][0] = p0.x; Pb[k][1] = p0.y; Pb[k][2] = p0.z; Pb[k][3] = p0.w; Pb[k][4] = p1.x; Pb[k][5] = p1.y;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    float P[SN][3], R[SN][3], Q[SN][3], D[SN][3];
+    char* zb = reinterpret_cast<char*>(zl);
+
+    int status = ST_CONVERGED;
+    // per-task copy: a kernel-lifetime value would be kept live across tasks
+    double cgt = A.cg_tol;
+    asm volatile("" : "+v"(cgt));
+    const double tol2 = uniformd(cgt * cgt);
+    const int64_t maxit = A.cg_max > 0 ? A.cg_max : 6 * (int64_t)nf + 100;
+    int64_t it_total = 0;
+    bool done = !(bb > 0.0);
+    for (int outer = 0; outer < 8 && !done; ++outer) {
+        // thread id opaque per phase: no per-thread address is hoisted out of
+        // the loops and kept live across them
+        asm volatile("" : "+v"(tid));
+        // FP64 residual of the FP64 solution (x64 complete: barrier above);
+        // d = 0, p = z = P r
+        double rr = 0.0, rz = 0.0;
+#pragma unroll
+        for (int k = 0; k < SN; ++k) {
+            const int a = tid + T * k;
+            double z0 = 0.0;   // opaque: no zeros are held in registers for it
+            asm volatile("" : "+v"(z0));
+            double ra[3] = {z0, z0, z0};
+            if (a < nf) residual_node(A, c, a, x64, b64, outer == 0, ra);
+            for (int p = 0; p < 3; ++p) R[k][p] = (float)ra[p];
+            rr += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
+            apply_block(Pb[k], R[k], P[k]);
+            rz += (double)R[k][0] * P[k][0] + (double)R[k][1] * P[k][1] + (double)R[k][2] * P[k][2];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        half_sums<NW>(red, parity, tid, rr, rz);
+        parity ^= 1;
+        if (rr <= tol2 * bb) {
+            done = true;
+            break;
+        }
+        if (it_total >= maxit) {
+            status = ST_CG_MAXITER;
+            break;
+        }
+        // inner preconditioned CG (FP32 vectors, p exchanged through LDS):
+        // q = K p, alpha = rz / p.q, d += alpha p, r -= alpha q, z = P r,
+        // beta = r.z / rz, p = z + beta p
+        double drop = 1e-6;
+        asm volatile("" : "+s"(drop));
+        const double rr0 = uniformd(drop * rr);
+#pragma unroll
+        for (int k = 0; k < SN; ++k)
+            for (int p = 0; p < 3; ++p) D[k][p] = Q[k][p] = 0.f;
+        for (;;) {
+            if (it_total >= maxit) break;
+            ++it_total;
+            asm volatile("" : "+v"(tid));
+            // the packed offsets stay packed
+#pragma unroll
+            for (int k = 0; k < SN; ++k) asm volatile("" : "+v"(ro[k][0]), "+v"(ro[k][1]));
+#pragma unroll
+            for (int k = 0; k < SN; ++k) *(f32x3*)&zl[tid + T * k] = f32x3{P[k][0], P[k][1], P[k][2]};
+            __syncthreads();
+            double pq = 0.0;
+#pragma unroll
+            for (int k = 0; k < SN; ++k) {
+                if (wd[k] > 0) {
+                    f32x3 po[4];
+                    float s[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        po[u] = *(const f32x3*)(zb + ((u & 1) ? ro[k][u >> 1] >> 16 : ro[k][u >> 1] & 0xffffu));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        add_record(rx[k][u], ry[k][u], rz_[k][u], rc[k][u], rg[k][u], P[k], po[u], s);
+                    if (wd[k] > 4) {
+                        if (xtab) {
+                            const int i = tid + T * k - x4;
+                            if (i >= 0 && i < nx) {
+#pragma unroll 1
+                                for (int j = 0; j < wd[k] - 4; j += 2) {
+                                    const float4 a0 = X.A[j * nx + i], a1 = X.A[(j + 1) * nx + i];
+                                    const int2 b0 = X.B[j * nx + i], b1 = X.B[(j + 1) * nx + i];
+                                    const f32x3 q0 = *(const f32x3*)(zb + b0.x), q1 = *(const f32x3*)(zb + b1.x);
+                                    add_record(a0.x, a0.y, a0.z, a0.w, __int_as_float(b0.y), P[k], q0, s);
+                                    add_record(a1.x, a1.y, a1.z, a1.w, __int_as_float(b1.y), P[k], q1, s);
+                                }
+                            }
+                        } else {
+#pragma unroll 1
+                            for (int j = 4; j < wd[k]; ++j) {
+                                const float4 ra = recA[rb[k] + 64 * j];
+                                const int2 ob = recB[rb[k] + 64 * j];
+                                const float g = __int_as_float(ob.y);
+                                add_record(ra.x, ra.y, ra.z, ra.w - g, g, P[k], *(const f32x3*)&zl[ob.x < nf ? ob.x : T * SN], s);
+                            }
+                        }
+                    }
+                    for (int p = 0; p < 3; ++p) Q[k][p] = s[p];
+                    pq += (double)P[k][0] * s[0] + (double)P[k][1] * s[1] + (double)P[k][2] * s[2];
+                }
+            }
+            block_sum1<NW>(red, parity, pq);
+            parity ^= 1;
+            if (!(pq > 0.0)) {
+                status = ST_CG_INDEFINITE;
+                done = true;
+                break;
+            }
+            const float af = (float)(rz / pq);
+            double rn = 0.0, rzn = 0.0;
+            float Z[SN][3];
+#pragma unroll
+            for (int k = 0; k < SN; ++k) {
+                for (int p = 0; p < 3; ++p) {
+                    D[k][p] = fmaf(af, P[k][p], D[k][p]);
+                    R[k][p] = fmaf(-af, Q[k][p], R[k][p]);
+                }
+                apply_block(Pb[k], R[k], Z[k]);
+                rn += (double)R[k][0] * R[k][0] + (double)R[k][1] * R[k][1] + (double)R[k][2] * R[k][2];
+                rzn += (double)R[k][0] * Z[k][0] + (double)R[k][1] * Z[k][1] + (double)R[k][2] * Z[k][2];
+            }
+            half_sums<NW>(red, parity, tid, rn, rzn);
+            parity ^= 1;
+            if (rn <= rr0 || rn <= 0.25 * tol2 * bb) break;
+            const float bf = (float)(rzn / rz);
+            rz = rzn;
+#pragma unroll
+            for (int k = 0; k < SN; ++k)
+                for (int p = 0; p < 3; ++p) P[k][p] = fmaf(bf, P[k][p], Z[k][p]);
+        }
+        // x += d
+        asm volatile("" : "+v"(tid));
+#pragma unroll
+        for (int k = 0; k < SN; ++k) {
+            const int a = tid + T * k;
+            if (a < nf)
+                for (int p = 0; p < 3; ++p) x64[3 * a + p] += (double)D[k][p];
+        }
+        __syncthreads();
+        if (outer == 7 && !done && status == ST_CONVERGED) status = ST_CG_MAXITER;
+    }
+
+    // assembly (x64 complete: barrier above, or no update since the RHS sum)
+    double acc[9];
+    assembly_partial<TAN>(A, c, r, kk, ll, x64, tid, T, acc);
+    double tot[9];
+#pragma unroll
+    for (int p = 0; p < 9; p += 3) {
+        double a1 = acc[p], a2 = acc[p + 1], a3 = acc[p + 2];
+        block_sum3<NW>(red, parity, a1, a2, a3);
+        parity ^= 1;
+        tot[p] = a1;
+        tot[p + 1] = a2;
+        tot[p + 2] = a3;
+    }
+    if (tid == 0) assembly_write<TAN>(A, r, col, tot, status, it_total);
+    __syncthreads();
+}
+
+template <bool TAN, int T, int SN>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_chip_kernel(TangentArgs)
+{
+    TanArgs& A = *kernel_args<TangentArgs>();
+    __shared__ float4 zl[T * SN + 1];   // the last entry stays zero
+    __shared__ ChipExtra<T> X;
+    __shared__ CgRed red;
+    __shared__ int task;
+    if (threadIdx.x == 0) zl[T * SN] = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int per = TAN ? 9 : 1;
+    const int64_t n_tasks = A.n_order * per;
+    for (;;) {
+        if (threadIdx.x == 0) task = atomicAdd(A.queue, 1);
+        __syncthreads();
+        const int t = __builtin_amdgcn_readfirstlane(task);
+        __syncthreads();
+        if (t >= n_tasks) break;
+        cg_chip_task<TAN, T, SN>(A, __builtin_amdgcn_readfirstlane(A.order[t / per]), t % per, zl, X, red);
+    }
+}
+
 // ------------------------------------------------------------------ resident tasks
 // One workgroup of T threads per task; thread tid owns free nodes
 // tid + T k (k < SN), so wavefront w owns ELL chunks w + (T/64) k.  The
-// solver vectors of the inner solve stay in registers, the vector the
-// matrix-free product gathers is exchanged through LDS.
+// residual and the product of the inner solve stay in registers, p (which the
+// matrix-free product gathers) lives in LDS, the correction d in the
+// workgroup's global slot, and z = P r is recomputed where it is needed (PL,
+// the only layout: four node slots and more leave no registers for the rest).
 //
 // The inner solve is plain preconditioned CG with a fresh product q = K p
 // every iteration: three workgroup barriers per iteration (p exchanged, p.q
@@ -715,8 +1098,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_
 // Chronopoulos-Gear update of q) lose the sign of p.Kp to FP32 cancellation
 // on these ill-conditioned systems.
 template <bool TAN, int T, int SN, bool PL>
-__device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, CgRed& red)
+__device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
 {
+    static_assert(PL, "p in LDS, d in the slot");
     constexpr int NW = T / 64;
     // thread id made opaque per task: otherwise the compiler hoists every
     // per-thread address of every slot out of the persistent task loop and
@@ -784,15 +1168,9 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
         parity ^= 1;
     }
 
-    // Register state per node slot: r and q; unless PL also z, p and d.
-    // PL (lean, for large SN): p lives only in LDS, the correction d in the
-    // workgroup's global slot (d32), and z = P r is recomputed where needed.
     float R[SN][3], Q[SN][3];
-    float Z[PL ? 1 : SN][3], P[PL ? 1 : SN][3], D[PL ? 1 : SN][3];
-    float4* d32 = reinterpret_cast<float4*>(b64 + 3 * S);   // [S] (PL only)
-    auto own_p = [&](int k) __attribute__((always_inline)) -> float4 {
-        return PL ? zl[tid + T * k] : make_float4(P[k][0], P[k][1], P[k][2], 0.f);
-    };
+    float4* d32 = reinterpret_cast<float4*>(b64 + 3 * S);   // [S]
+    auto own_p = [&](int k) __attribute__((always_inline)) -> float4 { return zl[tid + T * k]; };
     // z = P_a r for slot k (block reloaded every time: keeping the blocks of
     // all slots live across the loop costs 8 registers per slot)
     auto precond_r = [&](int k) __attribute__((always_inline)) -> float4 {
@@ -835,15 +1213,8 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
             rr += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
             const float4 z = precond_r(k);
             rz += (double)R[k][0] * z.x + (double)R[k][1] * z.y + (double)R[k][2] * z.z;
-            if (PL) {
-                zl[tid + T * k] = z;
-                if (a < nf) d32[a] = make_float4(0.f, 0.f, 0.f, 0.f);
-            } else {
-                Z[k][0] = P[k][0] = z.x;
-                Z[k][1] = P[k][1] = z.y;
-                Z[k][2] = P[k][2] = z.z;
-                D[k][0] = D[k][1] = D[k][2] = 0.f;
-            }
+            zl[tid + T * k] = z;
+            if (a < nf) d32[a] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
         {
             block_sum2<NW>(red, parity, rr, rz);
@@ -865,10 +1236,6 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
             if (it_total >= maxit) break;
             ++it_total;
             asm volatile("" : "+v"(tid));
-            if (!PL) {
-#pragma unroll
-                for (int k = 0; k < SN; ++k) zl[tid + T * k] = make_float4(P[k][0], P[k][1], P[k][2], 0.f);
-            }
             __syncthreads();
             double pq = 0.0;
 #pragma unroll
@@ -916,27 +1283,16 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
 #pragma unroll
             for (int k = 0; k < SN; ++k) {
                 const float4 pk = own_p(k);
-                if (PL) {
-                    const int64_t a = tid + T * k;
-                    if (a < nf) {
-                        float4 d = d32[a];
-                        d.x = fmaf(af, pk.x, d.x);
-                        d.y = fmaf(af, pk.y, d.y);
-                        d.z = fmaf(af, pk.z, d.z);
-                        d32[a] = d;
-                    }
-                } else {
-                    D[k][0] = fmaf(af, pk.x, D[k][0]);
-                    D[k][1] = fmaf(af, pk.y, D[k][1]);
-                    D[k][2] = fmaf(af, pk.z, D[k][2]);
+                const int64_t a = tid + T * k;
+                if (a < nf) {
+                    float4 d = d32[a];
+                    d.x = fmaf(af, pk.x, d.x);
+                    d.y = fmaf(af, pk.y, d.y);
+                    d.z = fmaf(af, pk.z, d.z);
+                    d32[a] = d;
                 }
                 for (int p = 0; p < 3; ++p) R[k][p] = fmaf(-af, Q[k][p], R[k][p]);
                 const float4 z = precond_r(k);
-                if (!PL) {
-                    Z[k][0] = z.x;
-                    Z[k][1] = z.y;
-                    Z[k][2] = z.z;
-                }
                 rn += (double)R[k][0] * R[k][0] + (double)R[k][1] * R[k][1] + (double)R[k][2] * R[k][2];
                 rzn += (double)R[k][0] * z.x + (double)R[k][1] * z.y + (double)R[k][2] * z.z;
             }
@@ -949,13 +1305,9 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
             rz = rzn;
 #pragma unroll
             for (int k = 0; k < SN; ++k) {
-                if (PL) {
-                    const float4 z = precond_r(k);
-                    const float4 pk = zl[tid + T * k];
-                    zl[tid + T * k] = make_float4(fmaf(bf, pk.x, z.x), fmaf(bf, pk.y, z.y), fmaf(bf, pk.z, z.z), 0.f);
-                } else {
-                    for (int p = 0; p < 3; ++p) P[k][p] = fmaf(bf, P[k][p], Z[k][p]);
-                }
+                const float4 z = precond_r(k);
+                const float4 pk = zl[tid + T * k];
+                zl[tid + T * k] = make_float4(fmaf(bf, pk.x, z.x), fmaf(bf, pk.y, z.y), fmaf(bf, pk.z, z.z), 0.f);
             }
         }
         // x += d
@@ -964,14 +1316,10 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
         for (int k = 0; k < SN; ++k) {
             const int64_t a = tid + T * k;
             if (a < nf) {
-                if (PL) {
-                    const float4 d = d32[a];
-                    x64[3 * a] += (double)d.x;
-                    x64[3 * a + 1] += (double)d.y;
-                    x64[3 * a + 2] += (double)d.z;
-                } else {
-                    for (int p = 0; p < 3; ++p) x64[3 * a + p] += (double)D[k][p];
-                }
+                const float4 d = d32[a];
+                x64[3 * a] += (double)d.x;
+                x64[3 * a + 1] += (double)d.y;
+                x64[3 * a + 2] += (double)d.z;
             }
         }
         __syncthreads();
@@ -996,8 +1344,9 @@ __device__ void cg_res_task(const TangentArgs& A, int r, int col, float4* zl, Cg
 }
 
 template <bool TAN, int T, int SN, bool PL>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_res_kernel(TangentArgs A)
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_res_kernel(TangentArgs)
 {
+    TanArgs& A = *kernel_args<TangentArgs>();
     extern __shared__ float4 zl[];   // [T * SN + 1]; the last entry stays zero
     __shared__ CgRed red;
     __shared__ int task;
@@ -1055,7 +1404,7 @@ __device__ __forceinline__ void block_sum_n(BlkRed& red, int parity, double (&v)
 }
 
 template <int T, int SN, int BLK_RB>
-__device__ void cg_blk_task(const TangentArgs& A, int r, int grp, float4* zl, BlkRed& red)
+__device__ void cg_blk_task(TanArgs& A, int r, int grp, float4* zl, BlkRed& red)
 {
     constexpr int NW = T / 64;
     constexpr int ZS = T * SN + 1;   // LDS entries of one column's p
@@ -1396,8 +1745,9 @@ __device__ void cg_blk_task(const TangentArgs& A, int r, int grp, float4* zl, Bl
 // Waves per SIMD WPE (registers 512 / WPE): the three columns' residuals
 // stay in registers.
 template <int T, int SN, int WPE>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(WPE))) void cg_blk_kernel(TangentArgs A)
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(WPE))) void cg_blk_kernel(TangentArgs)
 {
+    TanArgs& A = *kernel_args<TangentArgs>();
     extern __shared__ float4 zl[];   // [kBlk][T * SN + 1]; entries past an RVE's nodes stay zero
     __shared__ BlkRed red;
     __shared__ int task;
@@ -1432,9 +1782,9 @@ const void* res_fn()
 const void* res_kernel(int v, bool vjp)
 {
     switch (v) {
-    case 0: return vjp ? res_fn<false, 256, 2, false>() : res_fn<true, 256, 2, false>();
-    case 1: return vjp ? res_fn<false, 512, 2, false>() : res_fn<true, 512, 2, false>();
-    case 2: return vjp ? res_fn<false, 1024, 2, false>() : res_fn<true, 1024, 2, false>();
+    case 0: return vjp ? (const void*)cg_chip_kernel<false, 256, 2> : (const void*)cg_chip_kernel<true, 256, 2>;
+    case 1: return vjp ? (const void*)cg_chip_kernel<false, 512, 2> : (const void*)cg_chip_kernel<true, 512, 2>;
+    case 2: return vjp ? (const void*)cg_chip_kernel<false, 1024, 2> : (const void*)cg_chip_kernel<true, 1024, 2>;
     case 3: return vjp ? res_fn<false, 1024, 4, true>() : res_fn<true, 1024, 4, true>();
     default: return vjp ? res_fn<false, 1024, 8, true>() : res_fn<true, 1024, 8, true>();
     }
@@ -1472,9 +1822,10 @@ hipError_t launch_tangent_stream(const TangentArgs& a, int threads, int grid, hi
     return hipGetLastError();
 }
 
+// dynamic LDS (the on-chip builds hold theirs statically)
 static size_t res_lds(int v)
 {
-    return 16 * ((size_t)kTanRes[v].threads * kTanRes[v].sn + 1);
+    return v < 3 ? 0 : 16 * ((size_t)kTanRes[v].threads * kTanRes[v].sn + 1);
 }
 
 hipError_t tangent_res_blocks(int v, bool vjp, int* blocks_per_cu)
@@ -1486,15 +1837,17 @@ hipError_t tangent_res_blocks(int v, bool vjp, int* blocks_per_cu)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, kTanRes[v].threads, res_lds(v));
 }
 
-hipError_t launch_tangent_res(int v, const TangentArgs& a, int grid, hipStream_t s)
+hipError_t launch_tangent_res(int v, const TangentArgs& a, int grid, bool own_cu, hipStream_t s)
 {
     if (v < 0 || v >= kNumTanRes) return hipErrorInvalidValue;
     if (a.n_order <= 0) return hipSuccess;
     const void* k = res_kernel(v, a.mode != 0);
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)res_lds(v));
+    // more than half of a CU's LDS keeps a second workgroup away
+    const size_t lds = own_cu && v < 3 ? 82 * 1024 - 15 * 1024 : res_lds(v);
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     void* args[] = {const_cast<TangentArgs*>(&a)};
-    return hipLaunchKernel(k, dim3(grid), dim3(kTanRes[v].threads), args, res_lds(v), s);
+    return hipLaunchKernel(k, dim3(grid), dim3(kTanRes[v].threads), args, lds, s);
 }
 
 hipError_t tangent_res_scratch_bytes(int v, bool vjp, size_t* bytes)

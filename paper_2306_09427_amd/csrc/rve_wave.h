@@ -36,6 +36,13 @@ __device__ __forceinline__ double add_xor16(double v)
     const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
     return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
+// a(i) + a(i ^ 32) in the lanes below 32, b(i) + b(i ^ 32) in those above
+__device__ __forceinline__ double halves_xor32(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
 __device__ __forceinline__ double wave_sum(double v)
 {
     v = add_xor32(v);
