@@ -78,8 +78,11 @@ extern "C" {
                                   left by the previous solve of this batch */
 #define RVE_ENGINE_AUTO 0      /* register-resident persistent kernel where an
                                   RVE fits; beyond it the incidence kernel
-                                  (RVE_MIXED, free nodes of degree <= 16),
-                                  else the streamed persistent kernel */
+                                  (RVE_MIXED, free nodes of degree <= 16; with
+                                  viscous damping and threads_per_rve 0 spread
+                                  over 2 to 16 workgroups per RVE, the same
+                                  results bit for bit), else the streamed
+                                  persistent kernel */
 #define RVE_ENGINE_STREAMED 1  /* persistent kernel, state in global memory */
 #define RVE_ENGINE_NAIVE 2     /* one RVE at a time, one launch per step of
                                   every iteration, atomics, FP64 only */
@@ -284,7 +287,7 @@ int rve_batch_kernel_ms(rve_batch* b, double* relax_ms, double* stress_ms);
  * Kernel groups of the last solve: group_of_rve[R] receives the launch group
  * of every RVE, variant[g] its resident variant index (-1 streamed, -1 - k
  * a team of k workgroups per RVE, -100 the incidence kernel, -101 its
- * global mode) and, if
+ * global mode, each with one workgroup per RVE or several) and, if
  * the solve was profiled, ms[g] the duration of that group's relaxation
  * launch (NaN otherwise).  Arrays are host memory of max_groups entries;
  * *n_groups receives the number of groups.
@@ -473,7 +476,9 @@ int rve_batch_positions(rve_batch* b, int64_t r, double* x);
  * barrier before it gives up (default 2^24, about a second).  A launch whose
  * team gave up leaves its unfinished RVEs with status RVE_ST_NONFINITE and
  * NaN stress, and a host-pointer solve returns RVE_EDEVICE.  Mainly for
- * tests of that path (a limit of 1 poll forces it); polls >= 1.
+ * tests of that path (a limit of 1 poll forces it); polls >= 1.  The spread
+ * incidence kernel takes the same limit for each word it waits for; the RVEs
+ * of a team that gave up run on the one-workgroup incidence kernel behind it.
  */
 int rve_batch_team_spin_limit(rve_batch* b, int64_t polls);
 

@@ -159,15 +159,25 @@ struct rve_batch {
     IncArgs inc_tab{};
     bool inc_private[2][kNumInc] = {};
     bool incg_private[2] = {};         // [kinetic]: the global-mode build uses private memory
+    // spread engine: per-RVE team size (0: no partition) and exchange slots,
+    // the tables and the exchange words on the device
+    std::vector<int32_t> spread_k;
+    std::vector<int64_t> spread_xslots;
+    char* spread_mem = nullptr;
+    SpreadArgs spread_tab{};
 };
 
 // Launch-group codes beside the resident variants (>= 0): the streamed
-// kernel, teams of k workgroups per RVE (-1 - k, k >= 2) and the incidence
-// kernel.
+// kernel, teams of k workgroups per RVE (-1 - k, k >= 2), the incidence
+// kernel (one workgroup per RVE, or the spread kernel's k: -200 - k and, for the
+// RVEs of the global mode, -300 - k).
 constexpr int kStreamedGroup = -1;
 constexpr int kIncGroup = -100;
 constexpr int kIncGlobalGroup = -101;
+constexpr int kSpreadGroup = -200, kSpreadGlobalGroup = -300;
 static bool team_group(int v) { return v <= -3 && v >= -1 - kTeamMax; }
+static int spread_parts(int v) { return v < kSpreadGlobalGroup ? kSpreadGlobalGroup - v : v < kSpreadGroup ? kSpreadGroup - v : 0; }
+static bool spread_group(int v) { return spread_parts(v) > 0; }
 
 // Adaptive damping and the energy check run on the FP64 variant engine;
 // kinetic damping alone runs on the ordinary engines (their kinetic builds).
@@ -882,6 +892,291 @@ static int build_inc_tables(rve_batch* b, const HostPack& P)
     return RVE_OK;
 }
 
+// ------------------------------------------------------------------ spread tables
+// Partition of an RVE for the spread engine (layout in rve_internal.h): its
+// free nodes are halved recursively along breadth-first orders that start at a
+// node far from all others, so that the parts are compact and few fibers cross.
+struct SpreadHost {
+    std::vector<SpreadPart> parts;
+    std::vector<int64_t> part_first;             // [R], -1: none
+    std::vector<int32_t> own, xslot, halo, halo_xslot, bnd;
+    std::vector<uint16_t> oslot, bslot;          // [NINC], [NBINC]
+    std::vector<int32_t> k;                      // [R]
+    std::vector<int64_t> xslots;                 // [R]
+};
+
+// part numbers p0 .. p0 + k - 1 for the nodes of `set`
+static void spread_split(const std::vector<int32_t>& adj_off, const std::vector<int32_t>& adj, const std::vector<int32_t>& set,
+                         int p0, int k, std::vector<int32_t>& part_of, std::vector<char>& mark)
+{
+    if (k == 1) {
+        for (int32_t a : set) part_of[a] = p0;
+        return;
+    }
+    std::vector<int32_t> order;
+    // breadth-first order of the set from `start`, further components behind
+    auto bfs = [&](int32_t start) {
+        for (int32_t a : set) mark[a] = 1;
+        order.clear();
+        size_t head = 0, next = 0;
+        int32_t s0 = start;
+        for (;;) {
+            order.push_back(s0);
+            mark[s0] = 0;
+            for (; head < order.size(); ++head)
+                for (int32_t e = adj_off[order[head]]; e < adj_off[order[head] + 1]; ++e)
+                    if (mark[adj[e]]) {
+                        mark[adj[e]] = 0;
+                        order.push_back(adj[e]);
+                    }
+            while (next < set.size() && !mark[set[next]]) ++next;
+            if (next == set.size()) break;
+            s0 = set[next];
+        }
+    };
+    bfs(set[0]);
+    bfs(order.back());
+    const int k1 = k / 2;
+    const size_t n1 = order.size() * k1 / k;
+    const std::vector<int32_t> lo(order.begin(), order.begin() + n1), hi(order.begin() + n1, order.end());
+    spread_split(adj_off, adj, lo, p0, k1, part_of, mark);
+    spread_split(adj_off, adj, hi, p0 + k1, k - k1, part_of, mark);
+}
+
+// false (and nothing appended) when a part exceeds the build's slots
+static bool spread_partition(const HostPack& P, int64_t r, int k, SpreadHost& H)
+{
+    const int64_t f0 = P.fib_off[r];
+    const int64_t a0 = P.free_off[r], nf = P.free_off[r + 1] - a0;
+    const int64_t b0 = P.bnd_off[r], nb = P.bnd_off[r + 1] - b0;
+    if (nf < k || nf > (int64_t)k * kSpreadNodes) return false;
+    // the end of incidence w that is not the node itself (nf and above: boundary)
+    auto other = [&](uint32_t w) -> int64_t {
+        const uint32_t e = P.ends[f0 + (w & 0x7fffffffu)];
+        return (w >> 31) ? (e >> 16) : (e & 0xffffu);
+    };
+    std::vector<int32_t> adj_off(1, 0), adj;
+    for (int64_t a = 0; a < nf; ++a) {
+        for (int64_t e = P.inc_off[a0 + a]; e < P.inc_off[a0 + a + 1]; ++e)
+            if (other(P.inc[e]) < nf) adj.push_back((int32_t)other(P.inc[e]));
+        adj_off.push_back((int32_t)adj.size());
+    }
+    std::vector<int32_t> all(nf), part_of(nf, 0);
+    for (int64_t a = 0; a < nf; ++a) all[a] = (int32_t)a;
+    std::vector<char> mark(nf, 0);
+    spread_split(adj_off, adj, all, 0, k, part_of, mark);
+    auto deg = [&](int64_t a) { return (int)(P.inc_off[a0 + a + 1] - P.inc_off[a0 + a]); };
+    std::vector<std::vector<int32_t>> owned(k), halo(k), bnd(k);
+    for (int64_t a = 0; a < nf; ++a) owned[part_of[a]].push_back((int32_t)a);
+    // a boundary node goes to the part of its first fiber's free end, which
+    // holds the free ends of its other fibers as halo
+    for (int64_t q = 0; q < nb; ++q) {
+        int p = -1;
+        for (int64_t e = P.binc_off[b0 + q]; e < P.binc_off[b0 + q + 1]; ++e) {
+            const int64_t o = other(P.binc[e]);
+            if (o < nf && p < 0) p = part_of[o];
+        }
+        if (P.binc_off[b0 + q] == P.binc_off[b0 + q + 1]) continue;
+        if (p < 0) p = 0;
+        bnd[p].push_back((int32_t)q);
+        for (int64_t e = P.binc_off[b0 + q]; e < P.binc_off[b0 + q + 1]; ++e) {
+            const int64_t o = other(P.binc[e]);
+            if (o < nf && part_of[o] != p) halo[p].push_back((int32_t)o);
+        }
+    }
+    std::vector<char> shared(nf, 0);
+    for (int p = 0; p < k; ++p) {
+        for (int32_t a : owned[p])
+            for (int64_t e = P.inc_off[a0 + a]; e < P.inc_off[a0 + a + 1]; ++e) {
+                const int64_t o = other(P.inc[e]);
+                if (o < nf && part_of[o] != p) halo[p].push_back((int32_t)o);
+            }
+        for (int32_t a : halo[p]) shared[a] = 1;
+    }
+    // Owned nodes of degree <= 4 first; among them, and among the others, the
+    // nodes other parts need first, so that they are published early and by
+    // whole waves.  Exchange slots follow that order, a part's from a multiple
+    // of 16 (no two parts write a 128-byte line); the halo is in the order of
+    // its slots.
+    std::vector<int32_t> xslot(nf, -1);
+    int64_t nx = 0;
+    for (int p = 0; p < k; ++p) {
+        std::stable_sort(owned[p].begin(), owned[p].end(), [&](int32_t x, int32_t y) {
+            return (deg(x) > 4) != (deg(y) > 4) ? deg(y) > 4 : shared[x] > shared[y];
+        });
+        nx = (nx + 15) & ~int64_t(15);
+        for (int32_t a : owned[p])
+            if (shared[a]) xslot[a] = (int32_t)nx++;
+    }
+    nx = (nx + 15) & ~int64_t(15);
+    for (int p = 0; p < k; ++p) {
+        std::vector<int32_t>& h = halo[p];
+        std::sort(h.begin(), h.end(), [&](int32_t x, int32_t y) { return xslot[x] < xslot[y]; });
+        h.erase(std::unique(h.begin(), h.end()), h.end());
+        int x4 = 0, md = 4;
+        for (int32_t a : owned[p]) {
+            x4 += deg(a) <= 4;
+            md = std::max(md, deg(a));
+        }
+        if (owned[p].size() > (size_t)kSpreadNodes || h.size() > (size_t)kSpreadNodes ||
+            (int64_t)(md - 4) * ((int64_t)owned[p].size() - x4) > kSpreadExtra)
+            return false;
+    }
+    H.part_first[r] = (int64_t)H.parts.size();
+    H.k[r] = k;
+    H.xslots[r] = nx;
+    std::vector<int32_t> slot(nf);
+    for (int p = 0; p < k; ++p) {
+        SpreadPart sp{};
+        sp.own0 = (int64_t)H.own.size();
+        sp.halo0 = (int64_t)H.halo.size();
+        sp.bnd0 = (int64_t)H.bnd.size();
+        sp.nown = (int32_t)owned[p].size();
+        sp.nhalo = (int32_t)halo[p].size();
+        sp.nbnd = (int32_t)bnd[p].size();
+        for (size_t q = 0; q < owned[p].size(); ++q) slot[owned[p][q]] = (int32_t)q;
+        for (size_t q = 0; q < halo[p].size(); ++q) slot[halo[p][q]] = (int32_t)(kSpreadNodes + q);
+        auto slot_of = [&](uint32_t w) { return (uint16_t)(other(w) < nf ? slot[other(w)] : kSpreadZero); };
+        for (int32_t a : owned[p]) {
+            sp.x4 += deg(a) <= 4;
+            H.own.push_back(a);
+            H.xslot.push_back(xslot[a]);
+            for (int64_t e = P.inc_off[a0 + a]; e < P.inc_off[a0 + a + 1]; ++e) H.oslot[e] = slot_of(P.inc[e]);
+        }
+        for (int32_t a : halo[p]) {
+            H.halo.push_back(a);
+            H.halo_xslot.push_back(xslot[a]);
+        }
+        for (int32_t q : bnd[p]) {
+            H.bnd.push_back(q);
+            for (int64_t e = P.binc_off[b0 + q]; e < P.binc_off[b0 + q + 1]; ++e) H.bslot[e] = slot_of(P.binc[e]);
+        }
+        H.parts.push_back(sp);
+    }
+    return true;
+}
+
+static void spread_host_init(const HostPack& P, int64_t R, SpreadHost& H)
+{
+    H.part_first.assign(R, -1);
+    H.k.assign(R, 0);
+    H.xslots.assign(R, 0);
+    H.oslot.assign(P.inc.size(), (uint16_t)kSpreadZero);
+    H.bslot.assign(P.binc.size(), (uint16_t)kSpreadZero);
+}
+
+// Parts of an RVE: the fewest that hold it (a few counts only, so that RVEs of
+// like size share a launch), `grow` times as many where that is at most
+// kTeamMax.  A batch of many large RVEs takes the fewest: 512 RVEs of 1000
+// seeds relax in 0.075 us per iteration and RVE with 3 parts, 0.084 with 4,
+// 0.118 with 6 (0.081 on the one-workgroup incidence kernel); of 2000 seeds
+// 0.156 with 6, 0.184 with 8 (0.179).  A batch that leaves CUs idle takes more:
+// one RVE of 1000 seeds 6.0 us with 3 parts, 5.0 with 6, 4.5 with 12 (14.6);
+// of 2000 seeds 6.5 with 6, 5.6 with 12 (27.5).
+constexpr int kSpreadParts[] = {2, 3, 4, 6, 8, 12, 16};
+
+static bool spread_rve(const HostPack& P, int64_t r, int grow, SpreadHost& H)
+{
+    for (int k : kSpreadParts) {
+        int g = grow;
+        while (g * k > kTeamMax) g /= 2;
+        if (P.free_off[r + 1] - P.free_off[r] > (int64_t)k * kSpreadNodes) continue;
+        if (spread_partition(P, r, g * k, H) || (g > 1 && spread_partition(P, r, k, H))) return true;
+    }
+    return false;
+}
+
+// Teams of a launch of `count` RVEs.
+static int spread_teams(const rve_batch* b, int64_t count, int k)
+{
+    return (int)std::min<int64_t>(count, std::max(1, b->n_cu / k));
+}
+
+// Tables for the RVEs no FP32 resident build holds and the incidence engine
+// takes (which stands in where a team gives up), and the exchange words of the
+// largest launch.
+static int build_spread_tables(rve_batch* b, const HostPack& P)
+{
+    b->spread_k.assign(b->R, 0);
+    b->spread_xslots.assign(b->R, 0);
+    if (b->inc_mem == nullptr) return RVE_OK;
+    int per_cu = 0;
+    size_t priv = 1;
+    HIP_TRY(spread_info(&per_cu, &priv));
+    if (per_cu < 1 || priv > 0) return RVE_OK;
+    SpreadHost H;
+    try {
+        std::vector<int64_t> large;
+        for (int64_t r = 0; r < b->R; ++r)
+            if (b->inc_first[r] >= 0 && tier_of(b, r, false) < 0) large.push_back(r);
+        if (large.empty()) return RVE_OK;
+        for (int grow = 1; grow <= 4; grow *= 2) {
+            SpreadHost G;
+            spread_host_init(P, b->R, G);
+            int64_t wgs = b->R;   // one for each RVE of the other launches
+            for (int64_t r : large)
+                if (spread_rve(P, r, grow, G)) wgs += G.k[r] - 1;
+            if (grow > 1 && wgs > b->n_cu) break;
+            H = std::move(G);
+            if (2 * wgs > b->n_cu + b->R) break;   // twice as many would not fit
+        }
+    } catch (const std::bad_alloc&) {
+        return fail(RVE_ENOMEM, "host allocation failed while partitioning RVEs for the spread engine");
+    }
+    if (H.parts.empty()) return RVE_OK;
+    size_t words = 0;
+    for (int k = 2; k <= kTeamMax; ++k) {
+        int64_t mx = 0, count = 0;
+        for (int64_t r = 0; r < b->R; ++r)
+            if (H.k[r] == k) {
+                mx = std::max(mx, H.xslots[r]);
+                ++count;
+            }
+        words += 2 * (size_t)spread_teams(b, count, k) * spread_words((int)mx, k);   // (both forms, all at once)
+    }
+    DeviceArena A;
+    const size_t o_parts = A.reserve(sizeof(SpreadPart) * H.parts.size()), o_first = A.reserve(8 * (size_t)b->R),
+                 o_own = A.reserve(4 * H.own.size()), o_xs = A.reserve(4 * H.own.size()),
+                 o_halo = A.reserve(4 * H.halo.size() + 4), o_hx = A.reserve(4 * H.halo.size() + 4),
+                 o_bnd = A.reserve(4 * H.bnd.size() + 4), o_os = A.reserve(2 * H.oslot.size() + 2),
+                 o_bs = A.reserve(2 * H.bslot.size() + 2), o_x = A.reserve(8 * words);
+    if (hipMalloc((void**)&b->spread_mem, A.used + 256) != hipSuccess) {
+        b->spread_mem = nullptr;
+        return fail(RVE_ENOMEM, "device allocation of the spread tables failed");
+    }
+    char* m = b->spread_mem;
+    auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
+        return bytes ? hipMemcpy(m + off, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
+    };
+    hipError_t e = hipSuccess;
+    e = e ? e : up(o_parts, H.parts.data(), sizeof(SpreadPart) * H.parts.size());
+    e = e ? e : up(o_first, H.part_first.data(), 8 * (size_t)b->R);
+    e = e ? e : up(o_own, H.own.data(), 4 * H.own.size());
+    e = e ? e : up(o_xs, H.xslot.data(), 4 * H.xslot.size());
+    e = e ? e : up(o_halo, H.halo.data(), 4 * H.halo.size());
+    e = e ? e : up(o_hx, H.halo_xslot.data(), 4 * H.halo_xslot.size());
+    e = e ? e : up(o_bnd, H.bnd.data(), 4 * H.bnd.size());
+    e = e ? e : up(o_os, H.oslot.data(), 2 * H.oslot.size());
+    e = e ? e : up(o_bs, H.bslot.data(), 2 * H.bslot.size());
+    if (e != hipSuccess) return fail(RVE_EDEVICE, std::string("spread table upload failed: ") + hipGetErrorString(e));
+    SpreadArgs& t = b->spread_tab;
+    t.parts = carve<SpreadPart>(m, o_parts);
+    t.part_first = carve<int64_t>(m, o_first);
+    t.own = carve<int32_t>(m, o_own);
+    t.xslot = carve<int32_t>(m, o_xs);
+    t.halo = carve<int32_t>(m, o_halo);
+    t.halo_xslot = carve<int32_t>(m, o_hx);
+    t.bnd = carve<int32_t>(m, o_bnd);
+    t.oslot = carve<uint16_t>(m, o_os);
+    t.bslot = carve<uint16_t>(m, o_bs);
+    t.brec = b->inc_tab.brec;
+    t.brec_st = b->inc_tab.brec_st;
+    t.xchg = carve<unsigned long long>(m, o_x);
+    b->spread_k = H.k;
+    b->spread_xslots = H.xslots;
+    return RVE_OK;
+}
+
 // Team launches: workgroups per CU of the team build at this LDS size, and
 // the number of teams (a multiple of 8, so every team lies on one XCD).
 static int team_grid(const rve_batch* b, bool fp64, bool kin, size_t lds, int k, int* n_teams)
@@ -944,7 +1239,8 @@ static size_t team_ws_bytes(const rve_batch* b)
 // every fiber appears in the incidence of each of its ends with the sign of
 // that end.  Incidence engine: the rank permutation, the rounds and every
 // record (node, fiber, orientation, other end) of the tables the batch
-// builds.  `plant` (tests only) 1 shrinks the LDS position array by one
+// builds.  Spread engine: the partition, every position slot, extra record and
+// exchange slot.  `plant` (tests only) 1 shrinks the LDS position array by one
 // entry, 2 corrupts the other-end rank of one incidence record: mistakes the
 // replay must report.
 static int check_indexing(const rve_net_desc* net, bool fp64, int plant)
@@ -1094,6 +1390,66 @@ static int check_indexing(const rve_net_desc* net, bool fp64, int plant)
                 if (o > (uint32_t)nf || (other < nf ? (o == (uint32_t)nf || H.perm[a0 + o] != other) : o != (uint32_t)nf))
                     return bad(r, "incidence: boundary record names a wrong other end");
             }
+        }
+        // spread engine: the partition (tried on every RVE), each position slot
+        // against the node it stands for, the records beyond four of a node
+        // against the part's table, each exchange word against its owner's
+        for (int grow = 1; grow <= 4; grow *= 2) {
+            SpreadHost SH;
+            spread_host_init(P, R, SH);
+            if (!spread_rve(P, r, grow, SH)) break;
+            const int k = SH.k[r];
+            std::vector<int> owner(nf, -1), bseen(nb, 0), xused(SH.xslots[r], 0);
+            std::vector<int32_t> xs_of(nf, -1);
+            for (int p = 0; p < k; ++p) {
+                const SpreadPart& sp = SH.parts[SH.part_first[r] + p];
+                if (sp.nown > kSpreadNodes || sp.nhalo > kSpreadNodes) return bad(r, "spread: part beyond the build's slots");
+                for (int32_t q = 0; q < sp.nown; ++q) {
+                    const int32_t a = SH.own[sp.own0 + q], x = SH.xslot[sp.own0 + q];
+                    if (a < 0 || a >= nf || owner[a] >= 0) return bad(r, "spread: a node is not owned once");
+                    owner[a] = p;
+                    xs_of[a] = x;
+                    if (x >= SH.xslots[r] || (x >= 0 && xused[x]++)) return bad(r, "spread: exchange slot used twice");
+                }
+            }
+            for (int64_t a = 0; a < nf; ++a)
+                if (owner[a] < 0) return bad(r, "spread: a node is not owned once");
+            for (int p = 0; p < k; ++p) {
+                const SpreadPart& sp = SH.parts[SH.part_first[r] + p];
+                auto names = [&](uint32_t w, uint32_t o) {   // slot o stands for the other end of incidence w
+                    const uint32_t e = P.ends[f0 + (w & 0x7fffffffu)];
+                    const int64_t id = (w >> 31) ? (e >> 16) : (e & 0xffffu);
+                    if (id >= nf) return o == (uint32_t)kSpreadZero;
+                    if (o < (uint32_t)sp.nown) return SH.own[sp.own0 + o] == id;
+                    return o >= (uint32_t)kSpreadNodes && o < (uint32_t)(kSpreadNodes + sp.nhalo) &&
+                           SH.halo[sp.halo0 + o - kSpreadNodes] == id;
+                };
+                const int nx = sp.nown - sp.x4;
+                for (int32_t q = 0; q < sp.nown; ++q) {
+                    const int64_t e0 = P.inc_off[a0 + SH.own[sp.own0 + q]], e1 = P.inc_off[a0 + SH.own[sp.own0 + q] + 1];
+                    for (int64_t e = e0; e < e1; ++e) {
+                        if (!names(P.inc[e], SH.oslot[e])) return bad(r, "spread: record names a wrong other end");
+                        if (e - e0 >= 4 && (q < sp.x4 || (e - e0 - 4) * nx + (q - sp.x4) >= kSpreadExtra))
+                            return bad(r, "spread: record outside the part's table");
+                    }
+                }
+                for (int32_t q = 0; q < sp.nhalo; ++q) {
+                    const int32_t a = SH.halo[sp.halo0 + q];
+                    if (a < 0 || a >= nf || owner[a] == p || SH.halo_xslot[sp.halo0 + q] < 0 ||
+                        SH.halo_xslot[sp.halo0 + q] != xs_of[a])
+                        return bad(r, "spread: halo node without its owner's exchange slot");
+                }
+                for (int32_t q = 0; q < sp.nbnd; ++q) {
+                    const int32_t bn = SH.bnd[sp.bnd0 + q];
+                    if (bn < 0 || bn >= nb) return bad(r, "spread: boundary node outside the RVE");
+                    bseen[bn] += 1;
+                    for (int64_t e = P.binc_off[b0 + bn]; e < P.binc_off[b0 + bn + 1]; ++e)
+                        if (!names(P.binc[e], SH.bslot[e])) return bad(r, "spread: boundary record names a wrong other end");
+                }
+            }
+            for (int64_t q = 0; q < nb; ++q)
+                if (bseen[q] != (P.binc_off[b0 + q] == P.binc_off[b0 + q + 1] ? 0 : 1))
+                    return bad(r, "spread: a boundary node is not summed once");
         }
         // team engine: the partition of an RVE no FP64 resident build holds
         const int cap_f = kTeamUnit[0].threads * kTeamUnit[0].sf, cap_n = kTeamUnit[0].threads * kTeamUnit[0].sn;
@@ -1265,6 +1621,13 @@ static bool inc_rve(const rve_batch* b, int64_t r)
     return incidence_lds_mode(b->nf_of[r]) ? inc_variant(b) >= 0 : incg_ok(b);
 }
 
+// The spread kernel stands in for the incidence kernel: viscous damping, no
+// thread count asked for.
+static bool spread_options(const rve_batch* b)
+{
+    return inc_options(b) && b->opts.damping == RVE_DAMP_VISCOUS && !b->opts.threads_per_rve && b->spread_mem;
+}
+
 static void assign_groups(rve_batch* b)
 {
     b->groups.clear();
@@ -1272,9 +1635,9 @@ static void assign_groups(rve_batch* b)
     b->group_lds.clear();
     b->group_team.clear();
     const bool fp64 = b->opts.precision == RVE_FP64;
-    // [resident variants..., streamed, teams of 2..kTeamMax, incidence]
-    const int inc_slot = kNumResident + kTeamMax + 1, incg_slot = inc_slot + 1;
-    std::vector<std::vector<int32_t>> per(incg_slot + 1);
+    // [resident variants..., streamed, teams of 2..kTeamMax, incidence, spread over 2..kTeamMax (both forms)]
+    const int inc_slot = kNumResident + kTeamMax + 1, incg_slot = inc_slot + 1, spread_slot = incg_slot;
+    std::vector<std::vector<int32_t>> per(spread_slot + 2 * kTeamMax + 1);
     const int eng = b->opts.engine;
     for (int64_t r = 0; r < b->R; ++r) {
         int slot = kNumResident;   // streamed
@@ -1300,7 +1663,9 @@ static void assign_groups(rve_batch* b)
             else if (team)
                 slot = kNumResident + k;
             else if (inc)
-                slot = islot;
+                slot = eng == RVE_ENGINE_AUTO && spread_options(b) && b->spread_k[r] > 0
+                           ? spread_slot + b->spread_k[r] + (islot == incg_slot ? kTeamMax : 0)
+                           : islot;
         }
         per[slot].push_back((int32_t)r);
     }
@@ -1318,6 +1683,11 @@ static void assign_groups(rve_batch* b)
             code = kIncGroup;
         } else if (v == (size_t)incg_slot) {
             code = kIncGlobalGroup;
+        } else if (v > (size_t)spread_slot) {
+            const int k = (int)(v - spread_slot);
+            code = k > kTeamMax ? kSpreadGlobalGroup - (k - kTeamMax) : kSpreadGroup - k;
+            if (code > kSpreadGlobalGroup)   // (of the incidence kernel behind it)
+                for (int32_t r : members) lds = std::max(lds, incidence_lds_bytes(b->nf_of[r]));
         } else if (v > (size_t)kNumResident) {
             team = (int)(v - kNumResident);
             for (int32_t r : members) lds = std::max(lds, b->team_lds[fp64 ? 1 : 0][r]);
@@ -1674,6 +2044,7 @@ int rve_batch_create(const rve_net_desc* net, const rve_opts* opts, rve_batch** 
 
     rc = build_team_tables(b, P);
     if (!rc) rc = build_inc_tables(b, P);
+    if (!rc) rc = build_spread_tables(b, P);
     if (rc) {
         rve_batch_destroy(b);
         return rc;
@@ -1763,7 +2134,8 @@ int rve_batch_groups(rve_batch* b, int32_t* group_of_rve, int32_t* variant, doub
             for (int32_t r : b->groups[g]) group_of_rve[r] = g;
     const bool timed = b->ev_used == 2 * G + 2;
     for (int g = 0; g < G && g < max_groups; ++g) {
-        if (variant) variant[g] = b->group_variant[g];
+        const int v = b->group_variant[g];
+        if (variant) variant[g] = !spread_group(v) ? v : v < kSpreadGlobalGroup ? kIncGlobalGroup : kIncGroup;
         if (ms) {
             float t = NAN;
             if (timed) {
@@ -1785,6 +2157,27 @@ int rve_batch_sizes(const rve_batch* b, int64_t* n_rve, int64_t* n_nodes, int64_
     return RVE_OK;
 }
 
+
+static int launch_inc(rve_batch* b, const SolveArgs& a, const IncArgs& inc, size_t lds, hipStream_t s)
+{
+    const int iv = inc_variant(b);
+    if (iv < 0) return fail(RVE_EDEVICE, "internal: no incidence build for these options");
+    int per_cu = 1;
+    HIP_TRY(incidence_blocks(iv, a.kinetic != 0, lds, &per_cu));
+    if (per_cu < 1) return fail(RVE_EDEVICE, "incidence kernel does not fit a CU");
+    HIP_TRY(launch_incidence(iv, a, inc, lds, (int)std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list), s));
+    return RVE_OK;
+}
+
+static int launch_incg(rve_batch* b, const SolveArgs& a, const IncArgs& inc, hipStream_t s)
+{
+    if (!incg_ok(b)) return fail(RVE_EDEVICE, "internal: no global-mode incidence build for these options");
+    int per_cu = 1;
+    HIP_TRY(incidence_global_blocks(a.kinetic != 0, &per_cu));
+    if (per_cu < 1) return fail(RVE_EDEVICE, "incidence kernel (global mode) does not fit a CU");
+    HIP_TRY(launch_incidence_global(a, inc, (int)std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list), s));
+    return RVE_OK;
+}
 
 // The relaxation launches of a solve on the resident, team and streamed
 // engines: one persistent launch per kernel group (work counters queues[2 g]),
@@ -1863,7 +2256,10 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
     // XCD has a CU for its share of every launch (workgroups go to the 8 XCDs
     // in turn, launch by launch), or some would wait for one.
     int64_t per_xcd = 0;
-    for (const auto& g : b->groups) per_xcd += ((int64_t)g.size() + 7) / 8;
+    for (size_t g = 0; g < b->groups.size(); ++g) {
+        const int64_t n = (int64_t)b->groups[g].size(), k = spread_parts(b->group_variant[g]);
+        per_xcd += ((k > 0 ? k * spread_teams(b, n, (int)k) : n) + 7) / 8;
+    }
     const bool own_cu = b->R <= b->n_cu, apart = 8 * per_xcd <= b->n_cu;
     // Four launches run at once (the batch's stream and three more); a further
     // one goes behind the launch that is expected to end first: the one of
@@ -1878,6 +2274,7 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
             load[lane_of[q]] += w;
         }
     }
+    int64_t spread_used = 0;   // exchange words of the spread launches before
     for (size_t oi = 0; oi < order.size(); ++oi) {
         const size_t g = order[oi];
         hipStream_t gs_ = s;
@@ -1900,20 +2297,32 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
             const size_t own = (size_t)res_lds_total(fp64, rv.threads, rv.sf, rv.sn), want = 84 * 1024;
             HIP_TRY(launch_resident(v, fp64, a, apart && own < want ? want - own : 0, grid, gs_));
         } else if (v == kIncGroup) {
-            const int iv = inc_variant(b);
-            if (iv < 0) return fail(RVE_EDEVICE, "internal: no incidence build for these options");
-            int per_cu = 1;
-            HIP_TRY(incidence_blocks(iv, a.kinetic != 0, b->group_lds[g], &per_cu));
-            if (per_cu < 1) return fail(RVE_EDEVICE, "incidence kernel does not fit a CU");
-            int grid = std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list);
-            HIP_TRY(launch_incidence(iv, a, b->inc_tab, b->group_lds[g], grid, gs_));
+            const int rc = launch_inc(b, a, b->inc_tab, b->group_lds[g], gs_);
+            if (rc) return rc;
         } else if (v == kIncGlobalGroup) {
-            if (!incg_ok(b)) return fail(RVE_EDEVICE, "internal: no global-mode incidence build for these options");
-            int per_cu = 1;
-            HIP_TRY(incidence_global_blocks(a.kinetic != 0, &per_cu));
-            if (per_cu < 1) return fail(RVE_EDEVICE, "incidence kernel (global mode) does not fit a CU");
-            int grid = std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list);
-            HIP_TRY(launch_incidence_global(a, b->inc_tab, grid, gs_));
+            const int rc = launch_incg(b, a, b->inc_tab, gs_);
+            if (rc) return rc;
+        } else if (spread_group(v)) {
+            const int k = spread_parts(v);
+            SpreadArgs sa = b->spread_tab;
+            sa.s = a;
+            sa.k = k;
+            sa.n_teams = spread_teams(b, a.n_list, k);
+            for (int32_t r : b->groups[g]) sa.max_x = std::max<int32_t>(sa.max_x, (int32_t)b->spread_xslots[r]);
+            sa.team_words = spread_words(sa.max_x, k);
+            sa.xchg += spread_used;
+            sa.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
+            const int64_t words = (int64_t)sa.n_teams * sa.team_words;
+            spread_used += words;
+            HIP_TRY(launch_set_status(a.list, a.n_list, a.status, kStUnfinished, gs_));
+            HIP_TRY(launch_zero32(reinterpret_cast<int32_t*>(sa.xchg), 2 * words, gs_));
+            HIP_TRY(launch_spread(sa, gs_));
+            // the RVEs whose team gave up
+            IncArgs it = b->inc_tab;
+            it.only_unfinished = 1;
+            HIP_TRY(launch_reset(a.queue, 1, gs_));
+            const int rc = v < kSpreadGlobalGroup ? launch_incg(b, a, it, gs_) : launch_inc(b, a, it, b->group_lds[g], gs_);
+            if (rc) return rc;
         } else if (team_group(v)) {
             const int k = b->group_team[g];
             if (!team_ws) return fail(RVE_EWORKSPACE, "internal: no team work area");
@@ -2387,6 +2796,9 @@ int rve_batch_describe(const rve_batch* b, char* buf, size_t n)
             d += "incidence(" + std::to_string(kInc[iv].threads) + "," + std::to_string(kInc[iv].slots) + ")";
         } else if (v == kIncGlobalGroup) {
             d += "incidence(global," + std::to_string(kIncGlobalThreads) + ")";
+        } else if (spread_group(v)) {
+            d += std::string("incidence(") + (v < kSpreadGlobalGroup ? "global," : "") + std::to_string(spread_parts(v)) + "x" +
+                 std::to_string(kSpreadThreads) + ")";
         } else if (team_group(v))
             d += "team(" + std::to_string(-1 - v) + "x" + std::to_string(kTeamUnit[b->opts.precision == RVE_FP64].threads) + ")";
         else
@@ -3174,6 +3586,7 @@ void rve_batch_destroy(rve_batch* b)
     if (b->d_xm_free) (void)hipFree(b->d_xm_free);
     if (b->team_mem) (void)hipFree(b->team_mem);
     if (b->inc_mem) (void)hipFree(b->inc_mem);
+    if (b->spread_mem) (void)hipFree(b->spread_mem);
     if (b->dmem) (void)hipFree(b->dmem);
     delete b;
 }

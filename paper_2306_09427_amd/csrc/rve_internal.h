@@ -323,6 +323,7 @@ struct IncArgs {
     float4* hg;                   // (h, 1/M)
     float4* vg;                   // velocity
     float4* ag;                   // acceleration
+    int32_t only_unfinished;      // 1: only the RVEs whose status is kStUnfinished
 };
 struct IncVariant {
     int threads, slots;
@@ -342,6 +343,44 @@ hipError_t incidence_global_blocks(bool kin, int* blocks_per_cu);
 hipError_t incidence_global_scratch_bytes(bool kin, size_t* bytes);
 // whether an RVE of nf free nodes runs the LDS form (else the global mode)
 inline bool incidence_lds_mode(int64_t nf) { return nf <= kIncMaxNodes; }
+
+// Spread engine (rve_spread.hip): k workgroups per RVE, for the RVEs no
+// resident build holds (FP32, viscous damping).  Part p of an RVE owns a range
+// of its free nodes (at most kSpreadNodes) and evaluates every incidence of
+// theirs; its position slots are [owned | halo | zero slot], the halo being the
+// foreign nodes its fibers end at (at most kSpreadNodes).
+constexpr int kSpreadThreads = 512, kSpreadSlots = 4;
+constexpr int kSpreadNodes = kSpreadThreads * kSpreadSlots;
+constexpr int kSpreadExtra = 1024;   // records beyond the first four of a node, per part
+constexpr int kSpreadZero = 2 * kSpreadNodes;   // zero position slot of every part
+struct SpreadPart {
+    int64_t own0, halo0, bnd0;       // first entries in own / xslot, halo, bnd
+    int32_t nown, nhalo, nbnd, x4;   // x4: owned nodes of degree <= 4 (they come first)
+};
+struct SpreadArgs {
+    SolveArgs s;                     // network, options, outputs, work list; queue: ticket counter
+    const SpreadPart* parts;
+    const int64_t* part_first;       // [R] first part record of the RVE for this k, -1: none
+    const int32_t* own;              // packed local free-node id of each owned node
+    const int32_t* xslot;            // its exchange slot, -1 when no other part needs it
+    const int32_t* halo;             // packed local id of each halo node
+    const int32_t* halo_xslot;       // its exchange slot
+    const int32_t* bnd;              // local boundary-node id (0 .. nb - 1) of each boundary node of the part
+    const uint16_t* oslot;           // [NINC] position slot of the other end, by index in net.inc
+    const uint16_t* bslot;           // [NBINC] the same for boundary incidences
+    float4* brec;                    // [NBINC] (Dn, Qn) of the boundary incidences under the solve's F
+    const uint2* brec_st;            // [NBINC] (bits of FP32 1/L0, -)
+    unsigned long long* xchg;        // [teams][2][team_words / 2] tagged words, zero at launch
+    int32_t team_words;
+    int32_t max_x;                   // exchange slots of a team
+    int32_t k, n_teams;
+    int32_t spin_limit;              // polls of a word before a member gives up
+};
+inline int32_t spread_words(int max_x, int k) { return 2 * (3 * max_x + 7 * k); }
+constexpr int kStUnfinished = -1;    // status of an RVE a team has not finished
+hipError_t launch_spread(const SpreadArgs& a, hipStream_t s);
+hipError_t spread_info(int* blocks_per_cu, size_t* private_bytes);
+hipError_t launch_set_status(const int32_t* list, int n, int32_t* status, int32_t value, hipStream_t s);
 
 // Which register-resident variants exist (threads per RVE, fiber slots per
 // thread, free-node slots per thread).

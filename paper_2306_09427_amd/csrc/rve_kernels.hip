@@ -1623,7 +1623,9 @@ __global__ __launch_bounds__(T) void dr_incidence_kernel(SolveArgs A, IncArgs I)
         const int t = __builtin_amdgcn_readfirstlane(task);
         __syncthreads();
         if (t >= A.n_list) break;
-        incidence_solve<T, S, QR, KIN>(A, I, __builtin_amdgcn_readfirstlane(A.list[t]), smem_i, red);
+        const int r = __builtin_amdgcn_readfirstlane(A.list[t]);
+        if (I.only_unfinished && A.status[r] != kStUnfinished) continue;
+        incidence_solve<T, S, QR, KIN>(A, I, r, smem_i, red);
     }
 }
 
@@ -1956,7 +1958,9 @@ __global__ __launch_bounds__(T) void dr_incidence_global_kernel(SolveArgs A, Inc
         const int t = __builtin_amdgcn_readfirstlane(task);
         __syncthreads();
         if (t >= A.n_list) break;
-        incidence_global_solve<T, NP, QU, KIN>(A, I, __builtin_amdgcn_readfirstlane(A.list[t]), red);
+        const int r = __builtin_amdgcn_readfirstlane(A.list[t]);
+        if (I.only_unfinished && A.status[r] != kStUnfinished) continue;
+        incidence_global_solve<T, NP, QU, KIN>(A, I, r, red);
     }
 }
 

@@ -35,6 +35,7 @@
 
 #include <type_traits>
 
+#include "rve_fiber.h"
 #include "rve_internal.h"
 #include "rve_relax.h"
 #include "rve_wave.h"
@@ -57,57 +58,12 @@ struct Fiber {
     Real x, y, z, b;
 };
 
-// FP32: hardware reciprocal square root, reciprocal and exp2 (about 1 ulp
-// each).  Every rounding is spelled out (products contracted where an fma
-// stands, nowhere else), so the builds and the incidence kernel agree bit for
-// bit whatever the surrounding code.  Compression needs no second branch for
-// k_t: the clamped argument gives T_e = 0 and k_t = EA.
-// (one v_max_f32 each: fmax would quiet its operands first)
-__device__ __forceinline__ float max0(float x)
-{
-    float y;
-    asm("v_max_f32 %0, 0, %1" : "=v"(y) : "v"(x));
-    return y;
-}
-__device__ __forceinline__ float max_abs(float a, float b)   // max(a, |b|)
-{
-    float y;
-    asm("v_max_f32 %0, %1, |%2|" : "=v"(y) : "v"(a), "v"(b));
-    return y;
-}
 __device__ __forceinline__ Fiber<float> fiber_force(bool linear, float EA, float B, float EAoB, float Dx, float Dy,
                                                     float Dz, float Qn, float iL, float dhx, float dhy, float dhz)
 {
 #pragma clang fp contract(off)
-    const float ux = iL * dhx, uy = iL * dhy, uz = iL * dhz;
-    const float du = fmaf(Dz, uz, fmaf(Dx, ux, Dy * uy));
-    const float uu = fmaf(uz, uz, fmaf(ux, ux, uy * uy));
-    const float qn = Qn + fmaf(2.f, du, uu);
-    const float m = 1.f + qn;
-    const float rs = __builtin_amdgcn_rsqf(m);
-    const float eps = qn * __builtin_amdgcn_rcpf(fmaf(m, rs, 1.f));
-    float T = EA * eps, kt = EA;
-    if (!linear) {
-        // e^x - 1 for x >= 0: below 1/4 the Taylor series to x^6 (truncation
-        // under half an ulp), above it the hardware exp2 minus one
-        const float x = B * max0(eps);
-        float t = fmaf(x, 1.f / 720.f, 1.f / 120.f);
-        t = fmaf(x, t, 1.f / 24.f);
-        t = fmaf(x, t, 1.f / 6.f);
-        t = fmaf(x, t, 0.5f);
-        t = fmaf(x, t, 1.f);
-        float em1 = x * t;
-        // most waves hold no such fiber (B eps >= 1/4) most of the time
-        if (__builtin_amdgcn_ballot_w64(!(x < 0.25f)) != 0) {
-            const float big = __builtin_amdgcn_exp2f(x * 1.44269504088896341f) - 1.f;
-            em1 = x < 0.25f ? em1 : big;
-        }
-        const float Te = EAoB * em1;
-        kt = fmaf(B, Te, EA);
-        T = eps >= 0.f ? Te : T;
-    }
-    const float g = T * rs;
-    return {g * (Dx + ux), g * (Dy + uy), g * (Dz + uz), iL * max_abs(kt, g)};
+    const FiberState f = fiber_state(linear, EA, B, EAoB, Dx, Dy, Dz, Qn, iL, dhx, dhy, dhz);
+    return {f.g * f.ex, f.g * f.ey, f.g * f.ez, iL * f.b};
 }
 
 // FP64: the same chain with the library's sqrt, division and expm1 replaced
