@@ -159,25 +159,23 @@ struct rve_batch {
     IncArgs inc_tab{};
     bool inc_private[2][kNumInc] = {};
     bool incg_private[2] = {};         // [kinetic]: the global-mode build uses private memory
-    // spread engine: per-RVE team size (0: no partition) and exchange slots,
-    // the tables and the exchange words on the device
+    // spread engine: per-RVE team size (0: no partition), the tables and the exchange words on the device
     std::vector<int32_t> spread_k;
-    std::vector<int64_t> spread_xslots;
     char* spread_mem = nullptr;
+    int32_t *spread_k_dev = nullptr, *spread_rve = nullptr, *spread_first = nullptr;   // spread_k; tasks of a launch
     SpreadArgs spread_tab{};
 };
 
 // Launch-group codes beside the resident variants (>= 0): the streamed
 // kernel, teams of k workgroups per RVE (-1 - k, k >= 2), the incidence
-// kernel (one workgroup per RVE, or the spread kernel's k: -200 - k and, for the
-// RVEs of the global mode, -300 - k).
+// kernel with one workgroup per RVE and the spread kernel (one launch for both
+// of its groups; the second holds the RVEs of the global mode).
 constexpr int kStreamedGroup = -1;
 constexpr int kIncGroup = -100;
 constexpr int kIncGlobalGroup = -101;
-constexpr int kSpreadGroup = -200, kSpreadGlobalGroup = -300;
+constexpr int kSpreadGroup = -200, kSpreadGlobalGroup = -201;
 static bool team_group(int v) { return v <= -3 && v >= -1 - kTeamMax; }
-static int spread_parts(int v) { return v < kSpreadGlobalGroup ? kSpreadGlobalGroup - v : v < kSpreadGroup ? kSpreadGroup - v : 0; }
-static bool spread_group(int v) { return spread_parts(v) > 0; }
+static bool spread_group(int v) { return v == kSpreadGroup || v == kSpreadGlobalGroup; }
 
 // Adaptive damping and the energy check run on the FP64 variant engine;
 // kinetic damping alone runs on the ordinary engines (their kinetic builds).
@@ -1086,10 +1084,12 @@ static bool spread_rve(const HostPack& P, int64_t r, int grow, SpreadHost& H)
     return false;
 }
 
-// Teams of a launch of `count` RVEs.
-static int spread_teams(const rve_batch* b, int64_t count, int k)
+// Exchange areas of a launch of n tasks: all of them up to 64 MB, then the
+// tasks take turns (at least two for every team that can run at once).
+static int64_t spread_areas(const rve_batch* b, int64_t n, int64_t max_x)
 {
-    return (int)std::min<int64_t>(count, std::max(1, b->n_cu / k));
+    const int64_t fit = (int64_t(64) << 20) / (8 * (int64_t)spread_words((int)max_x));
+    return std::max<int64_t>(1, std::min(n, std::max<int64_t>(fit, b->n_cu)));
 }
 
 // Tables for the RVEs no FP32 resident build holds and the incidence engine
@@ -1098,7 +1098,6 @@ static int spread_teams(const rve_batch* b, int64_t count, int k)
 static int build_spread_tables(rve_batch* b, const HostPack& P)
 {
     b->spread_k.assign(b->R, 0);
-    b->spread_xslots.assign(b->R, 0);
     if (b->inc_mem == nullptr) return RVE_OK;
     int per_cu = 0;
     size_t priv = 1;
@@ -1124,22 +1123,19 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
         return fail(RVE_ENOMEM, "host allocation failed while partitioning RVEs for the spread engine");
     }
     if (H.parts.empty()) return RVE_OK;
-    size_t words = 0;
-    for (int k = 2; k <= kTeamMax; ++k) {
-        int64_t mx = 0, count = 0;
-        for (int64_t r = 0; r < b->R; ++r)
-            if (H.k[r] == k) {
-                mx = std::max(mx, H.xslots[r]);
-                ++count;
-            }
-        words += 2 * (size_t)spread_teams(b, count, k) * spread_words((int)mx, k);   // (both forms, all at once)
+    int64_t mx = 0, count = 0;
+    for (int64_t r = 0; r < b->R; ++r) {
+        mx = std::max(mx, H.xslots[r]);
+        count += H.k[r] > 0;
     }
+    const size_t words = (size_t)spread_areas(b, count, mx) * spread_words((int)mx);
     DeviceArena A;
     const size_t o_parts = A.reserve(sizeof(SpreadPart) * H.parts.size()), o_first = A.reserve(8 * (size_t)b->R),
                  o_own = A.reserve(4 * H.own.size()), o_xs = A.reserve(4 * H.own.size()),
                  o_halo = A.reserve(4 * H.halo.size() + 4), o_hx = A.reserve(4 * H.halo.size() + 4),
                  o_bnd = A.reserve(4 * H.bnd.size() + 4), o_os = A.reserve(2 * H.oslot.size() + 2),
-                 o_bs = A.reserve(2 * H.bslot.size() + 2), o_x = A.reserve(8 * words);
+                 o_bs = A.reserve(2 * H.bslot.size() + 2), o_x = A.reserve(8 * words), o_k = A.reserve(4 * (size_t)b->R),
+                 o_tr = A.reserve(4 * (size_t)count), o_tf = A.reserve(4 * (size_t)count + 4);
     if (hipMalloc((void**)&b->spread_mem, A.used + 256) != hipSuccess) {
         b->spread_mem = nullptr;
         return fail(RVE_ENOMEM, "device allocation of the spread tables failed");
@@ -1158,6 +1154,7 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
     e = e ? e : up(o_bnd, H.bnd.data(), 4 * H.bnd.size());
     e = e ? e : up(o_os, H.oslot.data(), 2 * H.oslot.size());
     e = e ? e : up(o_bs, H.bslot.data(), 2 * H.bslot.size());
+    e = e ? e : up(o_k, H.k.data(), 4 * H.k.size());
     if (e != hipSuccess) return fail(RVE_EDEVICE, std::string("spread table upload failed: ") + hipGetErrorString(e));
     SpreadArgs& t = b->spread_tab;
     t.parts = carve<SpreadPart>(m, o_parts);
@@ -1172,8 +1169,12 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
     t.brec = b->inc_tab.brec;
     t.brec_st = b->inc_tab.brec_st;
     t.xchg = carve<unsigned long long>(m, o_x);
+    t.max_x = (int32_t)mx;
+    t.area_words = spread_words((int)mx);
+    t.task_rve = b->spread_rve = carve<int32_t>(m, o_tr);
+    t.task_first = b->spread_first = carve<int32_t>(m, o_tf);
+    b->spread_k_dev = carve<int32_t>(m, o_k);
     b->spread_k = H.k;
-    b->spread_xslots = H.xslots;
     return RVE_OK;
 }
 
@@ -1635,9 +1636,9 @@ static void assign_groups(rve_batch* b)
     b->group_lds.clear();
     b->group_team.clear();
     const bool fp64 = b->opts.precision == RVE_FP64;
-    // [resident variants..., streamed, teams of 2..kTeamMax, incidence, spread over 2..kTeamMax (both forms)]
-    const int inc_slot = kNumResident + kTeamMax + 1, incg_slot = inc_slot + 1, spread_slot = incg_slot;
-    std::vector<std::vector<int32_t>> per(spread_slot + 2 * kTeamMax + 1);
+    // [resident variants..., streamed, teams of 2..kTeamMax, incidence, spread (both forms)]
+    const int inc_slot = kNumResident + kTeamMax + 1, incg_slot = inc_slot + 1, spread_slot = incg_slot + 1;
+    std::vector<std::vector<int32_t>> per(spread_slot + 2);
     const int eng = b->opts.engine;
     for (int64_t r = 0; r < b->R; ++r) {
         int slot = kNumResident;   // streamed
@@ -1664,7 +1665,7 @@ static void assign_groups(rve_batch* b)
                 slot = kNumResident + k;
             else if (inc)
                 slot = eng == RVE_ENGINE_AUTO && spread_options(b) && b->spread_k[r] > 0
-                           ? spread_slot + b->spread_k[r] + (islot == incg_slot ? kTeamMax : 0)
+                           ? spread_slot + (islot == incg_slot)
                            : islot;
         }
         per[slot].push_back((int32_t)r);
@@ -1683,11 +1684,11 @@ static void assign_groups(rve_batch* b)
             code = kIncGroup;
         } else if (v == (size_t)incg_slot) {
             code = kIncGlobalGroup;
-        } else if (v > (size_t)spread_slot) {
-            const int k = (int)(v - spread_slot);
-            code = k > kTeamMax ? kSpreadGlobalGroup - (k - kTeamMax) : kSpreadGroup - k;
-            if (code > kSpreadGlobalGroup)   // (of the incidence kernel behind it)
-                for (int32_t r : members) lds = std::max(lds, incidence_lds_bytes(b->nf_of[r]));
+        } else if (v == (size_t)spread_slot) {
+            for (int32_t r : members) lds = std::max(lds, incidence_lds_bytes(b->nf_of[r]));   // (the kernel behind it)
+            code = kSpreadGroup;
+        } else if (v == (size_t)spread_slot + 1) {
+            code = kSpreadGlobalGroup;
         } else if (v > (size_t)kNumResident) {
             team = (int)(v - kNumResident);
             for (int32_t r : members) lds = std::max(lds, b->team_lds[fp64 ? 1 : 0][r]);
@@ -2135,7 +2136,7 @@ int rve_batch_groups(rve_batch* b, int32_t* group_of_rve, int32_t* variant, doub
     const bool timed = b->ev_used == 2 * G + 2;
     for (int g = 0; g < G && g < max_groups; ++g) {
         const int v = b->group_variant[g];
-        if (variant) variant[g] = !spread_group(v) ? v : v < kSpreadGlobalGroup ? kIncGlobalGroup : kIncGroup;
+        if (variant) variant[g] = v == kSpreadGlobalGroup ? kIncGlobalGroup : v == kSpreadGroup ? kIncGroup : v;
         if (ms) {
             float t = NAN;
             if (timed) {
@@ -2176,6 +2177,50 @@ static int launch_incg(rve_batch* b, const SolveArgs& a, const IncArgs& inc, hip
     HIP_TRY(incidence_global_blocks(a.kinetic != 0, &per_cu));
     if (per_cu < 1) return fail(RVE_EDEVICE, "incidence kernel (global mode) does not fit a CU");
     HIP_TRY(launch_incidence_global(a, inc, (int)std::min<int64_t>((int64_t)per_cu * b->n_cu, a.n_list), s));
+    return RVE_OK;
+}
+
+// The spread launch of both of its groups (the larger RVEs first), then the
+// incidence kernels for the RVEs whose team gave up.
+static int launch_spread_groups(rve_batch* b, const SolveArgs& a, int32_t* queues, bool profile, hipStream_t s)
+{
+    int gl = -1, gg = -1;
+    for (int g = 0; g < (int)b->groups.size(); ++g) {
+        if (b->group_variant[g] == kSpreadGroup) gl = g;
+        if (b->group_variant[g] == kSpreadGlobalGroup) gg = g;
+    }
+    const int n0 = gg >= 0 ? (int)b->groups[gg].size() : 0, n1 = gl >= 0 ? (int)b->groups[gl].size() : 0;
+    const int32_t *list0 = gg >= 0 ? b->dlist + b->group_first[gg] : nullptr,
+                  *list1 = gl >= 0 ? b->dlist + b->group_first[gl] : nullptr;
+    int64_t slots = 0;
+    for (int g : {gl, gg})
+        if (g >= 0) {
+            for (int32_t r : b->groups[g]) slots += b->spread_k[r];
+            if (profile) HIP_TRY(hipEventRecord(b->ev[2 * g], s));
+        }
+    SpreadArgs sa = b->spread_tab;
+    sa.s = a;
+    sa.queue = queues + 2 * std::max(gl, gg) + 1;
+    sa.n_tasks = n0 + n1;
+    sa.n_areas = (int32_t)spread_areas(b, sa.n_tasks, sa.max_x);
+    sa.grid = (int32_t)std::min<int64_t>(slots, b->n_cu);
+    sa.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
+    HIP_TRY(launch_team_slots(list0, n0, list1, n1, b->spread_k_dev, b->spread_rve, b->spread_first, s));
+    HIP_TRY(launch_zero32(reinterpret_cast<int32_t*>(sa.xchg), 2 * (int64_t)sa.n_areas * sa.area_words, s));
+    HIP_TRY(launch_set_status(b->spread_rve, sa.n_tasks, a.status, kStUnfinished, s));
+    HIP_TRY(launch_spread(sa, s));
+    IncArgs it = b->inc_tab;
+    it.only_unfinished = 1;
+    for (int g : {gg, gl})
+        if (g >= 0) {
+            SolveArgs f = a;
+            f.list = b->dlist + b->group_first[g];
+            f.n_list = (int32_t)b->groups[g].size();
+            f.queue = queues + 2 * g;
+            const int rc = g == gg ? launch_incg(b, f, it, s) : launch_inc(b, f, it, b->group_lds[g], s);
+            if (rc) return rc;
+            if (profile) HIP_TRY(hipEventRecord(b->ev[2 * g + 1], s));
+        }
     return RVE_OK;
 }
 
@@ -2232,12 +2277,17 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
         if (team_group(b->group_variant[g])) order.push_back(g);
     const size_t n_team = order.size();
     std::vector<std::pair<int64_t, size_t>> rest;
-    for (size_t g = 0; g < b->groups.size(); ++g)
-        if (!team_group(b->group_variant[g])) {
-            int64_t w = 0;
-            for (int32_t r : b->groups[g]) w += b->nfib_of[r];
-            rest.push_back({-w, g});
-        }
+    bool spread_seen = false;
+    for (size_t g = 0; g < b->groups.size(); ++g) {
+        const bool sp = spread_group(b->group_variant[g]);
+        if (team_group(b->group_variant[g]) || (sp && spread_seen)) continue;   // (one launch for both spread groups)
+        spread_seen = spread_seen || sp;
+        int64_t w = 0;
+        for (int32_t r : b->groups[g]) w += b->nfib_of[r];
+        if (sp && g + 1 < b->groups.size())
+            for (int32_t r : b->groups[g + 1]) w += b->nfib_of[r];
+        rest.push_back({-w, g});
+    }
     std::sort(rest.begin(), rest.end());
     if (b->R <= b->n_cu)   // the largest RVEs first
         std::stable_sort(rest.begin(), rest.end(), [&](const std::pair<int64_t, size_t>& x, const std::pair<int64_t, size_t>& y) {
@@ -2257,8 +2307,12 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
     // in turn, launch by launch), or some would wait for one.
     int64_t per_xcd = 0;
     for (size_t g = 0; g < b->groups.size(); ++g) {
-        const int64_t n = (int64_t)b->groups[g].size(), k = spread_parts(b->group_variant[g]);
-        per_xcd += ((k > 0 ? k * spread_teams(b, n, (int)k) : n) + 7) / 8;
+        int64_t n = (int64_t)b->groups[g].size();
+        if (spread_group(b->group_variant[g])) {
+            n = 0;
+            for (int32_t r : b->groups[g]) n += b->spread_k[r];
+        }
+        per_xcd += (n + 7) / 8;
     }
     const bool own_cu = b->R <= b->n_cu, apart = 8 * per_xcd <= b->n_cu;
     // Four launches run at once (the batch's stream and three more); a further
@@ -2274,7 +2328,6 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
             load[lane_of[q]] += w;
         }
     }
-    int64_t spread_used = 0;   // exchange words of the spread launches before
     for (size_t oi = 0; oi < order.size(); ++oi) {
         const size_t g = order[oi];
         hipStream_t gs_ = s;
@@ -2303,25 +2356,8 @@ static int launch_groups(rve_batch* b, SolveArgs& a, int32_t* queues, void* ws_f
             const int rc = launch_incg(b, a, b->inc_tab, gs_);
             if (rc) return rc;
         } else if (spread_group(v)) {
-            const int k = spread_parts(v);
-            SpreadArgs sa = b->spread_tab;
-            sa.s = a;
-            sa.k = k;
-            sa.n_teams = spread_teams(b, a.n_list, k);
-            for (int32_t r : b->groups[g]) sa.max_x = std::max<int32_t>(sa.max_x, (int32_t)b->spread_xslots[r]);
-            sa.team_words = spread_words(sa.max_x, k);
-            sa.xchg += spread_used;
-            sa.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
-            const int64_t words = (int64_t)sa.n_teams * sa.team_words;
-            spread_used += words;
-            HIP_TRY(launch_set_status(a.list, a.n_list, a.status, kStUnfinished, gs_));
-            HIP_TRY(launch_zero32(reinterpret_cast<int32_t*>(sa.xchg), 2 * words, gs_));
-            HIP_TRY(launch_spread(sa, gs_));
-            // the RVEs whose team gave up
-            IncArgs it = b->inc_tab;
-            it.only_unfinished = 1;
-            HIP_TRY(launch_reset(a.queue, 1, gs_));
-            const int rc = v < kSpreadGlobalGroup ? launch_incg(b, a, it, gs_) : launch_inc(b, a, it, b->group_lds[g], gs_);
+            // both groups in one launch, the larger RVEs (global mode) first
+            const int rc = launch_spread_groups(b, a, queues, profile, gs_);
             if (rc) return rc;
         } else if (team_group(v)) {
             const int k = b->group_team[g];
@@ -2797,8 +2833,13 @@ int rve_batch_describe(const rve_batch* b, char* buf, size_t n)
         } else if (v == kIncGlobalGroup) {
             d += "incidence(global," + std::to_string(kIncGlobalThreads) + ")";
         } else if (spread_group(v)) {
-            d += std::string("incidence(") + (v < kSpreadGlobalGroup ? "global," : "") + std::to_string(spread_parts(v)) + "x" +
-                 std::to_string(kSpreadThreads) + ")";
+            int lo = kTeamMax, hi = 0;
+            for (int32_t r : b->groups[g]) {
+                lo = std::min(lo, (int)b->spread_k[r]);
+                hi = std::max(hi, (int)b->spread_k[r]);
+            }
+            d += std::string("incidence(") + (v == kSpreadGlobalGroup ? "global," : "") + std::to_string(lo) +
+                 (hi > lo ? "-" + std::to_string(hi) : "") + "x" + std::to_string(kSpreadThreads) + ")";
         } else if (team_group(v))
             d += "team(" + std::to_string(-1 - v) + "x" + std::to_string(kTeamUnit[b->opts.precision == RVE_FP64].threads) + ")";
         else

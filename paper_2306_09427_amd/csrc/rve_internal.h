@@ -358,9 +358,9 @@ struct SpreadPart {
     int32_t nown, nhalo, nbnd, x4;   // x4: owned nodes of degree <= 4 (they come first)
 };
 struct SpreadArgs {
-    SolveArgs s;                     // network, options, outputs, work list; queue: ticket counter
+    SolveArgs s;                     // network, options, outputs
     const SpreadPart* parts;
-    const int64_t* part_first;       // [R] first part record of the RVE for this k, -1: none
+    const int64_t* part_first;       // [R] first part record of the RVE, -1: none
     const int32_t* own;              // packed local free-node id of each owned node
     const int32_t* xslot;            // its exchange slot, -1 when no other part needs it
     const int32_t* halo;             // packed local id of each halo node
@@ -370,13 +370,19 @@ struct SpreadArgs {
     const uint16_t* bslot;           // [NBINC] the same for boundary incidences
     float4* brec;                    // [NBINC] (Dn, Qn) of the boundary incidences under the solve's F
     const uint2* brec_st;            // [NBINC] (bits of FP32 1/L0, -)
-    unsigned long long* xchg;        // [teams][2][team_words / 2] tagged words, zero at launch
-    int32_t team_words;
-    int32_t max_x;                   // exchange slots of a team
-    int32_t k, n_teams;
+    const int32_t* task_rve;         // [n_tasks] RVE of each task
+    const int32_t* task_first;       // [n_tasks + 1] first slot of each task
+    unsigned long long* xchg;        // [n_areas][area_words] tagged words, zero at launch
+    int32_t* queue;                  // slot counter
+    int32_t n_tasks, n_areas;
+    int32_t area_words;              // 16 + two halves of 3 max_x + 7 kTeamMax words
+    int32_t max_x;                   // exchange slots of an RVE
+    int32_t grid;
     int32_t spin_limit;              // polls of a word before a member gives up
 };
-inline int32_t spread_words(int max_x, int k) { return 2 * (3 * max_x + 7 * k); }
+inline int32_t spread_words(int max_x) { return 16 + 2 * (((3 * max_x + 7 * kTeamMax) + 15) & ~15); }
+hipError_t launch_team_slots(const int32_t* list0, int n0, const int32_t* list1, int n1, const int32_t* k_of,
+                             int32_t* task_rve, int32_t* task_first, hipStream_t s);
 constexpr int kStUnfinished = -1;    // status of an RVE a team has not finished
 hipError_t launch_spread(const SpreadArgs& a, hipStream_t s);
 hipError_t spread_info(int* blocks_per_cu, size_t* private_bytes);

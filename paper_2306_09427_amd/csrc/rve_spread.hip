@@ -14,25 +14,17 @@
 // time at 1700 nodes), then the exchange's round trip through memory (2.2 to 3.5
 // us), which no work can hide, as the time step needs every part's maximum.
 //
-// Exchange without fences or atomic counters: every word that crosses carries
-// its own tag, one relaxed 64-bit store of (tag << 32 | value) at device scope,
-// and a reader polls the word until the tag is the one it waits for.  Nothing
-// else is shared while an RVE runs, so no ordering between words is needed.
 // Per iteration a workgroup publishes the acceleration of the nodes other
 // parts hold as halo (three words each) and its time-step maximum (one word;
 // on test iterations its three FP64 sums in six).  A reader advances its halo
 // nodes itself, with the same operations as the owner, so nothing is exchanged
-// between the time step and the next force pass.  Two buffers alternate: a
-// workgroup writes tag n + 2 over tag n only after it has read every member's
-// word of tag n + 1, which they publish after reading tag n.  Polls are bounded
-// (spin_limit); a member that gives up leaves the RVE's status unfinished and
-// stops, the others follow at their next exchange, and the incidence kernel
-// launched behind takes every unfinished RVE.
+// between the time step and the next force pass.  A member that gives up at a
+// poll leaves the RVE's status unfinished and stops, the others follow at
+// their next exchange, and the incidence kernel launched behind takes every
+// unfinished RVE.
 //
-// Workgroups take tickets on arrival and team t is the tickets t k .. t k + k - 1,
-// so a team is complete as soon as k workgroups run, wherever they run; only
-// the last team can wait for workgroups that other kernels keep off the GPU,
-// and complete teams never wait for it.
+// One launch runs teams of every size (rve_exchange.h): as a launch per size,
+// at most four at once, 256 RVEs of 100 to 3000 seeds took 135 ms, 71 ms so.
 //
 // 512 threads of up to 256 VGPRs with four nodes each: 1024 of 128 spill.
 //
@@ -42,6 +34,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "rve_exchange.h"
 #include "rve_fiber.h"
 #include "rve_internal.h"
 #include "rve_relax.h"
@@ -52,52 +45,18 @@ namespace rve {
 namespace {
 
 typedef float f32x3 __attribute__((ext_vector_type(3)));
-typedef unsigned long long u64;
 typedef KernArgsT<SpreadArgs> Args;
 
 constexpr int T = kSpreadThreads, SN = kSpreadSlots, NW = T / 64;
 constexpr int HN = kSpreadNodes / T;   // halo nodes per thread
 constexpr int XN = kSpreadExtra;
 
-__device__ __forceinline__ void put_word(u64* p, unsigned tag, unsigned v)
-{
-    __hip_atomic_store(p, (u64)tag << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 get_word(const u64* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ bool tagged(u64 w, unsigned tag) { return (unsigned)(w >> 32) == tag; }
-
-struct SpreadRed {
+struct SpreadRed : TeamSlot {
     double v[3][16];
     double sum[3][kTeamMax];
     float g[16];
     float gmax;
-    int ticket, bad, next;
 };
-
-// Every member says that it is done with the RVE and waits for the others
-// (their last reads of its words are then over); the first one's word carries
-// the team's next RVE.  False when a poll gave up.
-__device__ __forceinline__ bool team_done(Args& A, u64* xbuf, int rank, unsigned& tag, SpreadRed& red)
-{
-    __syncthreads();
-    ++tag;
-    const int k = A.k, t = threadIdx.x;
-    u64* const words = xbuf + (tag & 1) * (A.team_words / 2) + 3 * (int64_t)A.max_x;
-    if (t == 0) put_word(words + rank, tag, rank == 0 ? (unsigned)(A.n_teams + atomicAdd(A.s.queue + 1, 1)) : 0u);
-    if (t < k) {
-        int polls = 0;
-        const int limit = A.spin_limit;
-        u64 v = get_word(words + t);
-        while (!tagged(v, tag) && ++polls < limit) v = get_word(words + t);
-        if (!tagged(v, tag)) red.bad = 1;
-        if (t == 0) red.next = (int)(unsigned)v;
-    }
-    __syncthreads();
-    return uniform32(red.bad) == 0;
-}
 
 // (Dn, Qn, 1/L0) of one incidence under F, the fiber oriented so that the node
 // is its end j; formed in FP64 (inc_record in rve_kernels.hip).
@@ -116,11 +75,12 @@ __device__ __forceinline__ void record_of(const double* F, const Net& net, int64
     iL = (float)il;
 }
 
-// One RVE.  `tag` is the last exchange's tag (every member of the team counts
-// alike); returns false when a poll gave up.
-__device__ __forceinline__ bool spread_solve(Args& A, int r, int team, int rank, unsigned& tag, f32x3* H, f32x3* W, float4* XA,
-                                             uint2* XB, SpreadRed& red)
+// One RVE; returns false when a poll gave up.
+__device__ __forceinline__ bool spread_solve(Args& A, int r, Team& tm, f32x3* H, f32x3* W, float4* XA, uint2* XB,
+                                             SpreadRed& red)
 {
+    unsigned& tag = tm.tag;
+    const int rank = tm.rank, k = tm.k;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int wave64 = uniform32(tid & ~63);
@@ -130,9 +90,9 @@ __device__ __forceinline__ bool spread_solve(Args& A, int r, int team, int rank,
     const int nown = uniform32(A.parts[pi].nown), nhalo = uniform32(A.parts[pi].nhalo);
     const int x4 = uniform32(A.parts[pi].x4);
     const int64_t own0 = uniform64(A.parts[pi].own0), halo0 = uniform64(A.parts[pi].halo0);
-    const int k = A.k, max_x = A.max_x;
-    u64* const xbuf = A.xchg + (int64_t)team * A.team_words;
-    const int half = A.team_words / 2;
+    const int max_x = A.max_x, half = (A.area_words - 16) / 2;
+    u64* const xbuf = tm.area + 16;
+    auto words_of = [&](unsigned t) __attribute__((always_inline)) { return xbuf + (t & 1) * half + 3 * (int64_t)max_x; };
 
     double F[9];
     bool finite = true;
@@ -148,7 +108,8 @@ __device__ __forceinline__ bool spread_solve(Args& A, int r, int team, int rank,
             A.s.Rres[r] = NAN; A.s.Dres[r] = NAN; A.s.Bres[r] = NAN;
             for (int q = 0; q < 9; ++q) A.s.sigma[9 * r + q] = NAN;
         }
-        return team_done(A, xbuf, rank, tag, red);
+        ++tag;
+        return team_done(A, red, tm, words_of(tag));
     }
     const bool linear = A.s.law == kLawLinear;
     const float EA = uniform((float)A.s.EA), Bc = uniform((float)A.s.B), EAoB = uniform((float)(A.s.EA / A.s.B));
@@ -336,7 +297,7 @@ __device__ __forceinline__ bool spread_solve(Args& A, int r, int team, int rank,
             }
         }
         __syncthreads();
-        u64* const words = xbuf + (tag & 1) * half + 3 * (int64_t)max_x;   // [k] maxima, [k][3][2] sums
+        u64* const words = words_of(tag);   // [k] maxima, [k][3][2] sums
         int polls = 0;
         const int limit = kernel_args<SpreadArgs>()->spin_limit;
         bool ok = true;
@@ -541,7 +502,8 @@ __device__ __forceinline__ bool spread_solve(Args& A, int r, int team, int rank,
             h[0] = (double)hx[s]; h[1] = (double)hy[s]; h[2] = (double)hz[s];
         }
     }
-    const bool all = team_done(*K, xbuf, rank, tag, red);
+    ++tag;
+    const bool all = team_done(*K, red, tm, words_of(tag));
     if (te == 0 && rank == 0 && all) {
         K->s.status[r] = status;
         K->s.iters[r] = n;
@@ -560,17 +522,39 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(2))) void dr_
     __shared__ uint2 XB[XN];
     __shared__ SpreadRed red;
     auto& A = *kernel_args<SpreadArgs>();
-    if (threadIdx.x == 0) {
-        red.ticket = atomicAdd(A.s.queue, 1);
-        red.bad = 0;
-    }
+    if (threadIdx.x == 0) red.bad = 0;
     if (threadIdx.x < 16) red.g[threadIdx.x] = 0.f;   // (a row of the maximum's tree; NW of them are written)
-    __syncthreads();
-    const int ticket = uniform32(red.ticket);
-    const int team = ticket / A.k, rank = ticket - team * A.k;
-    unsigned tag = 0;
-    for (int q = team; q < A.s.n_list; q = uniform32(red.next)) {
-        if (!spread_solve(*kernel_args<SpreadArgs>(), uniform32(A.s.list[q]), team, rank, tag, H, W, XA, XB, red)) break;
+    Team tm;
+    while (team_take(A, red, tm))
+        if (!spread_solve(*kernel_args<SpreadArgs>(), uniform32(kernel_args<SpreadArgs>()->task_rve[tm.task]), tm, H, W, XA, XB, red))
+            break;
+}
+
+// Tasks of a launch, list0 then list1, and the first slot of each (k slots per
+// task).  One workgroup.
+__global__ __launch_bounds__(1024) void team_slots(const int32_t* list0, int n0, const int32_t* list1, int n1,
+                                                   const int32_t* k_of, int32_t* task_rve, int32_t* task_first)
+{
+    __shared__ int part[16], base;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, n = n0 + n1;
+    if (t == 0) base = 0;
+    for (int q0 = 0; q0 <= n; q0 += 1024) {
+        const int q = q0 + t;
+        const int r = q < n0 ? list0[q] : q < n ? list1[q - n0] : -1, k = r >= 0 ? k_of[r] : 0;
+        int x = k;
+        for (int d = 1; d < 64; d *= 2) {
+            const int y = __shfl_up(x, d);
+            x += lane >= d ? y : 0;
+        }
+        if (lane == 63) part[wave] = x;
+        __syncthreads();
+        int b = base;
+        for (int w = 0; w < wave; ++w) b += part[w];
+        if (q <= n) task_first[q] = b + x - k;
+        if (r >= 0) task_rve[q] = r;
+        __syncthreads();
+        if (t == 1023) base = b + x;
+        __syncthreads();
     }
 }
 
@@ -584,8 +568,15 @@ __global__ void set_status(const int32_t* list, int n, int32_t* status, int32_t 
 
 hipError_t launch_spread(const SpreadArgs& a, hipStream_t s)
 {
-    if (a.s.n_list <= 0) return hipSuccess;
-    hipLaunchKernelGGL(dr_spread_kernel, dim3((unsigned)(a.n_teams * a.k)), dim3(T), 0, s, a);
+    if (a.n_tasks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(dr_spread_kernel, dim3((unsigned)a.grid), dim3(T), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_team_slots(const int32_t* list0, int n0, const int32_t* list1, int n1, const int32_t* k_of,
+                             int32_t* task_rve, int32_t* task_first, hipStream_t s)
+{
+    hipLaunchKernelGGL(team_slots, dim3(1), dim3(1024), 0, s, list0, n0, list1, n1, k_of, task_rve, task_first);
     return hipGetLastError();
 }
 
@@ -600,7 +591,7 @@ hipError_t spread_info(int* blocks_per_cu, size_t* private_bytes)
 {
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void*)dr_spread_kernel, T, 0);
     if (e != hipSuccess) return e;
-    return max_private_bytes({(const void*)dr_spread_kernel, (const void*)set_status}, private_bytes);
+    return max_private_bytes({(const void*)dr_spread_kernel, (const void*)team_slots, (const void*)set_status}, private_bytes);
 }
 
 }  // namespace rve
