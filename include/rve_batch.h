@@ -479,6 +479,8 @@ int rve_batch_positions(rve_batch* b, int64_t r, double* x);
  * tests of that path (a limit of 1 poll forces it); polls >= 1.  The spread
  * incidence kernel takes the same limit for each word it waits for; the RVEs
  * of a team that gave up run on the one-workgroup incidence kernel behind it.
+ * Tangents and VJPs of RVEs beyond 4096 free nodes run on such teams too, with
+ * the streamed kernel behind.
  */
 int rve_batch_team_spin_limit(rve_batch* b, int64_t polls);
 

@@ -102,7 +102,9 @@ struct rve_batch {
     int32_t* t_status = nullptr;
     int64_t* t_iters = nullptr;
     int32_t* t_order = nullptr;
-    std::vector<int64_t> t_group_first;   // [kNumTanRes + 2] offsets of the task groups in t_order
+    int32_t* t_spread_first = nullptr;    // first slots of the spread tasks (tangent, VJP), then their marks
+    int64_t t_spread_slots[2] = {0, 0};   // slots of a tangent, of a VJP
+    std::vector<int64_t> t_group_first;   // [kTanGroups + 1] offsets of the task groups in t_order
     std::vector<int32_t> t_order_host;    // host copy of t_order
     std::vector<int64_t> t_max_nf;        // per launch of the last call: largest free-node count
     char* t_slots = nullptr;           // per-wavefront solver vectors
@@ -161,6 +163,8 @@ struct rve_batch {
     bool incg_private[2] = {};         // [kinetic]: the global-mode build uses private memory
     // spread engine: per-RVE team size (0: no partition), the tables and the exchange words on the device
     std::vector<int32_t> spread_k;
+    int64_t spread_areas = 0;          // exchange areas held
+    bool t_spread_ok = false;          // the spread tangent may run
     char* spread_mem = nullptr;
     int32_t *spread_k_dev = nullptr, *spread_rve = nullptr, *spread_first = nullptr;   // spread_k; tasks of a launch
     SpreadArgs spread_tab{};
@@ -1007,6 +1011,7 @@ static bool spread_partition(const HostPack& P, int64_t r, int k, SpreadHost& H)
             if (shared[a]) xslot[a] = (int32_t)nx++;
     }
     nx = (nx + 15) & ~int64_t(15);
+    if (nx >= 0xffff) return false;   // (16-bit slots in the spread tangent)
     for (int p = 0; p < k; ++p) {
         std::vector<int32_t>& h = halo[p];
         std::sort(h.begin(), h.end(), [&](int32_t x, int32_t y) { return xslot[x] < xslot[y]; });
@@ -1128,7 +1133,8 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
         mx = std::max(mx, H.xslots[r]);
         count += H.k[r] > 0;
     }
-    const size_t words = (size_t)spread_areas(b, count, mx) * spread_words((int)mx);
+    const int64_t areas = spread_areas(b, 9 * count, mx);   // (a tangent has nine tasks per RVE)
+    const size_t words = (size_t)areas * spread_words((int)mx);
     DeviceArena A;
     const size_t o_parts = A.reserve(sizeof(SpreadPart) * H.parts.size()), o_first = A.reserve(8 * (size_t)b->R),
                  o_own = A.reserve(4 * H.own.size()), o_xs = A.reserve(4 * H.own.size()),
@@ -1175,6 +1181,7 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
     t.task_first = b->spread_first = carve<int32_t>(m, o_tf);
     b->spread_k_dev = carve<int32_t>(m, o_k);
     b->spread_k = H.k;
+    b->spread_areas = areas;
     return RVE_OK;
 }
 
@@ -1918,6 +1925,11 @@ int rve_batch_create(const rve_net_desc* net, const rve_opts* opts, rve_batch** 
             if (tangent_res_scratch_bytes(v, m == 1, &sb) != hipSuccess) sb = 1;
             b->tangent_private[m][v] = sb > 0;
         }
+    {
+        int per_cu = 0;
+        size_t sb = 1;
+        b->t_spread_ok = tangent_spread_info(&per_cu, &sb) == hipSuccess && per_cu >= 1 && sb == 0;
+    }
     for (int v = 0; v < kNumTanBlk; ++v) {
         size_t sb = 1;
         if (tangent_blk_scratch_bytes(v, &sb) != hipSuccess) sb = 1;
@@ -2202,7 +2214,7 @@ static int launch_spread_groups(rve_batch* b, const SolveArgs& a, int32_t* queue
     sa.s = a;
     sa.queue = queues + 2 * std::max(gl, gg) + 1;
     sa.n_tasks = n0 + n1;
-    sa.n_areas = (int32_t)spread_areas(b, sa.n_tasks, sa.max_x);
+    sa.n_areas = (int32_t)std::min<int64_t>(sa.n_tasks, b->spread_areas);
     sa.grid = (int32_t)std::min<int64_t>(slots, b->n_cu);
     sa.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
     HIP_TRY(launch_team_slots(list0, n0, list1, n1, b->spread_k_dev, b->spread_rve, b->spread_first, s));
@@ -2990,10 +3002,31 @@ int rve_batch_import_state(rve_batch* b, const double* F, const double* h, const
 // Tangent workspace: fiber operators, ELL records, preconditioner, chunk
 // tables and task groups for the whole batch (allocated once), and the
 // per-workgroup solver slots (`slot_bytes`, grown on demand).
+// RVEs of the spread tangent: those beyond every resident build that have a
+// partition (us per iteration and column, streamed -> spread: one RVE of 4900 free
+// nodes 22 -> 7.2, of 16 000 76 -> 10; 28 at once 46 -> 37 and 184 -> 65).  Not
+// those of 2048 to 4096 free nodes: 10 to 15 us on one CU, about 2 x 8 on two.
+static bool tangent_spread_rve(const rve_batch* b, int64_t r)
+{
+    if (!b->t_spread_ok || !b->spread_mem || b->spread_k[r] == 0) return false;
+    for (int u = 0; u < kNumTanRes; ++u)
+        if (!b->tangent_private[0][u] && !b->tangent_private[1][u] && b->nf_of[r] <= (int64_t)kTanRes[u].threads * kTanRes[u].sn)
+            return false;
+    return true;
+}
+
+static size_t spread_tasks(const rve_batch* b, int per)
+{
+    size_t n = 0;
+    for (int64_t r = 0; r < b->R; ++r) n += tangent_spread_rve(b, r) ? (size_t)per : 0;
+    return n;
+}
+
 // Offsets of the tangent arena: fiber operators, ELL records,
-// preconditioner, chunk tables, outputs/inputs, statuses, iterations, order.
+// preconditioner, chunk tables, outputs/inputs, statuses, iterations, order,
+// first slots (tangent, VJP) and marks of the spread tasks.
 struct TanArena {
-    size_t par, rs, ra, rb, pc, cf, cr, out, in, st, it, ord, bytes;
+    size_t par, rs, ra, rb, pc, cf, cr, out, in, st, it, ord, tf, bytes;
 };
 
 static TanArena tangent_arena(const rve_batch* b)
@@ -3013,13 +3046,15 @@ static TanArena tangent_arena(const rve_batch* b)
     t.st = A.reserve(4 * (size_t)b->R);
     t.it = A.reserve(8 * (size_t)b->R);
     t.ord = A.reserve(4 * (size_t)b->R);
+    t.tf = A.reserve(4 * (spread_tasks(b, 9) + spread_tasks(b, 1) + 2) + 4 * spread_tasks(b, 9));
     t.bytes = A.used + 256;
     return t;
 }
 
 // Task groups of the tangent (host tables, computed once): RVEs for each
 // resident variant (smallest that holds the RVE), then the rest for the
-// streamed kernel; longest first in each.
+// streamed kernel, then those of the spread kernel; longest first in each.
+constexpr int kTanStream = kNumTanRes, kTanSpread = kNumTanRes + 1, kTanGroups = kNumTanRes + 2;
 static void tangent_groups(rve_batch* b)
 {
     if (!b->t_group_first.empty()) return;
@@ -3028,11 +3063,11 @@ static void tangent_groups(rve_batch* b)
     std::stable_sort(lpt.begin(), lpt.end(), [&](int32_t x, int32_t y) { return b->nf_of[x] > b->nf_of[y]; });
     std::vector<int32_t> order;
     order.reserve(b->R);
-    std::vector<int64_t> first(kNumTanRes + 2, 0);
-    for (int v = 0; v <= kNumTanRes; ++v) {
+    std::vector<int64_t> first(kTanGroups + 1, 0);
+    for (int v = 0; v < kTanGroups; ++v) {
         first[v] = (int64_t)order.size();
         for (int32_t r : lpt) {
-            int g = kNumTanRes;
+            int g = tangent_spread_rve(b, r) ? kTanSpread : kTanStream;
             for (int u = 0; u < kNumTanRes; ++u) {
                 if (b->tangent_private[0][u] || b->tangent_private[1][u]) continue;   // never launched
                 if (b->nf_of[r] <= (int64_t)kTanRes[u].threads * kTanRes[u].sn) {
@@ -3043,7 +3078,7 @@ static void tangent_groups(rve_batch* b)
             if (g == v) order.push_back(r);
         }
     }
-    first[kNumTanRes + 1] = (int64_t)order.size();
+    first[kTanGroups] = (int64_t)order.size();
     b->t_order_host = order;
     b->t_group_first = first;
 }
@@ -3076,8 +3111,23 @@ static int ensure_tangent_ws(rve_batch* b, size_t slot_bytes)
         b->t_status = carve<int32_t>(m, t.st);
         b->t_iters = carve<int64_t>(m, t.it);
         b->t_order = carve<int32_t>(m, t.ord);
+        b->t_spread_first = carve<int32_t>(m, t.tf);
         tangent_groups(b);
         hipError_t e = hipMemcpy(b->t_order, b->t_order_host.data(), 4 * (size_t)b->R, hipMemcpyHostToDevice);
+        // first slots of the spread tasks: nine columns per RVE, then one
+        std::vector<int32_t> tf;
+        b->t_spread_slots[0] = b->t_spread_slots[1] = 0;
+        for (int mode = 0; mode < 2; ++mode) {
+            int32_t at = 0;
+            for (int64_t q = b->t_group_first[kTanSpread]; q < b->t_group_first[kTanSpread + 1]; ++q)
+                for (int col = 0; col < (mode == 0 ? 9 : 1); ++col) {
+                    tf.push_back(at);
+                    at += b->spread_k[b->t_order_host[q]];
+                }
+            tf.push_back(at);
+            b->t_spread_slots[mode] = at;
+        }
+        if (e == hipSuccess) e = hipMemcpy(b->t_spread_first, tf.data(), 4 * tf.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy(b->t_chunk_first, b->chunk_first.data(), 8 * (size_t)(b->R + 1), hipMemcpyHostToDevice);
         if (e == hipSuccess)
@@ -3122,17 +3172,16 @@ static int tangent_plan(rve_batch* b, int mode, int engine, int rhs_opt, std::ve
 {
     tangent_groups(b);
     const int per = mode == 0 ? 9 : 1;
-    for (int v = 0; v <= kNumTanRes; ++v)
+    for (int v = 0; v < kTanGroups; ++v)
         blk[v] = mode == 0 && engine == RVE_ENGINE_AUTO && rhs_opt == 3 && v < kNumTanBlk &&
                  !b->tangent_blk_private[v];
     gf = b->t_group_first;
     if (engine != RVE_ENGINE_AUTO) {
-        for (int v = 0; v <= kNumTanRes; ++v) gf[v] = 0;
-        gf[kNumTanRes + 1] = b->R;
+        for (int v = 0; v <= kTanGroups; ++v) gf[v] = v > kTanStream ? b->R : 0;
     }
     *slot_bytes = 0;
     const int stream_threads = engine == RVE_ENGINE_AUTO ? 1024 : 64;
-    for (int v = 0; v <= kNumTanRes; ++v) {
+    for (int v = 0; v < kTanGroups; ++v) {
         const int64_t tasks = (gf[v + 1] - gf[v]) * per;
         grid[v] = 0;
         S[v] = 1;
@@ -3161,6 +3210,8 @@ static int tangent_plan(rve_batch* b, int mode, int engine, int rhs_opt, std::ve
             for (int64_t r = 0; r < b->R; ++r) S[v] = std::max<int64_t>(S[v], b->nf_of[r] + 1);
             bytes = 128 * (size_t)S[v] * (size_t)grid[v];
         }
+        if (v == kTanSpread)   // the members' x and b behind the slots of the streamed launch
+            bytes += tangent_spread_slot_bytes() * (size_t)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]);
         *slot_bytes += (bytes + 255) & ~size_t(255);   // the launches run at once: slots of their own
     }
     return RVE_OK;
@@ -3184,12 +3235,12 @@ static int ws_layout(rve_batch* b, WsLayout& L)
     for (int mode = 0; mode < 2; ++mode)
         for (int engine : {(int)RVE_ENGINE_AUTO, (int)RVE_ENGINE_STREAMED}) {
             std::vector<int64_t> gf;
-            int grid[kNumTanRes + 1];
-            int64_t S[kNumTanRes + 1];
+            int grid[kTanGroups];
+            int64_t S[kTanGroups];
             size_t sb = 0;
             for (int rhs : {0, 3}) {
-                bool blk[kNumTanRes + 1];
-                size_t slot_off[kNumTanRes + 1];
+                bool blk[kTanGroups];
+                size_t slot_off[kTanGroups];
                 int rc = tangent_plan(b, mode, engine, rhs, gf, grid, S, blk, slot_off, &sb);
                 if (rc) return rc;
                 L.slots = std::max(L.slots, sb);
@@ -3307,16 +3358,16 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
     if (rc) return rc;
     const int stream_threads = b->opts.engine == RVE_ENGINE_AUTO ? 1024 : 64;
     std::vector<int64_t> gf;
-    int grid[kNumTanRes + 1];
-    int64_t S[kNumTanRes + 1];
+    int grid[kTanGroups];
+    int64_t S[kTanGroups];
     size_t slot_bytes = 0;
-    bool blk[kNumTanRes + 1];
-    size_t slot_off[kNumTanRes + 1];
+    bool blk[kTanGroups];
+    size_t slot_off[kTanGroups];
     rc = tangent_plan(b, mode, b->opts.engine, b->opts.tangent_rhs, gf, grid, S, blk, slot_off, &slot_bytes);
     if (rc) return rc;
     // largest free-node count of each launch's RVEs
-    b->t_max_nf.assign(kNumTanRes + 1, 0);
-    for (int v = 0; v <= kNumTanRes; ++v)
+    b->t_max_nf.assign(kTanGroups, 0);
+    for (int v = 0; v < kTanGroups; ++v)
         for (int64_t q = gf[v]; q < gf[v + 1]; ++q)
             b->t_max_nf[v] = std::max<int64_t>(b->t_max_nf[v], b->nf_of[b->t_order_host[q]]);
     rc = ensure_tangent_ws(b, slot_bytes);
@@ -3353,18 +3404,18 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
     a.build_static = b->t_static_built ? 0 : 1;
     HIP_TRY(launch_tangent_prep(a, s));
     b->t_static_built = true;
-    HIP_TRY(launch_reset(b->dqueue, kNumTanRes + 1, s));
+    HIP_TRY(launch_reset(b->dqueue, kTanGroups + 1, s));
     // The launches run at once on up to four streams, the most work first, so
     // that the tail of one (its last tasks on few CUs) overlaps the others; a
     // launch beyond four goes behind the one of least work.
     std::vector<std::pair<int64_t, int>> order;
     int total = 0;
-    for (int v = 0; v <= kNumTanRes; ++v) {
+    for (int v = 0; v < kTanGroups; ++v) {
         if (grid[v] == 0) continue;
         int64_t w = 0;
         for (int64_t q = gf[v]; q < gf[v + 1]; ++q) w += b->nf_of[b->t_order_host[q]];
         order.push_back({-w, v});
-        total += (grid[v] + 7) / 8 * 8;   // workgroups go to the 8 XCDs in turn
+        total += ((v == kTanSpread ? (int)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]) : grid[v]) + 7) / 8 * 8;   // workgroups go to the 8 XCDs in turn
     }
     std::sort(order.begin(), order.end());
     const bool fork = order.size() > 1;
@@ -3395,7 +3446,25 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
             HIP_TRY(launch_tangent_blk(v, a, grid[v], ls));
         else if (v < kNumTanRes)
             HIP_TRY(launch_tangent_res(v, a, grid[v], total <= b->n_cu, ls));
-        else
+        else if (v == kTanSpread) {
+            const int64_t per = mode == 0 ? 9 : 1, n_tasks = a.n_order * per;
+            SpreadArgs sp = b->spread_tab;
+            sp.task_first = b->t_spread_first + (mode == 0 ? 0 : 9 * a.n_order + 1);
+            sp.queue = b->dqueue + kTanGroups;
+            sp.n_tasks = (int32_t)n_tasks;
+            sp.n_areas = (int32_t)std::min<int64_t>(n_tasks, b->spread_areas);
+            sp.grid = (int32_t)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]);
+            sp.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
+            TangentArgs c = a;
+            c.done = b->t_spread_first + 10 * a.n_order + 2;
+            c.slot_ws64 = reinterpret_cast<double*>(b->t_slots + slot_off[v] + need);
+            HIP_TRY(launch_zero32(c.done, n_tasks, ls));
+            HIP_TRY(launch_zero32(reinterpret_cast<int32_t*>(sp.xchg), 2 * (int64_t)sp.n_areas * sp.area_words, ls));
+            HIP_TRY(launch_tangent_spread(c, sp, ls));
+            a.done = c.done;   // the tasks whose team gave up
+            HIP_TRY(launch_tangent_stream(a, stream_threads, grid[v], ls));
+            a.done = nullptr;
+        } else
             HIP_TRY(launch_tangent_stream(a, stream_threads, grid[v], ls));
     }
     if (fork)

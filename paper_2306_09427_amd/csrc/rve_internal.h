@@ -90,6 +90,7 @@ struct TangentArgs {
     float4* slot_ws32;           // [grid][5][slot_nodes] per-wavefront FP32 p, q, r, d, z (wave kernel)
     int64_t slot_nodes;          // free-node capacity of a slot + 1
     int32_t build_static;        // 1: fill rec_static from the incidence first
+    int32_t* done;               // [tasks] 1: finished by the spread launch, skipped by the streamed one (or null)
 };
 
 // Fiber-orientation outputs at the state of the last solve.
@@ -383,6 +384,9 @@ struct SpreadArgs {
 inline int32_t spread_words(int max_x) { return 16 + 2 * (((3 * max_x + 7 * kTeamMax) + 15) & ~15); }
 hipError_t launch_team_slots(const int32_t* list0, int n0, const int32_t* list1, int n1, const int32_t* k_of,
                              int32_t* task_rve, int32_t* task_first, hipStream_t s);
+hipError_t launch_tangent_spread(const TangentArgs& a, const SpreadArgs& sp, hipStream_t s);
+hipError_t tangent_spread_info(int* blocks_per_cu, size_t* private_bytes);
+size_t tangent_spread_slot_bytes();
 constexpr int kStUnfinished = -1;    // status of an RVE a team has not finished
 hipError_t launch_spread(const SpreadArgs& a, hipStream_t s);
 hipError_t spread_info(int* blocks_per_cu, size_t* private_bytes);

@@ -37,6 +37,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "rve_exchange.h"
 #include "rve_internal.h"
 #include "rve_relax.h"
 #include "rve_wave.h"
@@ -389,6 +390,45 @@ __device__ __forceinline__ void assembly_partial(TanArgs& A, const Ctx& c, int r
     }
 }
 
+// The same sums for one fixed end (0: i, 1: j) of fiber k; xo: x64 of the other
+// end (zero where that is fixed too).
+template <bool TAN>
+__device__ __forceinline__ void assembly_end(TanArgs& A, const Ctx& c, const double* F, const double* G, int kk, int ll,
+                                             int64_t k, int end, const double* xo, double* acc)
+{
+    auto& net = A.net;
+    const uint32_t en = c.ends[k];
+    const int64_t ends[2] = {(int64_t)(en & 0xffff), (int64_t)(en >> 16)};
+    const double* q = c.par64 + 6 * k;
+    const double s = end ? 1.0 : -1.0;
+    const double* Xm = net.Xb + 3 * (c.b0 + (ends[end] - c.nf));
+    double x[3], u[3], w[3];
+    for (int p = 0; p < 3; ++p) x[p] = F[3 * p] * Xm[0] + F[3 * p + 1] * Xm[1] + F[3 * p + 2] * Xm[2];
+    const double fv[3] = {q[5] * q[0], q[5] * q[1], q[5] * q[2]};
+    if (TAN) {
+        const double d0l = net.d0[3 * (c.f0 + k) + ll];
+        for (int p = 0; p < 3; ++p) u[p] = (p == kk ? d0l : 0.0) - s * xo[p];
+        apply_B64(q, u[0], u[1], u[2], w[0], w[1], w[2]);
+        const double xl = ll == 0 ? Xm[0] : (ll == 1 ? Xm[1] : Xm[2]);
+        for (int p = 0; p < 3; ++p)
+            for (int cc = 0; cc < 3; ++cc) acc[3 * p + cc] += s * (w[p] * x[cc] + (cc == kk ? fv[p] * xl : 0.0));
+    } else {
+        // u = [-lambda; y] at the two ends, difference j - i
+        for (int p = 0; p < 3; ++p) u[p] = s * xo[p] + s * (G[3 * p] * x[0] + G[3 * p + 1] * x[1] + G[3 * p + 2] * x[2]);
+        if (ends[1 - end] >= c.nf) {
+            const double* Xo = net.Xb + 3 * (c.b0 + (ends[1 - end] - c.nf));
+            double y[3];
+            for (int p = 0; p < 3; ++p) y[p] = F[3 * p] * Xo[0] + F[3 * p + 1] * Xo[1] + F[3 * p + 2] * Xo[2];
+            for (int p = 0; p < 3; ++p) u[p] -= s * (G[3 * p] * y[0] + G[3 * p + 1] * y[1] + G[3 * p + 2] * y[2]);
+        }
+        apply_B64(q, u[0], u[1], u[2], w[0], w[1], w[2]);
+        double gtf[3];
+        for (int p = 0; p < 3; ++p) gtf[p] = G[p] * fv[0] + G[3 + p] * fv[1] + G[6 + p] * fv[2];
+        for (int p = 0; p < 3; ++p)
+            for (int cc = 0; cc < 3; ++cc) acc[3 * p + cc] += s * (w[p] + gtf[p]) * Xm[cc];
+    }
+}
+
 // Final outputs of a task from the summed assembly (one thread).
 template <bool TAN>
 __device__ void assembly_write(TanArgs& A, int r, int col, const double* acc, int status, int64_t iters)
@@ -705,6 +745,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_
         const int t = __builtin_amdgcn_readfirstlane(task);
         __syncthreads();
         if (t >= n_tasks) break;
+        if (A.done && A.done[t]) continue;
         cg_stream_task<TAN, T>(A, __builtin_amdgcn_readfirstlane(A.order[t / per]), t % per, red);
     }
 }
@@ -1082,6 +1123,477 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_
         if (t >= n_tasks) break;
         cg_chip_task<TAN, T, SN>(A, __builtin_amdgcn_readfirstlane(A.order[t / per]), t % per, zl, X, red);
     }
+}
+
+// ------------------------------------------------------------------ spread tasks
+// Tasks of RVEs above 4096 free nodes: k workgroups per task, on the partition
+// and with the exchange of the spread relaxation (rve_internal.h,
+// rve_exchange.h).  A member holds its nodes (at most 2048) as cg_chip_task
+// does, four per thread of 512; the streamed kernel read 3.7 MB per iteration
+// and column at 10 300 free nodes, beyond every L2 once several columns run.
+//
+// Two exchanges per iteration: p.K p, and r.r and r.z with z of the nodes other
+// parts hold as halo, whose p (and correction) each part then updates itself,
+// with the operations of the owner.  Each is one round trip through memory
+// (about 2 us), which with the barriers around it is what bounds an iteration.
+// Microseconds per iteration and column, streamed -> here: one RVE of 4900 free
+// nodes 22 -> 7.2, of 10 300 42 -> 9.3, of 16 000 76 -> 10; 28 RVEs at once 46 ->
+// 37, 110 -> 42 and 184 -> 65.  The tangents of 256 RVEs of 100 to 3000 seeds took
+// 50 ms with the streamed kernel and take 27.
+//
+// The arithmetic and its rounding are those of cg_stream_task but for the order
+// of the FP64 sums.  A task whose team gave up keeps its mark and runs on the
+// streamed kernel launched behind.
+
+// z = P r with the order of the products in cg_stream_task
+__device__ __forceinline__ void apply_block_yxz(const float* P, const float* r, float* z)
+{
+#pragma clang fp contract(off)
+    z[0] = fmaf(P[2], r[2], fmaf(P[0], r[0], P[1] * r[1]));
+    z[1] = fmaf(P[4], r[2], fmaf(P[1], r[0], P[3] * r[1]));
+    z[2] = fmaf(P[5], r[2], fmaf(P[2], r[0], P[4] * r[1]));
+}
+
+struct SpreadCgArgs {
+    TangentArgs t;
+    SpreadArgs sp;
+};
+constexpr int kCgT = kSpreadThreads, kCgSN = kSpreadSlots, kCgHN = kSpreadNodes / kSpreadThreads;
+
+struct CgSpreadRed : TeamSlot {
+    double v[2][3][kCgT / 64];
+    double sum[2][3][kTeamMax];
+};
+
+template <bool TAN>
+__device__ __forceinline__ bool cg_spread_task(KernArgsT<SpreadCgArgs>& AA, Team& tm, float4* zl, f32x3* dh, f32x3* hz, float4* XA, int2* XB,
+                                               CgSpreadRed& red)
+{
+    constexpr int T = kCgT, SN = kCgSN, HN = kCgHN, NW = T / 64;
+    constexpr int per = TAN ? 9 : 1;
+    TanArgs& A = AA.t;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wave64 = 64 * wave;
+    const int r = __builtin_amdgcn_readfirstlane(A.order[tm.task / per]), col = tm.task % per;
+    const int k = tm.k, rank = tm.rank, max_x = AA.sp.max_x, half = (AA.sp.area_words - 16) / 2;
+    u64* const xbuf = tm.area + 16;
+    auto words_of = [&](unsigned t) __attribute__((always_inline)) { return xbuf + (t & 1) * half + 3 * (int64_t)max_x; };
+    if (__builtin_amdgcn_readfirstlane(A.solve_status[r]) != 0) {   // the same in every member
+        ++tm.tag;
+        const bool all = team_done(AA.sp, red, tm, words_of(tm.tag));
+        if (rank == 0 && all) {
+            no_state<TAN>(A, r, col, tid);
+            if (tid == 0) A.done[tm.task] = 1;
+        }
+        return all;
+    }
+    const Ctx c = make_ctx(A, r);
+    const int kk = col / 3, ll = col % 3;
+    const int64_t pi = uni64(AA.sp.part_first[r]) + rank;
+    const int nown = __builtin_amdgcn_readfirstlane(AA.sp.parts[pi].nown), nhalo = __builtin_amdgcn_readfirstlane(AA.sp.parts[pi].nhalo);
+    const int x4 = __builtin_amdgcn_readfirstlane(AA.sp.parts[pi].x4), nx = nown - x4;
+    const int64_t own0 = uni64(AA.sp.parts[pi].own0), halo0 = uni64(AA.sp.parts[pi].halo0);
+    const int64_t cf = uni64(A.chunk_first[r]);
+    // FP64 x (by position slot, the last entry zero) and b of this part
+    double* x64 = A.slot_ws64 + (int64_t)blockIdx.x * (3 * (kSpreadZero + 1) + 3 * kSpreadNodes);
+    double* b64 = x64 + 3 * (kSpreadZero + 1);
+    int parity = 0;
+
+    // exchange slots of the own nodes (low half, 0xffff: none) and the halo's
+    // (high half); publish: z of a node other parts hold
+    static_assert(HN == SN, "packed slots");
+    uint32_t xh[SN];
+    auto publish = [&](int s, const float* z) __attribute__((always_inline)) {
+        if ((xh[s] & 0xffffu) != 0xffffu) {
+            u64* p = xbuf + (tm.tag & 1) * half + (xh[s] & 0xffffu);
+            put_word(p, tm.tag, __float_as_uint(z[0]));
+            put_word(p + max_x, tm.tag, __float_as_uint(z[1]));
+            put_word(p + 2 * max_x, tm.tag, __float_as_uint(z[2]));
+        }
+    };
+    // The exchange of tag tm.tag: the team's totals of N sums (the same in
+    // every member) and, on request, z of the halo (each thread its own).  Two barriers; false when a
+    // poll gave up.
+    auto exchange = [&](auto& v, bool halo) __attribute__((always_inline)) -> bool {
+        constexpr int N = sizeof(v) / sizeof(double);
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        const int lane = t & 63, limit = AA.sp.spin_limit;
+        if (N == 2) {
+            double x = halves_xor32(v[0], v[N - 1]);
+            x = add_xor16(x);
+            x += dpp_mov<kDppRor8>(x);
+            x += dpp_mov<kDppRor4>(x);
+            x += dpp_mov<kDppXor2>(x);
+            x += dpp_mov<kDppXor1>(x);
+            if ((lane & 31) == 0) red.v[parity][lane >> 5][wave] = x;
+        } else {
+#pragma unroll
+            for (int q = 0; q < N; ++q) v[q] = wave_sum(v[q]);
+            if (lane == 0)
+                for (int q = 0; q < N; ++q) red.v[parity][q][wave] = v[q];
+        }
+        __syncthreads();
+        u64* const words = words_of(tm.tag);
+        int polls = 1;
+        bool ok = true;
+        if (wave == 0) {
+            if (lane < N) {
+                double x = 0.0;
+#pragma unroll
+                for (int i = 0; i < NW; ++i) x += red.v[parity][lane][i];
+                put_word(words + 2 * (N * rank + lane), tm.tag, (unsigned)__double2loint(x));
+                put_word(words + 2 * (N * rank + lane) + 1, tm.tag, (unsigned)__double2hiint(x));
+            }
+            if (lane < N * k) {   // (k <= 16)
+                const u64* p = words + 2 * lane;
+                u64 lo = get_word(p), hi = get_word(p + 1);
+                while (!(tagged(lo, tm.tag) && tagged(hi, tm.tag)) && polls++ < limit) {
+                    lo = get_word(p);
+                    hi = get_word(p + 1);
+                }
+                ok = tagged(lo, tm.tag) && tagged(hi, tm.tag);
+                red.sum[parity][lane % N][lane / N] = __hiloint2double((int)(unsigned)hi, (int)(unsigned)lo);
+            }
+        }
+        if (halo) {
+#pragma unroll
+            for (int u = 0; u < HN; ++u)
+                if (xh[u] < 0xffff0000u) {
+                    const u64* p = xbuf + (tm.tag & 1) * half + (xh[u] >> 16);
+                    u64 x = get_word(p), y = get_word(p + max_x), z = get_word(p + 2 * max_x);
+                    while (!(tagged(x, tm.tag) && tagged(y, tm.tag) && tagged(z, tm.tag)) && polls++ < limit) {
+                        x = get_word(p);
+                        y = get_word(p + max_x);
+                        z = get_word(p + 2 * max_x);
+                    }
+                    ok = ok && tagged(x, tm.tag) && tagged(y, tm.tag) && tagged(z, tm.tag);
+                    hz[t + T * u] = f32x3{__uint_as_float((unsigned)x), __uint_as_float((unsigned)y), __uint_as_float((unsigned)z)};
+                }
+        }
+        if (!ok) red.bad = 1;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            double x = 0.0;
+#pragma unroll 1
+            for (int p = 0; p < k; ++p) x += red.sum[parity][q][p];
+            v[q] = uniformd(x);
+        }
+        parity ^= 1;
+        return __builtin_amdgcn_readfirstlane(red.bad) == 0;
+    };
+
+    // right-hand side (FP64) and x = 0
+    double one[1], two[2];
+    {
+        double bb = 0.0;
+        asm volatile("" : "+v"(bb));
+        double F[9], G[9];
+        for (int q = 0; q < 9; ++q) F[q] = A.F[9 * r + q];
+        if (!TAN)
+            for (int q = 0; q < 9; ++q) G[q] = A.gsigma[9 * r + q];
+#pragma unroll 1
+        for (int s = tid; s < nown; s += T) {
+            double b[3];
+            rhs_node<TAN>(A, c, AA.sp.own[own0 + s], kk, ll, F, G, b);
+            for (int p = 0; p < 3; ++p) {
+                b64[3 * s + p] = b[p];
+                x64[3 * s + p] = 0.0;
+            }
+            bb += b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+        }
+        for (int s = tid; s < 3 * nhalo; s += T) x64[3 * kSpreadNodes + s] = 0.0;
+        if (tid < 3) x64[3 * kSpreadZero + tid] = 0.0;
+        one[0] = bb;
+    }
+    ++tm.tag;
+    if (!exchange(one, false)) return false;
+    const double bb = one[0];
+
+    // records, blocks and extra records on chip (read once per task)
+    float zf = 0.f;
+    asm volatile("" : "+v"(zf));
+    float rx[SN][4], ry[SN][4], rz_[SN][4], rc[SN][4], rg[SN][4];
+    uint32_t ro[SN][2];   // LDS byte offsets / 8 of the other ends, two per word
+    float Pb[SN][6];
+    int degw[SN];         // the wave's largest degree of the slot
+#pragma unroll
+    for (int s = 0; s < SN; ++s) {
+        const int i = tid + T * s;
+        float4 p0 = make_float4(zf, zf, zf, zf), p1 = p0;
+        uint32_t o4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            rx[s][u] = ry[s][u] = rz_[s][u] = rc[s][u] = rg[s][u] = zf;
+            o4[u] = 2u * kSpreadZero;
+        }
+        xh[s] = 0xffffffffu;
+        int deg = 0;
+        if (i < nown) {
+            const int a = AA.sp.own[own0 + i];
+            xh[s] = 0xffff0000u | (AA.sp.xslot[own0 + i] & 0xffff);
+            p0 = A.precond[2 * (c.a0 + a)];
+            p1 = A.precond[2 * (c.a0 + a) + 1];
+            const int64_t e0 = c.incoff[a], rec = A.chunk_rec[cf + (a >> 6)] + (a & 63);
+            deg = (int)(c.incoff[a + 1] - e0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (u < deg) {
+                    const float4 ra = A.recA[rec + 64 * u];
+                    rx[s][u] = ra.x; ry[s][u] = ra.y; rz_[s][u] = ra.z;
+                    rg[s][u] = __int_as_float(A.recB[rec + 64 * u].y);
+                    rc[s][u] = ra.w - rg[s][u];
+                    o4[u] = 2u * AA.sp.oslot[e0 + u];
+                }
+#pragma unroll 1
+            for (int u = 4; u < deg; ++u) {
+                float4 ra = A.recA[rec + 64 * u];
+                const int g = A.recB[rec + 64 * u].y;
+                ra.w -= __int_as_float(g);
+                XA[(u - 4) * nx + (i - x4)] = ra;
+                XB[(u - 4) * nx + (i - x4)] = make_int2((int)AA.sp.oslot[e0 + u] | deg << 16, g);
+            }
+        }
+        ro[s][0] = o4[0] | o4[1] << 16;
+        ro[s][1] = o4[2] | o4[3] << 16;
+        Pb[s][0] = p0.x; Pb[s][1] = p0.y; Pb[s][2] = p0.z; Pb[s][3] = p0.w; Pb[s][4] = p1.x; Pb[s][5] = p1.y;
+        degw[s] = __builtin_amdgcn_readfirstlane((int)__float_as_uint(wave_max_nonneg(__uint_as_float((unsigned)deg))));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < HN; ++u) {
+        const int i = tid + T * u;
+        if (i < nhalo) xh[u] = (xh[u] & 0xffffu) | (uint32_t)AA.sp.halo_xslot[halo0 + i] << 16;
+    }
+    float P[SN][3], R[SN][3], Q[SN][3], D[SN][3];
+    const char* zb = reinterpret_cast<const char*>(zl);
+
+    int status = ST_CONVERGED;
+    double cgt = A.cg_tol;
+    asm volatile("" : "+v"(cgt));
+    const double tol2 = uniformd(cgt * cgt);
+    const int64_t maxit = A.cg_max > 0 ? A.cg_max : 6 * c.nf + 100;
+    int64_t it_total = 0;
+    bool done = !(bb > 0.0);
+    for (int outer = 0; outer < 8 && !done; ++outer) {
+        asm volatile("" : "+v"(tid));
+        // FP64 residual of the FP64 solution (x64 of own and halo nodes are
+        // this part's own, complete: barrier above); d = 0, p = z = P r
+        two[0] = two[1] = 0.0;
+        ++tm.tag;
+#pragma unroll
+        for (int s = 0; s < SN; ++s) {
+            const int i = tid + T * s;
+            double z0 = 0.0;
+            asm volatile("" : "+v"(z0));
+            double ra[3] = {z0, z0, z0};
+            if (i < nown) {
+                for (int p = 0; p < 3; ++p) ra[p] = b64[3 * i + p];
+                if (outer > 0) {
+                    const int a = AA.sp.own[own0 + i];
+                    const double xa[3] = {x64[3 * i], x64[3 * i + 1], x64[3 * i + 2]};
+#pragma unroll 1
+                    for (int64_t e = c.incoff[a]; e < c.incoff[a + 1]; ++e) {
+                        const double* xo = x64 + 3 * (int)AA.sp.oslot[e];
+                        double w3[3];
+                        apply_B64(c.par64 + 6 * (int64_t)(A.net.inc[e] & 0x7fffffffu), xa[0] - xo[0], xa[1] - xo[1], xa[2] - xo[2],
+                                  w3[0], w3[1], w3[2]);
+                        for (int p = 0; p < 3; ++p) ra[p] -= w3[p];
+                    }
+                }
+            }
+            for (int p = 0; p < 3; ++p) {
+                R[s][p] = (float)ra[p];
+                D[s][p] = Q[s][p] = 0.f;
+            }
+            two[0] += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
+            apply_block_yxz(Pb[s], R[s], P[s]);
+            publish(s, P[s]);
+            two[1] += (double)R[s][0] * P[s][0] + (double)R[s][1] * P[s][1] + (double)R[s][2] * P[s][2];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!exchange(two, true)) return false;
+        const double rr = two[0];
+        double rz = two[1];
+        if (rr <= tol2 * bb) {
+            done = true;
+            break;
+        }
+        if (it_total >= maxit) {
+            status = ST_CG_MAXITER;
+            break;
+        }
+        // inner preconditioned CG, as cg_chip_task
+        double drop = 1e-6;
+        asm volatile("" : "+s"(drop));
+        const double rr0 = uniformd(drop * rr);
+        f32x3* const zh = reinterpret_cast<f32x3*>(zl) + kSpreadNodes;
+#pragma unroll
+        for (int u = 0; u < HN; ++u)
+            if (T * u + wave64 < nhalo) {
+                zh[tid + T * u] = hz[tid + T * u];
+                dh[tid + T * u] = f32x3{zf, zf, zf};
+            }
+        for (;;) {
+            if (it_total >= maxit) break;
+            ++it_total;
+            asm volatile("" : "+v"(tid));
+#pragma unroll
+            for (int s = 0; s < SN; ++s) asm volatile("" : "+v"(ro[s][0]), "+v"(ro[s][1]), "+v"(xh[s]));
+#pragma unroll
+            for (int s = 0; s < SN; ++s) *(f32x3*)&zl[tid + T * s] = f32x3{P[s][0], P[s][1], P[s][2]};
+            __syncthreads();
+            double pq = 0.0;
+#pragma unroll
+            for (int s = 0; s < SN; ++s) {
+                if (T * s + wave64 < nown) {
+                    f32x3 po[4];
+                    float q[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        po[u] = *(const f32x3*)(zb + 8u * ((u & 1) ? ro[s][u >> 1] >> 16 : ro[s][u >> 1] & 0xffffu));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        add_record(rx[s][u], ry[s][u], rz_[s][u], rc[s][u], rg[s][u], P[s], po[u], q);
+                    if (degw[s] > 4) {
+                        const int i = tid + T * s - x4;
+                        if (i >= 0 && i < nx) {
+                            int2 b = XB[i];
+                            const int extra = (b.x >> 16) - 4;
+#pragma unroll 1
+                            for (int j = 0; j < extra; ++j) {
+                                const float4 ra = XA[j * nx + i];
+                                if (j > 0) b = XB[j * nx + i];
+                                add_record(ra.x, ra.y, ra.z, ra.w, __int_as_float(b.y), P[s], *(const f32x3*)&zl[b.x & 0xffff], q);
+                            }
+                        }
+                    }
+                    for (int p = 0; p < 3; ++p) Q[s][p] = q[p];
+                    pq += (double)P[s][0] * q[0] + (double)P[s][1] * q[1] + (double)P[s][2] * q[2];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ++tm.tag;
+            one[0] = pq;
+            if (!exchange(one, false)) return false;
+            pq = one[0];
+            if (!(pq > 0.0)) {
+                status = ST_CG_INDEFINITE;
+                done = true;
+                break;
+            }
+            const float af = uniform((float)(rz / pq));
+            two[0] = two[1] = 0.0;
+            ++tm.tag;
+            float Z[SN][3];
+#pragma unroll
+            for (int s = 0; s < SN; ++s) {
+                for (int p = 0; p < 3; ++p) {
+                    D[s][p] = fmaf(af, P[s][p], D[s][p]);
+                    R[s][p] = fmaf(-af, Q[s][p], R[s][p]);
+                }
+                apply_block_yxz(Pb[s], R[s], Z[s]);
+                publish(s, Z[s]);
+                two[0] += (double)R[s][0] * R[s][0] + (double)R[s][1] * R[s][1] + (double)R[s][2] * R[s][2];
+                two[1] += (double)R[s][0] * Z[s][0] + (double)R[s][1] * Z[s][1] + (double)R[s][2] * Z[s][2];
+            }
+#pragma unroll
+            for (int u = 0; u < HN; ++u)
+                if (T * u + wave64 < nhalo) {
+                    const f32x3 p = zh[tid + T * u], d = dh[tid + T * u];
+                    dh[tid + T * u] = f32x3{fmaf(af, p.x, d.x), fmaf(af, p.y, d.y), fmaf(af, p.z, d.z)};
+                }
+            if (!exchange(two, true)) return false;
+            const double rn = two[0], rzn = two[1];
+            if (rn <= rr0 || rn <= 0.25 * tol2 * bb) break;
+            const float bf = uniform((float)(rzn / rz));
+            rz = rzn;
+#pragma unroll
+            for (int s = 0; s < SN; ++s)
+                for (int p = 0; p < 3; ++p) P[s][p] = fmaf(bf, P[s][p], Z[s][p]);
+#pragma unroll
+            for (int u = 0; u < HN; ++u)
+                if (T * u + wave64 < nhalo) {
+                    const f32x3 p = zh[tid + T * u], z = hz[tid + T * u];
+                    zh[tid + T * u] = f32x3{fmaf(bf, p.x, z.x), fmaf(bf, p.y, z.y), fmaf(bf, p.z, z.z)};
+                }
+        }
+        // x += d, of the own and of the halo nodes
+        asm volatile("" : "+v"(tid));
+#pragma unroll
+        for (int s = 0; s < SN; ++s) {
+            const int i = tid + T * s;
+            if (i < nown)
+                for (int p = 0; p < 3; ++p) x64[3 * i + p] += (double)D[s][p];
+        }
+#pragma unroll 1
+        for (int i = tid; i < nhalo; i += T) {
+            const f32x3 d = dh[i];
+            double* x = x64 + 3 * (kSpreadNodes + i);
+            x[0] += (double)d.x; x[1] += (double)d.y; x[2] += (double)d.z;
+        }
+        __syncthreads();
+        if (outer == 7 && !done && status == ST_CONVERGED) status = ST_CG_MAXITER;
+    }
+
+    // assembly over the part's boundary nodes (x64 complete: barrier above, or
+    // no update since the first exchange)
+    double tot[9];
+    {
+        double acc[9];
+        for (int p = 0; p < 9; ++p) acc[p] = 0.0;
+        double F[9], G[9];
+        for (int q = 0; q < 9; ++q) F[q] = A.F[9 * r + q];
+        if (!TAN)
+            for (int q = 0; q < 9; ++q) G[q] = A.gsigma[9 * r + q];
+        const int64_t bp0 = uni64(AA.sp.parts[pi].bnd0);
+        const int nbnd = __builtin_amdgcn_readfirstlane(AA.sp.parts[pi].nbnd);
+#pragma unroll 1
+        for (int q = tid; q < nbnd; q += T) {
+            const int64_t bn = c.b0 + AA.sp.bnd[bp0 + q];
+#pragma unroll 1
+            for (int64_t e = A.net.binc_off[bn]; e < A.net.binc_off[bn + 1]; ++e) {
+                const uint32_t w = A.net.binc[e];
+                assembly_end<TAN>(A, c, F, G, kk, ll, (int64_t)(w & 0x7fffffffu), (w >> 31) ? 0 : 1,
+                                  x64 + 3 * (int)AA.sp.bslot[e], acc);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < 9; p += 3) {
+            double three[3] = {acc[p], acc[p + 1], acc[p + 2]};
+            ++tm.tag;
+            if (!exchange(three, false)) return false;
+            for (int q = 0; q < 3; ++q) tot[p + q] = three[q];
+        }
+    }
+    ++tm.tag;
+    const bool all = team_done(AA.sp, red, tm, words_of(tm.tag));
+    if (rank == 0 && all && threadIdx.x == 0) {
+        assembly_write<TAN>(A, r, col, tot, status, it_total);
+        A.done[tm.task] = 1;
+    }
+    return all;
+}
+
+template <bool TAN>
+__global__ __launch_bounds__(kCgT) __attribute__((amdgpu_waves_per_eu(2))) void cg_spread_kernel(SpreadCgArgs)
+{
+    __shared__ float4 zl[kSpreadZero + 1];   // p: own, halo, zero
+    __shared__ f32x3 dh[kSpreadNodes];       // correction of the halo
+    __shared__ f32x3 hz[kSpreadNodes];       // z of the halo
+    __shared__ float4 XA[kSpreadExtra];      // records beyond the fourth: (n, k_t/L0 - T/l)
+    __shared__ int2 XB[kSpreadExtra];        // (slot of the other end | degree << 16, bits of T/l)
+    __shared__ CgSpreadRed red;
+    auto& AA = *kernel_args<SpreadCgArgs>();
+    if (threadIdx.x == 0) {
+        red.bad = 0;
+        zl[kSpreadZero] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    Team tm;
+    while (team_take(AA.sp, red, tm))
+        if (!cg_spread_task<TAN>(*kernel_args<SpreadCgArgs>(), tm, zl, dh, hz, XA, XB, red)) break;
 }
 
 // ------------------------------------------------------------------ resident tasks
@@ -1820,6 +2332,29 @@ hipError_t launch_tangent_stream(const TangentArgs& a, int threads, int grid, hi
         return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_tangent_spread(const TangentArgs& a, const SpreadArgs& sp, hipStream_t s)
+{
+    if (a.n_order <= 0) return hipSuccess;
+    const SpreadCgArgs args{a, sp};
+    if (a.mode == 0)
+        hipLaunchKernelGGL(cg_spread_kernel<true>, dim3((unsigned)sp.grid), dim3(kCgT), 0, s, args);
+    else
+        hipLaunchKernelGGL(cg_spread_kernel<false>, dim3((unsigned)sp.grid), dim3(kCgT), 0, s, args);
+    return hipGetLastError();
+}
+
+size_t tangent_spread_slot_bytes() { return 8 * (3 * (size_t)(kSpreadZero + 1) + 3 * (size_t)kSpreadNodes); }
+
+hipError_t tangent_spread_info(int* blocks_per_cu, size_t* private_bytes)
+{
+    for (const void* f : {(const void*)cg_spread_kernel<true>, (const void*)cg_spread_kernel<false>}) {
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, kCgT, 0);
+        if (e != hipSuccess) return e;
+        if (*blocks_per_cu < 1) return hipSuccess;
+    }
+    return max_private_bytes({(const void*)cg_spread_kernel<true>, (const void*)cg_spread_kernel<false>}, private_bytes);
 }
 
 // dynamic LDS (the on-chip builds hold theirs statically)

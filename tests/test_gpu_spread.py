@@ -1,6 +1,8 @@
 """Spread relaxation (several workgroups per RVE) against the incidence kernel,
 whose arithmetic it shares: states and iteration counts agree bit for bit, the
 norms (summed in another order) to rounding."""
+import re
+
 import numpy as np
 import pytest
 
@@ -26,7 +28,7 @@ def run(rb, nets, engine, F, spin=None, warm=None, **kw):
     o.update(kw)
     b = rb.Batch(synth.pack(nets), **o)
     if engine == rb.ENGINE_AUTO:
-        assert all("x512):" in g for g in b.describe().split(";")[:-1]), b.describe()
+        assert all(re.match(r"incidence\((global,)?\d+(-\d+)?x\d+\):", g) for g in b.describe().split(";")[:-1]), b.describe()
     if spin is not None:
         b.team_spin_limit(spin)
     out = []
@@ -76,3 +78,37 @@ def test_teams_that_give_up(rb, nets):
     """One poll per word: the incidence kernel behind takes what the teams left."""
     F = stretch(3)
     same(run(rb, nets, rb.ENGINE_AUTO, F, spin=1), run(rb, nets, rb.ENGINE_INCIDENCE, F))
+
+
+@pytest.mark.parametrize("spin", [None, 1])
+def test_spread_tangent_and_vjp(rb, nets, spin):
+    """Tangent columns and VJPs over several workgroups against the streamed
+    kernel at the same states (one of them not converged, and the lattice's
+    stiffness indefinite under the lateral compression); spin 1: the teams
+    give up and the streamed kernel behind takes their tasks."""
+    some = [nets[0], nets[2], nets[0], nets[1]]
+    o = dict(precision=rb.MIXED, mass=rb.MASS_SCALED, alpha=0.5, c=0.1, tol_abs=0.0, tol_rel=1e-5, n_max=20000,
+             check_every=8, cg_tol=1e-9)
+    b = rb.Batch(synth.pack(some), **o)
+    F, h, st = (b.solve(stretch(4)), b.export_state())[1]
+    assert (st == 0).all()
+    st[2] = 1
+    g = np.random.default_rng(3).standard_normal((4, 3, 3))
+    out = []
+    for engine in (rb.ENGINE_AUTO, rb.ENGINE_STREAMED):
+        b.set_opts(engine=engine, **o)
+        if spin is not None:
+            b.team_spin_limit(spin)
+        b.import_state(F, h, st)
+        C, cs = b.tangent()
+        C2, _ = b.tangent()
+        gF, gs = b.vjp(g)
+        assert np.array_equal(C, C2, equal_nan=True)
+        assert cs.tolist() == [0, rb.ST_CG_INDEFINITE, rb.ST_NO_STATE, 0] and gs[[0, 2, 3]].tolist() == [0, rb.ST_NO_STATE, 0]
+        out.append((C, gF))
+    b.close()
+    on = [0, 3]
+    scale = np.abs(out[1][0][on]).max(axis=(1, 2))
+    assert np.isnan(out[0][0][2]).all() and np.isnan(out[0][1][2]).all()
+    assert np.all(np.abs(out[0][0] - out[1][0])[on].max(axis=(1, 2)) < 1e-7 * scale)
+    assert np.all(np.abs(out[0][1] - out[1][1])[on].max(axis=(1, 2)) < 1e-7 * scale * np.abs(g).max() * 9)
