@@ -467,6 +467,27 @@ struct CgRed {
     double s[2][3][16];   // per-wavefront partial sums, alternating buffers
 };
 
+// q[0] + ... + q[NW - 1] in order, the reads issued eight together (left to
+// itself the compiler waits for each pair before the next: eight LDS latencies
+// in a row; all sixteen at once spill).
+template <int NW>
+__device__ __forceinline__ double sum_in_order(const double* q)
+{
+    constexpr int U = NW < 8 ? NW : 8;
+    double x = 0.0;
+#pragma unroll
+    for (int j = 0; j < NW; j += U) {
+        double v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) v[i] = q[j + i];
+#pragma unroll
+        for (int i = 0; i < U; ++i) asm volatile("" : "+v"(v[i]));
+#pragma unroll
+        for (int i = 0; i < U; ++i) x += v[i];
+    }
+    return x;
+}
+
 // Totals of N <= 3 values over the workgroup, in every thread: wave sums, then
 // the waves in order.  One barrier; the buffers alternate with `parity`.
 template <int NW, int N>
@@ -482,10 +503,7 @@ __device__ __forceinline__ void block_sums(CgRed& red, int parity, double (&v)[N
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < N; ++q) {
-        double x = 0.0;
-#pragma unroll
-        for (int i = 0; i < NW; ++i) x += red.s[parity][q][i];
-        v[q] = uniformd(x);
+        v[q] = uniformd(sum_in_order<NW>(red.s[parity][q]));
     }
 }
 template <int NW>
@@ -760,18 +778,22 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_
 // held too.  Reading the records from L2 in every iteration (24 bytes each,
 // about 250 iterations) took three quarters of an iteration.
 //
-// An iteration is bound by its serial chain: three barriers, two FP64 sums over
-// the workgroup and two FP64 quotients.  The sums of r.r and r.z share one
-// butterfly (the halves of the wave), see half_sums.  Microseconds per iteration
-// of one RVE alone, records from L2 -> here: 2.43 -> 1.64 at 183 free nodes,
-// 3.78 -> 2.42 at 790, 6.16 -> 3.95 at 1720; the 9216 columns of 1024 RVEs of 60
-// seeds: 51.9 -> 30.5 ms.
+// An iteration is bound by vector instruction issue (0.72 of the cycles) and by
+// its serial chain: three barriers, two FP64 sums over the workgroup and two FP64
+// quotients, which every wave works out for itself (r.r and r.z share one
+// butterfly, put_pair).  From 1024 free nodes on these cost more than the
+// latency that more waves hide: four nodes in 512 threads take 3.3 us per
+// iteration at 1742 free nodes where two in 1024 took 3.7 (2.8 and 3.05 on a
+// full chip); below, two nodes per thread are better (178 free nodes 1.55 us in
+// 256 threads, 1.98 in 128; 791 2.35 in 512, 2.61 in 256).  Microseconds per
+// iteration of one RVE, records from L2 -> here: 2.43 -> 1.55 at 178 free nodes,
+// 3.78 -> 2.35 at 791, 6.16 -> 3.3 at 1742.
 //
 // The arithmetic, its rounding and the order of every sum are those of
 // cg_res_task.
-template <int T>
+template <int N>
 struct ChipExtra {
-    static constexpr int XN = T / 4;   // rows of nodes: 4 records each
+    static constexpr int XN = N / 8;   // rows of nodes: 4 records each
     float4 A[4 * XN];                  // (n, k_t/L0 - T/l)
     int2 B[4 * XN];                    // (LDS byte offset of the other end, bits of T/l)
     int x4, xd;
@@ -797,33 +819,57 @@ __device__ __forceinline__ void apply_block(const float* P, const float* r, floa
     z[2] = fmaf(P[5], r[2], fmaf(P[2], r[0], P[4] * r[1]));
 }
 
-// Totals of a and b over the workgroup, in every thread, with one butterfly:
-// after the exchange of stage 32 the lower half of the wave holds a's sums and
-// the upper half b's; the additions are those of block_sum2.
+// Sums over the workgroup, in every thread.  H = 2: in the order of twice as many
+// threads with half the nodes: the even slots' partial sum a[0] and the odd
+// slots' a[1] of wave w are those of waves w and w + NW there.  put_pair: one
+// butterfly for two sums; after the exchange of stage 32 the lower half of the
+// wave holds v0's, the upper half v1's.
 template <int NW>
-__device__ __forceinline__ void half_sums(CgRed& red, int parity, int tid, double& a, double& b)
+__device__ __forceinline__ void put_pair(double* s0, double* s1, int tid, double v0, double v1)
 {
     const int lane = tid & 63, wave = tid >> 6;
-    double v = halves_xor32(a, b);
+    double v = halves_xor32(v0, v1);
     v = add_xor16(v);
     v += dpp_mov<kDppRor8>(v);
     v += dpp_mov<kDppRor4>(v);
     v += dpp_mov<kDppXor2>(v);
     v += dpp_mov<kDppXor1>(v);
-    if ((lane & 31) == 0) red.s[parity][lane >> 5][wave] = v;
+    if ((lane & 31) == 0) (lane ? s1 : s0)[wave] = v;
+}
+template <int NW, int H>
+__device__ __forceinline__ double chip_sum(CgRed& red, int parity, int tid, const double* a)
+{
+    double* s = red.s[parity][0];
+    if (H == 2) {
+        put_pair<NW>(s, s + NW, tid, a[0], a[H - 1]);
+    } else {
+        const double v = wave_sum(a[0]);
+        if ((tid & 63) == 0) s[tid >> 6] = v;
+    }
     __syncthreads();
-    double x = 0.0;
-    const double* q = red.s[parity][lane >> 5];
-#pragma unroll
-    for (int i = 0; i < NW; ++i) x += q[i];
-    a = readlane_d(x, 0);
-    b = readlane_d(x, 32);
+    return uniformd(sum_in_order<H * NW>(s));
+}
+// two sums; the halves of the wave add one each
+template <int NW, int H>
+__device__ __forceinline__ void chip_sum2(CgRed& red, int parity, int tid, double* a, double* b)
+{
+    double *sa = red.s[parity][0], *sb = red.s[parity][1];
+    if (H == 2) {
+        put_pair<NW>(sa, sa + NW, tid, a[0], a[H - 1]);
+        put_pair<NW>(sb, sb + NW, tid, b[0], b[H - 1]);
+    } else {
+        put_pair<NW>(sa, sb, tid, a[0], b[0]);
+    }
+    __syncthreads();
+    const double x = sum_in_order<H * NW>((tid & 32) ? sb : sa);
+    a[0] = readlane_d(x, 0);
+    b[0] = readlane_d(x, 32);
 }
 
 template <bool TAN, int T, int SN>
-__device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T>& X, CgRed& red)
+__device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T * SN>& X, CgRed& red)
 {
-    constexpr int NW = T / 64;
+    constexpr int NW = T / 64, H = SN > 2 ? 2 : 1;   // H partial sums per thread (chip_sum)
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -851,9 +897,9 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
     __syncthreads();
 
     // opaque zeros: no zero vectors are held in registers across tasks
-    double bb = 0.0;
+    double b2[2] = {0.0, 0.0};
     float zf = 0.f;
-    asm volatile("" : "+v"(bb), "+v"(zf));
+    asm volatile("" : "+v"(b2[0]), "+v"(b2[1]), "+v"(zf));
     // right-hand side (FP64)
     {
         double F[9], G[9];
@@ -872,7 +918,11 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
                     b64[3 * a + p] = b[p];
                     x64[3 * a + p] = zx;
                 }
-                bb += b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+                const double bn = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+                if (k % H)
+                    b2[1] += bn;
+                else
+                    b2[0] += bn;
                 const int deg = (int)(c.incoff[a + 1] - c.incoff[a]);
                 if (deg > 4) {
                     atomicMin(&X.x4, a);
@@ -884,13 +934,13 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
         asm volatile("" : "+v"(zx));
         if (tid < 3) x64[3 * nf + tid] = zx;
     }
-    block_sum1<NW>(red, parity, bb);
+    const double bb = chip_sum<NW, H>(red, parity, tid, b2);
     parity ^= 1;
 
     // records, blocks and extra records on chip (read once per task)
     const int x4 = __builtin_amdgcn_readfirstlane(X.x4), nx = nf - x4;
     const int xrows = (__builtin_amdgcn_readfirstlane(X.xd) - 1) / 4;
-    const bool xtab = xrows * nx <= ChipExtra<T>::XN;
+    const bool xtab = xrows * nx <= ChipExtra<T * SN>::XN;
     float rx[SN][4], ry[SN][4], rz_[SN][4], rc[SN][4], rg[SN][4];
     uint32_t ro[SN][2];   // LDS byte offsets of the other ends, two per word
     float Pb[SN][6];
@@ -964,7 +1014,7 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
         asm volatile("" : "+v"(tid));
         // FP64 residual of the FP64 solution (x64 complete: barrier above);
         // d = 0, p = z = P r
-        double rr = 0.0, rz = 0.0;
+        double rr2[2] = {0.0, 0.0}, rz2[2] = {0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < SN; ++k) {
             const int a = tid + T * k;
@@ -973,13 +1023,15 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
             double ra[3] = {z0, z0, z0};
             if (a < nf) residual_node(A, c, a, x64, b64, outer == 0, ra);
             for (int p = 0; p < 3; ++p) R[k][p] = (float)ra[p];
-            rr += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
+            rr2[k % H] += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
             apply_block(Pb[k], R[k], P[k]);
-            rz += (double)R[k][0] * P[k][0] + (double)R[k][1] * P[k][1] + (double)R[k][2] * P[k][2];
+            rz2[k % H] += (double)R[k][0] * P[k][0] + (double)R[k][1] * P[k][1] + (double)R[k][2] * P[k][2];
             __builtin_amdgcn_sched_barrier(0);
         }
-        half_sums<NW>(red, parity, tid, rr, rz);
+        chip_sum2<NW, H>(red, parity, tid, rr2, rz2);
         parity ^= 1;
+        const double rr = rr2[0];
+        double rz = rz2[0];
         if (rr <= tol2 * bb) {
             done = true;
             break;
@@ -1007,7 +1059,7 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
 #pragma unroll
             for (int k = 0; k < SN; ++k) *(f32x3*)&zl[tid + T * k] = f32x3{P[k][0], P[k][1], P[k][2]};
             __syncthreads();
-            double pq = 0.0;
+            double pq2[2] = {0.0, 0.0};
 #pragma unroll
             for (int k = 0; k < SN; ++k) {
                 if (wd[k] > 0) {
@@ -1043,10 +1095,10 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
                         }
                     }
                     for (int p = 0; p < 3; ++p) Q[k][p] = s[p];
-                    pq += (double)P[k][0] * s[0] + (double)P[k][1] * s[1] + (double)P[k][2] * s[2];
+                    pq2[k % H] += (double)P[k][0] * s[0] + (double)P[k][1] * s[1] + (double)P[k][2] * s[2];
                 }
             }
-            block_sum1<NW>(red, parity, pq);
+            const double pq = chip_sum<NW, H>(red, parity, tid, pq2);
             parity ^= 1;
             if (!(pq > 0.0)) {
                 status = ST_CG_INDEFINITE;
@@ -1054,26 +1106,29 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
                 break;
             }
             const float af = (float)(rz / pq);
-            double rn = 0.0, rzn = 0.0;
-            float Z[SN][3];
+            double rn2[2] = {0.0, 0.0}, rzn2[2] = {0.0, 0.0};
+            float (&Z)[SN][3] = Q;   // (q is done with)
 #pragma unroll
-            for (int k = 0; k < SN; ++k) {
-                for (int p = 0; p < 3; ++p) {
-                    D[k][p] = fmaf(af, P[k][p], D[k][p]);
-                    R[k][p] = fmaf(-af, Q[k][p], R[k][p]);
+            for (int k = 0; k < SN; ++k)
+                if (k == 0 || wd[k] > 0) {   // (nothing to do for a wave without nodes in the slot)
+                    for (int p = 0; p < 3; ++p) {
+                        D[k][p] = fmaf(af, P[k][p], D[k][p]);
+                        R[k][p] = fmaf(-af, Q[k][p], R[k][p]);
+                    }
+                    apply_block(Pb[k], R[k], Z[k]);
+                    rn2[k % H] += (double)R[k][0] * R[k][0] + (double)R[k][1] * R[k][1] + (double)R[k][2] * R[k][2];
+                    rzn2[k % H] += (double)R[k][0] * Z[k][0] + (double)R[k][1] * Z[k][1] + (double)R[k][2] * Z[k][2];
                 }
-                apply_block(Pb[k], R[k], Z[k]);
-                rn += (double)R[k][0] * R[k][0] + (double)R[k][1] * R[k][1] + (double)R[k][2] * R[k][2];
-                rzn += (double)R[k][0] * Z[k][0] + (double)R[k][1] * Z[k][1] + (double)R[k][2] * Z[k][2];
-            }
-            half_sums<NW>(red, parity, tid, rn, rzn);
+            chip_sum2<NW, H>(red, parity, tid, rn2, rzn2);
             parity ^= 1;
+            const double rn = rn2[0], rzn = rzn2[0];
             if (rn <= rr0 || rn <= 0.25 * tol2 * bb) break;
             const float bf = (float)(rzn / rz);
             rz = rzn;
 #pragma unroll
             for (int k = 0; k < SN; ++k)
-                for (int p = 0; p < 3; ++p) P[k][p] = fmaf(bf, P[k][p], Z[k][p]);
+                if (k == 0 || wd[k] > 0)
+                    for (int p = 0; p < 3; ++p) P[k][p] = fmaf(bf, P[k][p], Z[k][p]);
         }
         // x += d
         asm volatile("" : "+v"(tid));
@@ -1105,11 +1160,11 @@ __device__ void cg_chip_task(TanArgs& A, int r, int col, float4* zl, ChipExtra<T
 }
 
 template <bool TAN, int T, int SN>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_chip_kernel(TangentArgs)
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(SN > 2 ? 2 : 4))) void cg_chip_kernel(TangentArgs)
 {
     TanArgs& A = *kernel_args<TangentArgs>();
     __shared__ float4 zl[T * SN + 1];   // the last entry stays zero
-    __shared__ ChipExtra<T> X;
+    __shared__ ChipExtra<T * SN> X;
     __shared__ CgRed red;
     __shared__ int task;
     if (threadIdx.x == 0) zl[T * SN] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1240,9 +1295,7 @@ __device__ __forceinline__ bool cg_spread_task(KernArgsT<SpreadCgArgs>& AA, Team
         bool ok = true;
         if (wave == 0) {
             if (lane < N) {
-                double x = 0.0;
-#pragma unroll
-                for (int i = 0; i < NW; ++i) x += red.v[parity][lane][i];
+                const double x = sum_in_order<NW>(red.v[parity][lane]);
                 put_word(words + 2 * (N * rank + lane), tm.tag, (unsigned)__double2loint(x));
                 put_word(words + 2 * (N * rank + lane) + 1, tm.tag, (unsigned)__double2hiint(x));
             }
@@ -1274,12 +1327,17 @@ __device__ __forceinline__ bool cg_spread_task(KernArgsT<SpreadCgArgs>& AA, Team
         }
         if (!ok) red.bad = 1;
         __syncthreads();
+        // row q of the wave adds the members' parts of sum q (the same tree in
+        // every member)
+        {
+            const int q = lane >> 4, p = lane & 15;
+            double x = q < N && p < k ? red.sum[parity][q < N ? q : 0][p] : 0.0;
+            x += dpp_mov<kDppRor8>(x);
+            x += dpp_mov<kDppRor4>(x);
+            x += dpp_mov<kDppXor2>(x);
+            x += dpp_mov<kDppXor1>(x);
 #pragma unroll
-        for (int q = 0; q < N; ++q) {
-            double x = 0.0;
-#pragma unroll 1
-            for (int p = 0; p < k; ++p) x += red.sum[parity][q][p];
-            v[q] = uniformd(x);
+            for (int i = 0; i < N; ++i) v[i] = readlane_d(x, 16 * i);
         }
         parity ^= 1;
         return __builtin_amdgcn_readfirstlane(red.bad) == 0;
@@ -2296,7 +2354,7 @@ const void* res_kernel(int v, bool vjp)
     switch (v) {
     case 0: return vjp ? (const void*)cg_chip_kernel<false, 256, 2> : (const void*)cg_chip_kernel<true, 256, 2>;
     case 1: return vjp ? (const void*)cg_chip_kernel<false, 512, 2> : (const void*)cg_chip_kernel<true, 512, 2>;
-    case 2: return vjp ? (const void*)cg_chip_kernel<false, 1024, 2> : (const void*)cg_chip_kernel<true, 1024, 2>;
+    case 2: return vjp ? (const void*)cg_chip_kernel<false, 512, 4> : (const void*)cg_chip_kernel<true, 512, 4>;
     case 3: return vjp ? res_fn<false, 1024, 4, true>() : res_fn<true, 1024, 4, true>();
     default: return vjp ? res_fn<false, 1024, 8, true>() : res_fn<true, 1024, 8, true>();
     }
@@ -2304,7 +2362,7 @@ const void* res_kernel(int v, bool vjp)
 
 }  // namespace
 
-const TangentVariant kTanRes[kNumTanRes] = {{256, 2}, {512, 2}, {1024, 2}, {1024, 4}, {1024, 8}};
+const TangentVariant kTanRes[kNumTanRes] = {{256, 2}, {512, 2}, {512, 4}, {1024, 4}, {1024, 8}};
 
 hipError_t launch_tangent_prep(const TangentArgs& a, hipStream_t s)
 {
