@@ -3005,7 +3005,7 @@ int rve_batch_import_state(rve_batch* b, const double* F, const double* h, const
 // RVEs of the spread tangent: those beyond every resident build that have a
 // partition (us per iteration and column, streamed -> spread: one RVE of 4900 free
 // nodes 22 -> 7.2, of 16 000 76 -> 10; 28 at once 46 -> 37 and 184 -> 65).  Not
-// those of 2048 to 4096 free nodes: 10 to 15 us on one CU, about 2 x 8 on two.
+// those of 2048 to 4096 free nodes: 7 to 10 us on one CU, about 2 x 7 on two.
 static bool tangent_spread_rve(const rve_batch* b, int64_t r)
 {
     if (!b->t_spread_ok || !b->spread_mem || b->spread_k[r] == 0) return false;

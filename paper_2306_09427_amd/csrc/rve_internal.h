@@ -85,8 +85,7 @@ struct TangentArgs {
     int2* recB;                  // [NREC] (other end, bits of FP32 T/l)
     float4* precond;             // [NFREE][2] inverse 3x3 diagonal block: (00, 01, 02, 11), (12, 22, -, -)
     double* par64;               // [NF][6] FP64 fiber operators: n, k_t/L0, T/l, T
-    double* slot_ws64;           // per workgroup: FP64 x and b [3 slot_nodes] each (resident
-                                 // kernels: then FP32 d [slot_nodes] float4)
+    double* slot_ws64;           // per workgroup: FP64 x and b [3 slot_nodes] each
     float4* slot_ws32;           // [grid][5][slot_nodes] per-wavefront FP32 p, q, r, d, z (wave kernel)
     int64_t slot_nodes;          // free-node capacity of a slot + 1
     int32_t build_static;        // 1: fill rec_static from the incidence first

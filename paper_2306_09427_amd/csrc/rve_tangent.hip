@@ -1655,12 +1655,19 @@ __global__ __launch_bounds__(kCgT) __attribute__((amdgpu_waves_per_eu(2))) void 
 }
 
 // ------------------------------------------------------------------ resident tasks
-// One workgroup of T threads per task; thread tid owns free nodes
-// tid + T k (k < SN), so wavefront w owns ELL chunks w + (T/64) k.  The
-// residual and the product of the inner solve stay in registers, p (which the
-// matrix-free product gathers) lives in LDS, the correction d in the
-// workgroup's global slot, and z = P r is recomputed where it is needed (PL,
-// the only layout: four node slots and more leave no registers for the rest).
+// One workgroup of T threads per task, for the RVEs whose records no longer fit
+// the registers; thread tid owns free nodes tid + T k (k < SN), so wavefront w
+// owns ELL chunks w + (T/64) k.  The residual, the product, the correction and
+// the inverse blocks stay in registers, p (which the matrix-free product
+// gathers) lives in LDS (PL, the only layout), and the records are read from L2,
+// those of the next slot while the current one is worked on.
+//
+// Eight nodes in 512 threads, with the sums in the order of 1024 threads (as
+// cg_chip_task).  Four nodes in 1024 threads left no registers for the
+// correction, the blocks and the next records, and read the first two from
+// global memory as well.  Microseconds per iteration and column, four in 1024 ->
+// eight in 512: 8.3 -> 6.6 at 2532 free nodes alone, 10.4 -> 7.6 on a full chip;
+// 11.0 -> 8.5 and 16 -> 10.2 at 4090.
 //
 // The inner solve is plain preconditioned CG with a fresh product q = K p
 // every iteration: three workgroup barriers per iteration (p exchanged, p.q
@@ -1670,14 +1677,14 @@ __global__ __launch_bounds__(kCgT) __attribute__((amdgpu_waves_per_eu(2))) void 
 template <bool TAN, int T, int SN, bool PL>
 __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
 {
-    static_assert(PL, "p in LDS, d in the slot");
-    constexpr int NW = T / 64;
+    static_assert(PL, "p in LDS");
+    constexpr int NW = T / 64, H = T == 512 ? 2 : 1;   // H partial sums per thread (chip_sum)
     // thread id made opaque per task: otherwise the compiler hoists every
     // per-thread address of every slot out of the persistent task loop and
     // keeps them live (spilled) across the whole kernel
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (__builtin_amdgcn_readfirstlane(A.solve_status[r]) != 0) {
         no_state<TAN>(A, r, col, tid);
         return;
@@ -1688,7 +1695,7 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
     const float4* Pc = A.precond + 2 * c.a0;
     const int64_t cf = uni64(A.chunk_first[r]);
     const int64_t S = A.slot_nodes;
-    double* x64 = A.slot_ws64 + (int64_t)blockIdx.x * 8 * S;   // x, b (3 S each), d32 (S float4)
+    double* x64 = A.slot_ws64 + (int64_t)blockIdx.x * 8 * S;   // x, b (3 S each)
     double* b64 = x64 + 3 * S;
 
     // ELL chunk of each slot (uniform over the wavefront); width 0 past the
@@ -1706,13 +1713,13 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
         if (64 * ch < nf) {
             const int64_t c0 = uni64(A.chunk_rec[cf + ch]);
             wd[k] = (int)((uni64(A.chunk_rec[cf + ch + 1]) - c0) >> 6);
-            rb[k] = (int)(c0 - rec0) + lane;
+            rb[k] = (int)(c0 - rec0);
         }
     }
     int parity = 0;
 
     // right-hand side (FP64)
-    double bb = 0.0;
+    double b2[2] = {0.0, 0.0};
     {
         double F[9], G[9];
         for (int k = 0; k < 9; ++k) F[k] = A.F[9 * r + k];
@@ -1728,34 +1735,30 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
                     b64[3 * a + p] = b[p];
                     x64[3 * a + p] = 0.0;
                 }
-                bb += b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+                const double bn = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+                if (k % H)
+                    b2[1] += bn;
+                else
+                    b2[0] += bn;
             }
         }
         if (tid < 3) x64[3 * nf + tid] = 0.0;
     }
-    {
-        block_sum1<NW>(red, parity, bb);
-        parity ^= 1;
-    }
+    const double bb = chip_sum<NW, H>(red, parity, tid, b2);
+    parity ^= 1;
 
-    float R[SN][3], Q[SN][3];
-    float4* d32 = reinterpret_cast<float4*>(b64 + 3 * S);   // [S]
-    auto own_p = [&](int k) __attribute__((always_inline)) -> float4 { return zl[tid + T * k]; };
-    // z = P_a r for slot k (block reloaded every time: keeping the blocks of
-    // all slots live across the loop costs 8 registers per slot)
-    auto precond_r = [&](int k) __attribute__((always_inline)) -> float4 {
+    float R[SN][3], Q[SN][3], D[SN][3], Pb[SN][6];
+#pragma unroll
+    for (int k = 0; k < SN; ++k) {
         const int64_t a = tid + T * k;
         float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f), p1 = p0;
         if (a < nf) {
-            const float4* pp = Pc + 2 * a;
-            asm volatile("" : "+v"(pp));
-            p0 = pp[0];
-            p1 = pp[1];
+            p0 = Pc[2 * a];
+            p1 = Pc[2 * a + 1];
         }
-        return make_float4(p0.x * R[k][0] + p0.y * R[k][1] + p0.z * R[k][2],
-                           p0.y * R[k][0] + p0.w * R[k][1] + p1.x * R[k][2],
-                           p0.z * R[k][0] + p1.x * R[k][1] + p1.y * R[k][2], 0.f);
-    };
+        Pb[k][0] = p0.x; Pb[k][1] = p0.y; Pb[k][2] = p0.z; Pb[k][3] = p0.w; Pb[k][4] = p1.x; Pb[k][5] = p1.y;
+    }
+    auto own_p = [&](int k) __attribute__((always_inline)) -> f32x3 { return *(const f32x3*)&zl[tid + T * k]; };
     int status = ST_CONVERGED;
     // per-task copy: a kernel-lifetime value would be kept live across tasks
     double cgt = A.cg_tol;
@@ -1770,7 +1773,7 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
         asm volatile("" : "+v"(tid));
         // FP64 residual of the FP64 solution (x64 complete: barrier above);
         // d = 0, p = z = P r
-        double rr = 0.0, rz = 0.0;
+        double rr2[2] = {0.0, 0.0}, rz2[2] = {0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < SN; ++k) {
             const int64_t a = tid + T * k;
@@ -1778,18 +1781,19 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
             if (a < nf) residual_node(A, c, a, x64, b64, outer == 0, ra);
             for (int p = 0; p < 3; ++p) {
                 R[k][p] = (float)ra[p];
-                Q[k][p] = 0.f;
+                Q[k][p] = D[k][p] = 0.f;
             }
-            rr += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
-            const float4 z = precond_r(k);
-            rz += (double)R[k][0] * z.x + (double)R[k][1] * z.y + (double)R[k][2] * z.z;
-            zl[tid + T * k] = z;
-            if (a < nf) d32[a] = make_float4(0.f, 0.f, 0.f, 0.f);
+            rr2[k % H] += ra[0] * ra[0] + ra[1] * ra[1] + ra[2] * ra[2];
+            float z[3];
+            apply_block(Pb[k], R[k], z);
+            rz2[k % H] += (double)R[k][0] * z[0] + (double)R[k][1] * z[1] + (double)R[k][2] * z[2];
+            *(f32x3*)&zl[tid + T * k] = f32x3{z[0], z[1], z[2]};
+            __builtin_amdgcn_sched_barrier(0);
         }
-        {
-            block_sum2<NW>(red, parity, rr, rz);
-            parity ^= 1;
-        }
+        chip_sum2<NW, H>(red, parity, tid, rr2, rz2);
+        parity ^= 1;
+        const double rr = rr2[0];
+        double rz = rz2[0];
         if (rr <= tol2 * bb) {
             done = true;
             break;
@@ -1807,78 +1811,83 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
             ++it_total;
             asm volatile("" : "+v"(tid));
             __syncthreads();
-            double pq = 0.0;
+            double pq2[2] = {0.0, 0.0};
+            // the first four records of a slot (chunk widths are multiples of 4)
+            float4 nA[2][4];
+            int2 ob[2][4];
+            const uint32_t ln = tid & 63;   // (an offset from a scalar base)
+            auto rec_a = [&](int i) __attribute__((always_inline)) { return *(const float4*)((const char*)(recA + i) + 16 * ln); };
+            auto rec_b = [&](int i) __attribute__((always_inline)) { return *(const int2*)((const char*)(recB + i) + 8 * ln); };
+            auto load = [&](int k, int j) __attribute__((always_inline)) {
+                if (wd[k] > 0)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        nA[j][u] = rec_a(rb[k] + 64 * u);
+                        ob[j][u] = rec_b(rb[k] + 64 * u);
+                    }
+            };
+            load(0, 0);
 #pragma unroll
             for (int k = 0; k < SN; ++k) {
-                const float4 pk = own_p(k);
-                float sx = 0.f, sy = 0.f, sz = 0.f;
-                // records in groups of RB (chunk widths are multiples of 4)
-                constexpr int RB = SN > 2 ? 2 : 4;
+                if (k + 1 < SN) load(k + 1, (k + 1) & 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (wd[k] > 0) {
+                    const int j = k & 1;
+                    const f32x3 pk = own_p(k);
+                    const float pv[3] = {pk.x, pk.y, pk.z};
+                    float q[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float g = __int_as_float(ob[j][u].y);
+                        add_record(nA[j][u].x, nA[j][u].y, nA[j][u].z, nA[j][u].w - g, g, pv, *(const f32x3*)&zl[ob[j][u].x], q);
+                    }
 #pragma unroll 1
-                for (int s0 = 0; s0 < wd[k]; s0 += RB) {
-                    float4 nA[RB];
-                    int2 ob[RB];
-#pragma unroll
-                    for (int u = 0; u < RB; ++u) {
-                        nA[u] = recA[rb[k] + 64 * (s0 + u)];
-                        ob[u] = recB[rb[k] + 64 * (s0 + u)];
+                    for (int s0 = 4; s0 < wd[k]; ++s0) {
+                        const float4 ra = rec_a(rb[k] + 64 * s0);
+                        const int2 o = rec_b(rb[k] + 64 * s0);
+                        const float g = __int_as_float(o.y);
+                        add_record(ra.x, ra.y, ra.z, ra.w - g, g, pv, *(const f32x3*)&zl[o.x], q);
                     }
-#pragma unroll
-                    for (int u = 0; u < RB; ++u) {
-                        const float4 po = zl[ob[u].x];
-                        const float g = __int_as_float(ob[u].y);
-                        const float dx = pk.x - po.x, dy = pk.y - po.y, dz = pk.z - po.z;
-                        const float cn = (nA[u].w - g) * (nA[u].x * dx + nA[u].y * dy + nA[u].z * dz);
-                        sx += fmaf(g, dx, cn * nA[u].x);
-                        sy += fmaf(g, dy, cn * nA[u].y);
-                        sz += fmaf(g, dz, cn * nA[u].z);
-                    }
+                    for (int p = 0; p < 3; ++p) Q[k][p] = q[p];
+                    pq2[k % H] += (double)pk.x * q[0] + (double)pk.y * q[1] + (double)pk.z * q[2];
                 }
-                Q[k][0] = sx;
-                Q[k][1] = sy;
-                Q[k][2] = sz;
-                pq += (double)pk.x * sx + (double)pk.y * sy + (double)pk.z * sz;
+                __builtin_amdgcn_sched_barrier(0);
             }
-            {
-                block_sum1<NW>(red, parity, pq);
-                parity ^= 1;
-            }
+            const double pq = chip_sum<NW, H>(red, parity, tid, pq2);
+            parity ^= 1;
             if (!(pq > 0.0)) {
                 status = ST_CG_INDEFINITE;
                 done = true;
                 break;
             }
             const float af = (float)(rz / pq);
-            double rn = 0.0, rzn = 0.0;
+            double rn2[2] = {0.0, 0.0}, rzn2[2] = {0.0, 0.0};
+            float (&Z)[SN][3] = Q;   // (q is done with)
 #pragma unroll
-            for (int k = 0; k < SN; ++k) {
-                const float4 pk = own_p(k);
-                const int64_t a = tid + T * k;
-                if (a < nf) {
-                    float4 d = d32[a];
-                    d.x = fmaf(af, pk.x, d.x);
-                    d.y = fmaf(af, pk.y, d.y);
-                    d.z = fmaf(af, pk.z, d.z);
-                    d32[a] = d;
+            for (int k = 0; k < SN; ++k)
+                if (k == 0 || wd[k] > 0) {
+                    const f32x3 pk = own_p(k);
+                    D[k][0] = fmaf(af, pk.x, D[k][0]);
+                    D[k][1] = fmaf(af, pk.y, D[k][1]);
+                    D[k][2] = fmaf(af, pk.z, D[k][2]);
+                    for (int p = 0; p < 3; ++p) R[k][p] = fmaf(-af, Q[k][p], R[k][p]);
+                    apply_block(Pb[k], R[k], Z[k]);
+                    rn2[k % H] += (double)R[k][0] * R[k][0] + (double)R[k][1] * R[k][1] + (double)R[k][2] * R[k][2];
+                    rzn2[k % H] += (double)R[k][0] * Z[k][0] + (double)R[k][1] * Z[k][1] + (double)R[k][2] * Z[k][2];
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                for (int p = 0; p < 3; ++p) R[k][p] = fmaf(-af, Q[k][p], R[k][p]);
-                const float4 z = precond_r(k);
-                rn += (double)R[k][0] * R[k][0] + (double)R[k][1] * R[k][1] + (double)R[k][2] * R[k][2];
-                rzn += (double)R[k][0] * z.x + (double)R[k][1] * z.y + (double)R[k][2] * z.z;
-            }
-            {
-                block_sum2<NW>(red, parity, rn, rzn);
-                parity ^= 1;
-            }
+            chip_sum2<NW, H>(red, parity, tid, rn2, rzn2);
+            parity ^= 1;
+            const double rn = rn2[0], rzn = rzn2[0];
             if (rn <= 1e-6 * rr0 || rn <= 0.25 * tol2 * bb) break;
             const float bf = (float)(rzn / rz);
             rz = rzn;
 #pragma unroll
-            for (int k = 0; k < SN; ++k) {
-                const float4 z = precond_r(k);
-                const float4 pk = zl[tid + T * k];
-                zl[tid + T * k] = make_float4(fmaf(bf, pk.x, z.x), fmaf(bf, pk.y, z.y), fmaf(bf, pk.z, z.z), 0.f);
-            }
+            for (int k = 0; k < SN; ++k)
+                if (k == 0 || wd[k] > 0) {
+                    const f32x3 pk = own_p(k);
+                    *(f32x3*)&zl[tid + T * k] = f32x3{fmaf(bf, pk.x, Z[k][0]), fmaf(bf, pk.y, Z[k][1]), fmaf(bf, pk.z, Z[k][2])};
+                }
         }
         // x += d
         asm volatile("" : "+v"(tid));
@@ -1886,10 +1895,7 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
         for (int k = 0; k < SN; ++k) {
             const int64_t a = tid + T * k;
             if (a < nf) {
-                const float4 d = d32[a];
-                x64[3 * a] += (double)d.x;
-                x64[3 * a + 1] += (double)d.y;
-                x64[3 * a + 2] += (double)d.z;
+                for (int p = 0; p < 3; ++p) x64[3 * a + p] += (double)D[k][p];
             }
         }
         __syncthreads();
@@ -1914,7 +1920,7 @@ __device__ void cg_res_task(TanArgs& A, int r, int col, float4* zl, CgRed& red)
 }
 
 template <bool TAN, int T, int SN, bool PL>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void cg_res_kernel(TangentArgs)
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 2 : 4))) void cg_res_kernel(TangentArgs)
 {
     TanArgs& A = *kernel_args<TangentArgs>();
     extern __shared__ float4 zl[];   // [T * SN + 1]; the last entry stays zero
@@ -2355,14 +2361,14 @@ const void* res_kernel(int v, bool vjp)
     case 0: return vjp ? (const void*)cg_chip_kernel<false, 256, 2> : (const void*)cg_chip_kernel<true, 256, 2>;
     case 1: return vjp ? (const void*)cg_chip_kernel<false, 512, 2> : (const void*)cg_chip_kernel<true, 512, 2>;
     case 2: return vjp ? (const void*)cg_chip_kernel<false, 512, 4> : (const void*)cg_chip_kernel<true, 512, 4>;
-    case 3: return vjp ? res_fn<false, 1024, 4, true>() : res_fn<true, 1024, 4, true>();
+    case 3: return vjp ? res_fn<false, 512, 8, true>() : res_fn<true, 512, 8, true>();
     default: return vjp ? res_fn<false, 1024, 8, true>() : res_fn<true, 1024, 8, true>();
     }
 }
 
 }  // namespace
 
-const TangentVariant kTanRes[kNumTanRes] = {{256, 2}, {512, 2}, {512, 4}, {1024, 4}, {1024, 8}};
+const TangentVariant kTanRes[kNumTanRes] = {{256, 2}, {512, 2}, {512, 4}, {512, 8}, {1024, 8}};
 
 hipError_t launch_tangent_prep(const TangentArgs& a, hipStream_t s)
 {
