@@ -44,7 +44,7 @@ PEAK_HBM = 8.0e12            # B/s, MI355X HBM3E
 PEAK_FP32_PUBLISHED = 157.3e12
 PEAK_FP32_NONPACKED = 78.6e12
 
-VARIANTS = [(256, 4, 2), (512, 4, 2), (768, 4, 2), (512, 6, 3), (1024, 4, 2), (1024, 6, 3)]
+VARIANTS = [(256, 4, 2), (512, 4, 2), (768, 4, 2), (512, 6, 3), (1024, 4, 2), (1024, 6, 3), (512, 8, 4)]
 
 
 def rb_variant_name(v):
@@ -239,7 +239,7 @@ def main():
     # the relaxation of one step: every launch group (concurrent streams),
     # from the first group's start to the join, HIP events on those streams
     def gname(g):
-        return (f"dr_resident_kernel<float,{rb_variant_name(int(g_var[g]))}>" if g_var[g] >= 0
+        return (f"dr_chip_kernel<float,{rb_variant_name(int(g_var[g]))}>" if g_var[g] >= 0
                 else "dr_streamed_kernel<float,1024>" if g_var[g] == rb.GROUP_STREAMED
                 else "dr_incidence_kernel" if g_var[g] == rb.GROUP_INCIDENCE
                 else "dr_incidence_global_kernel" if g_var[g] == rb.GROUP_INCIDENCE_GLOBAL

@@ -139,7 +139,7 @@ def main(argv=None) -> int:
 
 # resident kernel variants (threads, fiber slots, node slots per thread), in
 # the library's order
-VARIANTS = [(256, 4, 2), (512, 4, 2), (768, 4, 2), (512, 6, 3), (1024, 4, 2), (1024, 6, 3)]
+VARIANTS = [(256, 4, 2), (512, 4, 2), (768, 4, 2), (512, 6, 3), (1024, 4, 2), (1024, 6, 3), (512, 8, 4)]
 
 
 def rb_variant(v: int) -> str:
