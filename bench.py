@@ -53,8 +53,8 @@ def rb_variant_name(v):
 
 # Committed rocprofv3 summaries: key -> (summary file, kernel source)
 TRAFFIC_PROFILES = {
-    "relax_cfg2": ("dr_resident_kernel_4096rve_200-400seeds_mixed.md", "rve_kernels.hip"),
-    "relax_cfg3": ("dr_incidence_kernel_512rve_2000seeds_mixed.md", "rve_kernels.hip"),
+    "relax_cfg2": ("dr_chip_kernel_4096rve_200-400seeds_mixed.md", "rve_resident.hip"),
+    "relax_cfg3": ("dr_spread_kernel_512rve_2000seeds_mixed.md", "rve_spread.hip"),
     "tangent": ("tangent_4096rve_200-400seeds_mixed.md", "rve_tangent.hip"),
 }
 
