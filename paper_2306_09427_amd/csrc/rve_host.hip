@@ -3079,6 +3079,11 @@ static void tangent_groups(rve_batch* b)
         }
     }
     first[kTanGroups] = (int64_t)order.size();
+    for (int mode = 0; mode < 2; ++mode) {   // nine columns per RVE, then one
+        b->t_spread_slots[mode] = 0;
+        for (int64_t q = first[kTanSpread]; q < first[kTanGroups]; ++q)
+            b->t_spread_slots[mode] += (mode == 0 ? 9 : 1) * (int64_t)b->spread_k[order[q]];
+    }
     b->t_order_host = order;
     b->t_group_first = first;
 }
@@ -3116,7 +3121,6 @@ static int ensure_tangent_ws(rve_batch* b, size_t slot_bytes)
         hipError_t e = hipMemcpy(b->t_order, b->t_order_host.data(), 4 * (size_t)b->R, hipMemcpyHostToDevice);
         // first slots of the spread tasks: nine columns per RVE, then one
         std::vector<int32_t> tf;
-        b->t_spread_slots[0] = b->t_spread_slots[1] = 0;
         for (int mode = 0; mode < 2; ++mode) {
             int32_t at = 0;
             for (int64_t q = b->t_group_first[kTanSpread]; q < b->t_group_first[kTanSpread + 1]; ++q)
@@ -3125,7 +3129,6 @@ static int ensure_tangent_ws(rve_batch* b, size_t slot_bytes)
                     at += b->spread_k[b->t_order_host[q]];
                 }
             tf.push_back(at);
-            b->t_spread_slots[mode] = at;
         }
         if (e == hipSuccess) e = hipMemcpy(b->t_spread_first, tf.data(), 4 * tf.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess)
@@ -3154,6 +3157,18 @@ static int ensure_tangent_ws(rve_batch* b, size_t slot_bytes)
         b->t_slot_bytes = slot_bytes;
     }
     return RVE_OK;
+}
+
+// Workgroups of the spread launch, and the bytes of their x and b (behind the
+// slots of the streamed launch).
+static int tangent_spread_grid(const rve_batch* b, int mode)
+{
+    return (int)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]);
+}
+
+static size_t tangent_spread_bytes(const rve_batch* b, int mode)
+{
+    return tangent_spread_slot_bytes() * (size_t)tangent_spread_grid(b, mode);
 }
 
 // Launch plan of a tangent (mode 0, nine right-hand sides per RVE) or VJP
@@ -3210,8 +3225,7 @@ static int tangent_plan(rve_batch* b, int mode, int engine, int rhs_opt, std::ve
             for (int64_t r = 0; r < b->R; ++r) S[v] = std::max<int64_t>(S[v], b->nf_of[r] + 1);
             bytes = 128 * (size_t)S[v] * (size_t)grid[v];
         }
-        if (v == kTanSpread)   // the members' x and b behind the slots of the streamed launch
-            bytes += tangent_spread_slot_bytes() * (size_t)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]);
+        if (v == kTanSpread) bytes += tangent_spread_bytes(b, mode);
         *slot_bytes += (bytes + 255) & ~size_t(255);   // the launches run at once: slots of their own
     }
     return RVE_OK;
@@ -3415,7 +3429,7 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
         int64_t w = 0;
         for (int64_t q = gf[v]; q < gf[v + 1]; ++q) w += b->nf_of[b->t_order_host[q]];
         order.push_back({-w, v});
-        total += ((v == kTanSpread ? (int)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]) : grid[v]) + 7) / 8 * 8;   // workgroups go to the 8 XCDs in turn
+        total += ((v == kTanSpread ? tangent_spread_grid(b, mode) : grid[v]) + 7) / 8 * 8;   // workgroups go to the 8 XCDs in turn
     }
     std::sort(order.begin(), order.end());
     const bool fork = order.size() > 1;
@@ -3434,7 +3448,8 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
         // every RVE of the launch must fit its slot (and, resident, its LDS)
         const size_t need =
             (v < kNumTanRes ? (blk[v] ? 80 * (size_t)kTanBlkRhs : 64) : 128) * (size_t)S[v] * (size_t)grid[v];
-        if (slot_off[v] + need > b->t_slot_bytes || b->t_max_nf[v] >= S[v])
+        const size_t spread = v == kTanSpread ? tangent_spread_bytes(b, mode) : 0;
+        if (slot_off[v] + need + spread > b->t_slot_bytes || b->t_max_nf[v] >= S[v])
             return fail(RVE_EINVAL, "internal: tangent slot smaller than an RVE of its group");
         a.order = b->t_order + gf[v];
         a.n_order = gf[v + 1] - gf[v];
@@ -3453,7 +3468,7 @@ static int run_cg(rve_batch* b, int mode, const double* gsigma, double* out, int
             sp.queue = b->dqueue + kTanGroups;
             sp.n_tasks = (int32_t)n_tasks;
             sp.n_areas = (int32_t)std::min<int64_t>(n_tasks, b->spread_areas);
-            sp.grid = (int32_t)std::min<int64_t>(b->n_cu, b->t_spread_slots[mode]);
+            sp.grid = tangent_spread_grid(b, mode);
             sp.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
             TangentArgs c = a;
             c.done = b->t_spread_first + 10 * a.n_order + 2;
