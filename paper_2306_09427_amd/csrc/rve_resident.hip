@@ -72,8 +72,12 @@ __device__ __forceinline__ Fiber<float> fiber_force(bool linear, float EA, float
 // estimate with a residual correction each, the quotient by Newton's
 // reciprocal with a residual correction, e^x - 1 by the Taylor series of the
 // argument reduced by a multiple of ln 2 (Cody and Waite's two-part ln 2).
+// x >= 0; beyond the largest double the result is infinite, as the library's:
+// the scale 2^k is applied as 2 * 2^(k - 1), which stays finite up to the
+// argument 710, where larger ones are cut (e^710 overflows).
 __device__ __forceinline__ double exp_minus_one(double x)
 {
+    x = fmin(x, 710.0);
     const double k = __builtin_rint(x * 1.4426950408889634);
     const double r = fma(-k, 1.90821492927058770002e-10, fma(-k, 6.93147180369123816490e-01, x));
     double p = 1.0 / 87178291200.0;   // 1/14!
@@ -90,8 +94,8 @@ __device__ __forceinline__ double exp_minus_one(double x)
     p = fma(p, r, 1.0 / 6.0);
     p = fma(p, r, 0.5);
     p = fma(p * r, r, r);
-    const double s = __builtin_amdgcn_ldexp(1.0, (int)fmin(k, 2000.0));
-    return fma(s, p, s - 1.0);
+    const double s = __builtin_amdgcn_ldexp(0.5, (int)k);
+    return 2.0 * fma(s, p, s - 0.5);
 }
 __device__ __forceinline__ Fiber<double> fiber_force(bool linear, double EA, double B, double EAoB, double Dx,
                                                      double Dy, double Dz, double Qn, double iL, double dhx,
