@@ -167,6 +167,7 @@ struct rve_batch {
     bool t_spread_ok = false;          // the spread tangent may run
     char* spread_mem = nullptr;
     int32_t *spread_k_dev = nullptr, *spread_rve = nullptr, *spread_first = nullptr;   // spread_k; tasks of a launch
+    double* spread_kept = nullptr;     // start of a warm solve (launch_keep_state)
     SpreadArgs spread_tab{};
 };
 
@@ -1141,7 +1142,8 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
                  o_halo = A.reserve(4 * H.halo.size() + 4), o_hx = A.reserve(4 * H.halo.size() + 4),
                  o_bnd = A.reserve(4 * H.bnd.size() + 4), o_os = A.reserve(2 * H.oslot.size() + 2),
                  o_bs = A.reserve(2 * H.bslot.size() + 2), o_x = A.reserve(8 * words), o_k = A.reserve(4 * (size_t)b->R),
-                 o_tr = A.reserve(4 * (size_t)count), o_tf = A.reserve(4 * (size_t)count + 4);
+                 o_tr = A.reserve(4 * (size_t)count), o_tf = A.reserve(4 * (size_t)count + 4),
+                 o_kept = A.reserve(24 * H.own.size());
     if (hipMalloc((void**)&b->spread_mem, A.used + 256) != hipSuccess) {
         b->spread_mem = nullptr;
         return fail(RVE_ENOMEM, "device allocation of the spread tables failed");
@@ -1179,6 +1181,7 @@ static int build_spread_tables(rve_batch* b, const HostPack& P)
     t.area_words = spread_words((int)mx);
     t.task_rve = b->spread_rve = carve<int32_t>(m, o_tr);
     t.task_first = b->spread_first = carve<int32_t>(m, o_tf);
+    b->spread_kept = carve<double>(m, o_kept);
     b->spread_k_dev = carve<int32_t>(m, o_k);
     b->spread_k = H.k;
     b->spread_areas = areas;
@@ -2220,7 +2223,10 @@ static int launch_spread_groups(rve_batch* b, const SolveArgs& a, int32_t* queue
     HIP_TRY(launch_team_slots(list0, n0, list1, n1, b->spread_k_dev, b->spread_rve, b->spread_first, s));
     HIP_TRY(launch_zero32(reinterpret_cast<int32_t*>(sa.xchg), 2 * (int64_t)sa.n_areas * sa.area_words, s));
     HIP_TRY(launch_set_status(b->spread_rve, sa.n_tasks, a.status, kStUnfinished, s));
+    const bool warm = a.init == RVE_INIT_WARM;
+    if (warm) HIP_TRY(launch_keep_state(sa, b->spread_kept, false, s));
     HIP_TRY(launch_spread(sa, s));
+    if (warm) HIP_TRY(launch_keep_state(sa, b->spread_kept, true, s));
     IncArgs it = b->inc_tab;
     it.only_unfinished = 1;
     for (int g : {gg, gl})

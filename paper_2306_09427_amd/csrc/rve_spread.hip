@@ -21,7 +21,9 @@
 // between the time step and the next force pass.  A member that gives up at a
 // poll leaves the RVE's status unfinished and stops, the others follow at
 // their next exchange, and the incidence kernel launched behind takes every
-// unfinished RVE.
+// unfinished RVE.  Members that had passed the last exchange by then have
+// stored their final positions; a warm start's are kept aside before the launch
+// and put back (keep_state), so that kernel starts from what the caller left.
 //
 // One launch runs teams of every size (rve_exchange.h): as a launch per size,
 // at most four at once, 256 RVEs of 100 to 3000 seeds took 135 ms, 71 ms so.
@@ -564,7 +566,32 @@ __global__ void set_status(const int32_t* list, int n, int32_t* status, int32_t 
     if (i < n) status[list[i]] = value;
 }
 
+// The free nodes' fluctuation of the listed RVEs into `kept` (in the order of
+// their parts' nodes), or back where the status is kStUnfinished.
+__global__ __launch_bounds__(256) void keep_state(const int32_t* list, const SpreadPart* parts, const int64_t* part_first,
+                                                  const int64_t* free_off, double* h, double* kept,
+                                                  const int32_t* unfinished)
+{
+    const int r = list[blockIdx.x];
+    if (unfinished && unfinished[r] != kStUnfinished) return;
+    const int64_t a0 = 3 * free_off[r], n = 3 * free_off[r + 1] - a0, k0 = 3 * parts[part_first[r]].own0;
+    for (int64_t q = blockIdx.y * 256 + threadIdx.x; q < n; q += 256 * gridDim.y) {
+        if (unfinished)
+            h[a0 + q] = kept[k0 + q];
+        else
+            kept[k0 + q] = h[a0 + q];
+    }
+}
+
 }  // namespace
+
+hipError_t launch_keep_state(const SpreadArgs& a, double* kept, bool restore, hipStream_t s)
+{
+    if (a.n_tasks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(keep_state, dim3((unsigned)a.n_tasks, 8), dim3(256), 0, s, a.task_rve, a.parts, a.part_first,
+                       a.s.net.free_off, a.s.h_state, kept, restore ? a.s.status : nullptr);
+    return hipGetLastError();
+}
 
 hipError_t launch_spread(const SpreadArgs& a, hipStream_t s)
 {
@@ -591,7 +618,8 @@ hipError_t spread_info(int* blocks_per_cu, size_t* private_bytes)
 {
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void*)dr_spread_kernel, T, 0);
     if (e != hipSuccess) return e;
-    return max_private_bytes({(const void*)dr_spread_kernel, (const void*)team_slots, (const void*)set_status}, private_bytes);
+    return max_private_bytes({(const void*)dr_spread_kernel, (const void*)team_slots, (const void*)set_status,
+                              (const void*)keep_state}, private_bytes);
 }
 
 }  // namespace rve
