@@ -178,10 +178,12 @@ constexpr int kResMaxFibers = 0x7fff;   // fiber ids and the zero slot fit the 1
 // starts at a compile-time offset, so an access is one VGPR address plus an
 // instruction offset.  Positions: NP slots and the zero slot NP that every
 // boundary end reads.  Fiber forces: NF slots, of which slot nfib stays zero
-// (the padding of short incidence lists), so an RVE has at most NF - 1 fibers.
-// One access unit is 16 bytes in FP32 (float4 records) and 8 in FP64
-// (structure of arrays).  The largest FP64 build holds fewer slots than its
-// threads could, because its arrays fill the 160 KB.
+// (the padding of short incidence lists): one more than the threads hold (two,
+// so that what follows stays aligned), but where the builds below have less
+// room and hold one fiber less.  The FP32 build of 4096 slots: its byte offsets
+// fill 16 bits.  The largest FP64 build: its arrays fill the 160 KB, and it
+// holds fewer slots than its threads could.  One access unit is 16 bytes in
+// FP32 (float4 records) and 8 in FP64 (structure of arrays).
 struct ResLayout {
     int NF, NP, unit;
     bool ids;   // incidence codes hold ids (the byte offsets of NF slots pass 16 bits)
@@ -189,8 +191,8 @@ struct ResLayout {
 __host__ __device__ constexpr bool res_lds_full(bool fp64, int threads, int sf) { return fp64 && threads * sf == 4096; }
 __host__ __device__ constexpr ResLayout res_layout(bool fp64, int threads, int sf, int sn)
 {
-    return {res_lds_full(fp64, threads, sf) ? 3968 : threads * sf, res_lds_full(fp64, threads, sf) ? 1920 : threads * sn,
-            fp64 ? 8 : 16, !fp64 && threads * sf > 4096};
+    return {res_lds_full(fp64, threads, sf) ? 3968 : threads * sf == 4096 ? 4096 : threads * sf + 2,
+            res_lds_full(fp64, threads, sf) ? 1920 : threads * sn, fp64 ? 8 : 16, !fp64 && threads * sf > 4096};
 }
 // Bytes of the positions, of both arrays, and the table sizes behind them:
 // boundary fibers and the incidences of nodes of degree above 4 (16 bits each).
@@ -409,7 +411,9 @@ extern const ResidentVariant kResident[kNumResident];
 inline bool resident_fixed(int v, bool fp64) { return fp64 ? v == 0 || v == 1 || v == 3 || v == 6 : v < 6; }
 inline int resident_fibers(int v, bool fp64)
 {
-    return res_layout(fp64, kResident[v].threads, kResident[v].sf, kResident[v].sn).NF - 1;
+    const ResidentVariant& rv = kResident[v];
+    const int nf = res_layout(fp64, rv.threads, rv.sf, rv.sn).NF - 1;
+    return nf < rv.threads * rv.sf ? nf : rv.threads * rv.sf;
 }
 inline int resident_nodes(int v, bool fp64)
 {
