@@ -20,14 +20,15 @@ Also measured: the same batch in FP64 at the same tolerance (the plain FP64
 batched speed baseline), the plain FP64 one-RVE-at-a-time engine on a few
 RVEs (extrapolated per fiber evaluation), kinetic damping and the
 stagnation stop (side lines, same accuracy count), the tangent dsigma/dF,
-a timed leg of 512 large RVEs (2000 seeds each) on the HBM-streamed
-kernel with its fraction of the HBM peak, and the CPU oracle on a bounded
-sample (cpu_baseline).  Prints one JSON line.
+a timed leg of 512 large RVEs (2000 seeds each, several CUs per RVE) and the
+same on the HBM-streamed kernel, and the CPU oracle on a bounded sample
+(cpu_baseline).  Prints one JSON line.
 """
 import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -238,9 +239,12 @@ def main():
     # dominant launch group and its roofline
     # the relaxation of one step: every launch group (concurrent streams),
     # from the first group's start to the join, HIP events on those streams
+    g_desc = groups.split(";")
+
     def gname(g):
         return (f"dr_chip_kernel<float,{rb_variant_name(int(g_var[g]))}>" if g_var[g] >= 0
                 else "dr_streamed_kernel<float,1024>" if g_var[g] == rb.GROUP_STREAMED
+                else "dr_spread_kernel" if re.match(r"incidence\((global,)?\d+(-\d+)?x", g_desc[g])
                 else "dr_incidence_kernel" if g_var[g] == rb.GROUP_INCIDENCE
                 else "dr_incidence_global_kernel" if g_var[g] == rb.GROUP_INCIDENCE_GLOBAL
                 else f"dr_team_kernel<float> x{-1 - int(g_var[g])}")
@@ -318,21 +322,29 @@ def main():
         # iterations summed over an RVE's nine right-hand sides, it_r / 9
         # block iterations of 20 N_f + 216 N_free bytes
         tan_bytes = float(((it / 9.0) * (20 * nfib + 216 * nfree)).sum())
+        # operations of one inner iteration of a column: 18 per fiber end, 30 per free node
+        tan_flops = float((it * (36.0 * nfib + 30.0 * nfree)).sum())
         out["tangent"] = {
             "workload": "dsigma/dF (9 right-hand sides) of every RVE of the batch at the mixed-precision state",
             "tangents_per_s": int(ok.sum()) / (t_ms / 1e3),
             "ms": t_ms,
             "cg_status_counts": np.bincount(ct, minlength=7).tolist(),
             "inner_iters_per_rhs_median": float(np.median(it[ok] / 9)) if ok.any() else None,
-            "roofline": {"bound": "hbm", "achieved": tan_bytes / (t_ms / 1e3) / 1e9, "peak": PEAK_HBM / 1e9,
-                         "unit": "GB/s", "frac": tan_bytes / (t_ms / 1e3) / PEAK_HBM,
+            "roofline": {"bound": "valu", "achieved": tan_flops / (t_ms / 1e3) / 1e12,
+                         "peak": PEAK_FP32_PUBLISHED / 1e12, "unit": "TFLOP/s",
+                         "frac": tan_flops / (t_ms / 1e3) / PEAK_FP32_PUBLISHED,
+                         "attainable_peak": PEAK_FP32_NONPACKED / 1e12,
+                         "attainable_frac": tan_flops / (t_ms / 1e3) / PEAK_FP32_NONPACKED,
                          "traffic": measured_traffic("tangent"),
                          "kernel": "all tangent launches of one call",
-                         "algorithmic_bytes_per_launch": tan_bytes,
-                         "bytes_per_unit": "20 per fiber + 216 per free node per block iteration of 9 RHS"},
+                         "algorithmic_flops_per_launch": tan_flops,
+                         "flops_per_unit": "36 per fiber + 30 per free node per iteration of a right-hand side"},
+            "hbm_equivalent": {"achieved": tan_bytes / (t_ms / 1e3) / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
+                               "frac": tan_bytes / (t_ms / 1e3) / PEAK_HBM, "algorithmic_bytes_per_launch": tan_bytes,
+                               "bytes_per_unit": "20 per fiber + 216 per free node per block iteration of 9 RHS"},
         }
         log(f"tangent: {t_ms:.1f} ms, status {np.bincount(ct, minlength=7).tolist()}, "
-            f"{out['tangent']['roofline']['achieved']:.0f} GB/s algorithmic")
+            f"{out['tangent']['roofline']['achieved']:.1f} TFLOP/s algorithmic")
     b.close()
 
     # ---------------- side lines on the same batch: kinetic damping, stagnation stop
@@ -443,7 +455,7 @@ def main():
                            "bytes_per_unit": "20 per fiber-iteration + 52 per free-node-iteration"},
     }
 
-    # ---------------- large RVEs (2000 seeds): the HBM-streamed regime
+    # ---------------- large RVEs (2000 seeds): several CUs per RVE
     if args.cfg3_rves > 0:
         t3 = time.time()
         b3net, F3 = load_or_make(3, args.cfg3_rves, args.cache3)
@@ -456,7 +468,8 @@ def main():
         b3.profile(True)
         ms3, s3, st3, it3, gms3 = timed_solves(b3, F3d, 1, 1)
         bytes3 = float((it3 * (20 * nf3 + 52 * nfr3)).sum())
-        rate3 = bytes3 / (ms3 / 1e3)
+        flops3 = float((it3 * (53 * nf3 + 40 * nfr3)).sum())
+        rate3, hbm3 = flops3 / (ms3 / 1e3), bytes3 / (ms3 / 1e3)
         out["large_rves"] = {
             "workload": "%d Voronoi RVEs of 2000 seeds (mean %d fibers), exp fibers, uniaxial F, mixed precision"
                         % (b3net.n_rve, nf3.mean()),
@@ -464,13 +477,18 @@ def main():
             "status_counts": np.bincount(st3, minlength=4).tolist(),
             "converged_per_s": int((st3 == 0).sum()) / (ms3 / 1e3),
             "element_updates_per_s": float((it3 * nf3).sum()) / (ms3 / 1e3),
-            "roofline": {"bound": "hbm", "achieved": rate3 / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
-                         "frac": rate3 / PEAK_HBM, "traffic": measured_traffic("relax_cfg3"),
-                         "algorithmic_bytes_per_launch": bytes3,
-                         "bytes_per_unit": "20 per fiber-iteration + 52 per free-node-iteration"},
+            "roofline": {"bound": "valu and the exchange between the workgroups of an RVE",
+                         "achieved": rate3 / 1e12, "peak": PEAK_FP32_PUBLISHED / 1e12, "unit": "TFLOP/s",
+                         "frac": rate3 / PEAK_FP32_PUBLISHED, "attainable_peak": PEAK_FP32_NONPACKED / 1e12,
+                         "attainable_frac": rate3 / PEAK_FP32_NONPACKED, "kernel": "dr_spread_kernel",
+                         "traffic": measured_traffic("relax_cfg3"), "algorithmic_flops_per_launch": flops3,
+                         "flops_per_unit": "53 per fiber-iteration + 40 per free-node-iteration"},
+            "hbm_equivalent": {"achieved": hbm3 / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
+                               "frac": hbm3 / PEAK_HBM, "algorithmic_bytes_per_launch": bytes3,
+                               "bytes_per_unit": "20 per fiber-iteration + 52 per free-node-iteration"},
         }
         log(f"large RVEs: {ms3:.0f} ms, groups {b3.describe()}, status {np.bincount(st3, minlength=4).tolist()}, "
-            f"{rate3 / 1e9:.0f} GB/s algorithmic ({rate3 / PEAK_HBM:.2f} of peak)")
+            f"{rate3 / 1e12:.1f} TFLOP/s algorithmic ({rate3 / PEAK_FP32_NONPACKED:.2f} of unpacked FP32)")
         b3.close()
         if args.cfg3_streamed:
             # the same workload on the streamed kernel (every array in global

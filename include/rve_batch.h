@@ -80,8 +80,10 @@ extern "C" {
                                   RVE fits; beyond it the incidence kernel
                                   (RVE_MIXED, free nodes of degree <= 16; with
                                   viscous damping and threads_per_rve 0 spread
-                                  over 2 to 16 workgroups per RVE, the same
-                                  results bit for bit), else the streamed
+                                  over 2 to 16 workgroups per RVE: the same
+                                  state bit for bit after the same number of
+                                  iterations, the norms of a convergence test
+                                  the same to rounding), else the streamed
                                   persistent kernel */
 #define RVE_ENGINE_STREAMED 1  /* persistent kernel, state in global memory */
 #define RVE_ENGINE_NAIVE 2     /* one RVE at a time, one launch per step of
@@ -160,8 +162,8 @@ typedef struct {
  *     autotuned variant per size tier), else 256/512/768/1024: only
  *     resident builds of that workgroup size; RVEs none of them holds run
  *     on the streamed kernel (256 threads when 256 is asked for, else 1024
- *     where that build uses no private memory).  A kernel build that uses
- *     private (scratch) memory is never launched.
+ *     where that build uses no private memory, else 512 in RVE_FP64).  A
+ *     kernel build that uses private (scratch) memory is never launched.
  *   cg_tol, cg_max_iter: conjugate-gradient controls of rve_batch_tangent and
  *     rve_batch_vjp.
  *   stream: hipStream_t for every launch and copy (NULL: the null stream).
@@ -204,9 +206,10 @@ typedef struct {
  *     RVE_ORDER_COST: from the second solve of the batch on, descending
  *     cost of the previous solve (iterations x fibers, longest processing
  *     time first; ties and the first solve in host order).  RVE_ORDER_AUTO:
- *     cost order for resident and incidence launches, host order for
- *     streamed and global-mode incidence ones.  Team launches keep host
- *     order.  Results do not depend on the order.
+ *     cost order for resident and incidence launches (over several
+ *     workgroups per RVE: of every size), host order for streamed and
+ *     global-mode incidence ones of one workgroup per RVE.  Team launches
+ *     keep host order.  Results do not depend on the order.
  */
 typedef struct {
     int32_t precision;
@@ -330,7 +333,8 @@ int rve_batch_describe(const rve_batch* b, char* buf, size_t n);
  * allocate on demand: the streamed relaxation workspace (sized for FP64, so
  * any later precision or engine fits), the tangent/VJP arena (per-fiber
  * operators, incidence records, preconditioner, task tables, outputs) and
- * solver slots (the larger of tangent and VJP, both engines), the
+ * solver slots (the larger of tangent and VJP, both engines; the launches of
+ * one call run at once, each with slots of its own), the
  * orientation outputs and the state-export map.  rve_batch_bind_workspace
  * makes the batch carve those areas from [ptr, ptr + bytes): ptr must be
  * device memory of the batch's device, 256-byte aligned, and bytes at least
@@ -478,7 +482,8 @@ int rve_batch_positions(rve_batch* b, int64_t r, double* x);
  * NaN stress, and a host-pointer solve returns RVE_EDEVICE.  Mainly for
  * tests of that path (a limit of 1 poll forces it); polls >= 1.  The spread
  * incidence kernel takes the same limit for each word it waits for; the RVEs
- * of a team that gave up run on the one-workgroup incidence kernel behind it.
+ * of a team that gave up run on the one-workgroup incidence kernel behind it,
+ * a warm start from the state the caller left.
  * Tangents and VJPs of RVEs beyond 4096 free nodes run on such teams too, with
  * the streamed kernel behind.
  */

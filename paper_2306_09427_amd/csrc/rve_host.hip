@@ -1069,14 +1069,14 @@ static void spread_host_init(const HostPack& P, int64_t R, SpreadHost& H)
     H.bslot.assign(P.binc.size(), (uint16_t)kSpreadZero);
 }
 
-// Parts of an RVE: the fewest that hold it (a few counts only, so that RVEs of
-// like size share a launch), `grow` times as many where that is at most
-// kTeamMax.  A batch of many large RVEs takes the fewest: 512 RVEs of 1000
-// seeds relax in 0.075 us per iteration and RVE with 3 parts, 0.084 with 4,
-// 0.118 with 6 (0.081 on the one-workgroup incidence kernel); of 2000 seeds
-// 0.156 with 6, 0.184 with 8 (0.179).  A batch that leaves CUs idle takes more:
-// one RVE of 1000 seeds 6.0 us with 3 parts, 5.0 with 6, 4.5 with 12 (14.6);
-// of 2000 seeds 6.5 with 6, 5.6 with 12 (27.5).
+// Parts of an RVE: the fewest that hold it of a few counts (those between them
+// are not measured), `grow` times as many where that is at most kTeamMax.  A
+// batch of many large RVEs takes the fewest: 512 RVEs of 1000 seeds relax in
+// 0.077 us per iteration and RVE with 3 parts, 0.084 with 4, 0.118 with 6 (0.080
+// on the one-workgroup incidence kernel); of 2000 seeds 0.153 with 6, 0.184 with
+// 8 (0.180).  A batch that leaves CUs idle takes more: one RVE of 1000 seeds 6.0
+// us with 3 parts, 5.0 with 6, 4.2 with 12 (14.6); of 2000 seeds 6.5 with 6, 5.5
+// with 12 (27.5).
 constexpr int kSpreadParts[] = {2, 3, 4, 6, 8, 12, 16};
 
 static bool spread_rve(const HostPack& P, int64_t r, int grow, SpreadHost& H)
@@ -1241,12 +1241,12 @@ static size_t team_ws_bytes(const rve_batch* b)
 // ------------------------------------------------------------------ index replay
 // Host replay of the index arithmetic of the relaxation kernels over a
 // packed batch, with every index bounded against the array it addresses.
-// Register-resident engine, for every RVE and every resident build whose
-// slots hold it: each fiber slot's packed ends (res_pack_ends) against the
-// nf + 1 LDS positions, each node slot's register-held incidence codes
-// (res_inc_code) and CSR overflow reads against the nfib + 1 LDS forces, the
-// code's sign against the incidence, the LDS bytes (dynamic + static)
-// against a CU's 160 KB.  Streamed engine: the workspace offsets of every
+// Register-resident engine, for every RVE and every resident build that holds
+// it (ResLayout): the LDS bytes against a CU's 160 KB, whole waves and the zero
+// slot inside the arrays, each fiber's end offsets (chip_ends) against the
+// positions and the nodes they name, each incidence code (chip_codes, in either
+// half of a word) against the forces, its fiber and its sign, and the nodes of
+// degree above 4 behind the others.  Streamed engine: the workspace offsets of every
 // fiber, node and zero slot against the workspace sizes.  The packing itself:
 // every fiber appears in the incidence of each of its ends with the sign of
 // that end.  Incidence engine: the rank permutation, the rounds and every
@@ -1747,8 +1747,8 @@ static int streamed_blocks_per_cu(int threads, int64_t lds_nodes, bool fp64)
 
 // Workgroup size of the streamed engine: 1024 threads unless 256 are asked
 // for or the 1024-thread build of this precision and damping uses private
-// memory (the FP64 builds do, and take 512 threads, else 256: one RVE of 550
-// seeds 22.7 us per iteration against 28.2 with 256 threads, 1024 of them 196
+// memory (the FP64 builds as compiled do, see wave_sum_by in rve_kernels.hip, and
+// take 512 threads, else 256: one RVE of 550 seeds 22.7 us per iteration against 28.2 with 256 threads, 1024 of them 196
 // against 215 us); 0 when no build may be launched.
 static int streamed_threads(const rve_batch* b, bool fp64)
 {
@@ -3010,8 +3010,8 @@ int rve_batch_import_state(rve_batch* b, const double* F, const double* h, const
 // tables and task groups for the whole batch (allocated once), and the
 // per-workgroup solver slots (`slot_bytes`, grown on demand).
 // RVEs of the spread tangent: those beyond every resident build that have a
-// partition (us per iteration and column, streamed -> spread: one RVE of 4900 free
-// nodes 22 -> 7.2, of 16 000 76 -> 10; 28 at once 46 -> 37 and 184 -> 65).  Not
+// partition (us per iteration, all columns at once, streamed -> spread: one RVE of
+// 4900 free nodes 22 -> 6.5, of 16 000 76 -> 8.7; 28 RVEs 46 -> 34 and 184 -> 59).  Not
 // those of 2048 to 4096 free nodes: 7 to 10 us on one CU, about 2 x 7 on two.
 static bool tangent_spread_rve(const rve_batch* b, int64_t r)
 {

@@ -172,7 +172,6 @@ __host__ __device__ inline uint32_t res_inc_code(uint32_t w) { return (w & 0x7ff
 __host__ __device__ inline uint32_t res_code_fiber(uint32_t code) { return code & 0x7fffu; }
 __host__ __device__ inline bool res_code_neg(uint32_t code) { return (code & 0x8000u) != 0; }
 constexpr int kResIncRegs = 4;          // incidences per node held in registers (two codes per word)
-constexpr int kResMaxFibers = 0x7fff;   // fiber ids and the zero slot fit the 15-bit code
 
 // Fixed LDS layout of a resident workgroup (rve_resident.hip): every array
 // starts at a compile-time offset, so an access is one VGPR address plus an

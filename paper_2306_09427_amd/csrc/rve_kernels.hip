@@ -261,8 +261,10 @@ __device__ __forceinline__ void reset_gslots(RedSlots& red)
 // barrier; the max slot alternates with `parity`, the other slot is cleared
 // for the next call (at least two barriers separate a clear from the next
 // atomic on that slot).
-// The 1024-thread FP64 builds, which exceed their 128 VGPRs and are never
-// launched, keep the ds_bpermute sums.
+// The 1024-thread FP64 builds keep the ds_bpermute sums, with which they exceed
+// their 128 VGPRs and are never launched.  With the lane swaps the viscous
+// streamed build would fit (126 VGPRs, no private memory); whether it is faster
+// than the 512 threads that run in its place has not been measured.
 template <bool LDS>
 __device__ __forceinline__ double wave_sum_by(double v)
 {
@@ -2135,9 +2137,10 @@ hipError_t launch_stress(const SolveArgs& a, int n_rve, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ launch helpers
-// Private bytes of the FP64 resident builds of 768 and 1024 threads with the
-// state of dr_resident_kernel: their state does not fit the 168 or 128 VGPRs,
-// so the host finds a private segment and never launches them.
+// Private bytes of the FP64 resident builds of 768 and 1024 threads, the only
+// ones of dr_resident_kernel that are still compiled: their state does not fit
+// the 168 or 128 VGPRs, so the host finds a private segment and never launches
+// them (no tier of resident_fixed holds them either).
 hipError_t resident_wide_scratch_bytes(int variant, bool fp64, bool kin, size_t* bytes)
 {
     if (!fp64) return hipErrorInvalidValue;

@@ -24,11 +24,13 @@
 // before, which kept the node's position and inverse mass in LDS, masked every
 // slot and read the rest of the incidences from global memory: one RVE of 60
 // seeds 1.60 -> 1.17, of 300 seeds 3.08 -> 2.25, of 400 seeds 3.35 -> 2.74; 1024
-// RVEs of 300 seeds (two per CU) 8.2 -> 7.2.  FP64: 60 seeds 2.34 -> 1.75, 300 seeds
-// 5.74 -> 4.85, 400 seeds (until then beyond the FP64 builds) 20.3 -> 6.2.  Counters
-// of 512 RVEs of 300 seeds: 446 VALU instructions per wave and iteration (496
-// before), 0.85 of the issue slots, LDS busy 0.70 of the time, 0.45 of that in
-// bank conflicts.
+// RVEs of 300 seeds (two per CU) 8.2 -> 7.0.  FP64: 60 seeds 2.34 -> 1.73, 300 seeds
+// 5.74 -> 4.60, 400 seeds (until then beyond the FP64 builds) 20.3 -> 6.2.  A test in
+// every iteration costs 0.8 more at 100 seeds in FP64 (2.30 -> 3.07; linear law 1.99
+// -> 2.76): the norms with a division per node, three wave sums, four dependent
+// two-sums and the boundary loop.  Counters of 2048 RVEs of 300 seeds, two per CU:
+// 472 VALU instructions per wave and iteration, in 0.95 of the busy cycles, LDS
+// busy 0.72 of the time, 0.45 of that in bank conflicts.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

@@ -7,9 +7,9 @@
 // the batch holds hundreds of large RVEs.  Here each workgroup keeps the records of
 // its nodes in registers, as the on-chip tangent does, and an iteration is
 // the share of the arithmetic plus one exchange between the workgroups: one RVE
-// of 10 300 free nodes takes 5.6 us per iteration on 12 CUs (27.5 on one), of
-// 16 000 6.3 us on 16 (51.6); 512 of 4800 free nodes 0.075 us per iteration and
-// RVE on 3 CUs each (0.081), 256 of 16 000 0.229 on 8 (0.712).  What bounds an
+// of 10 300 free nodes takes 5.5 us per iteration on 12 CUs (27.5 on one), of
+// 16 000 5.7 us on 16 (51.6); 512 of 4900 free nodes 0.077 us per iteration and
+// RVE on 3 CUs each (0.080), 256 of 16 000 0.229 on 8 (0.714).  What bounds an
 // iteration now is its chain: the force pass of the largest part (half of the
 // time at 1700 nodes), then the exchange's round trip through memory (2.2 to 3.5
 // us), which no work can hide, as the time step needs every part's maximum.
@@ -31,7 +31,10 @@
 // 512 threads of up to 256 VGPRs with four nodes each: 1024 of 128 spill.
 //
 // Arithmetic, its rounding and the order of every node's sum are those of the
-// incidence kernel (rve_kernels.hip): the results agree bit for bit.
+// incidence kernel (rve_kernels.hip): after the same number of iterations the
+// states agree bit for bit.  The FP64 norms of a convergence test are summed in
+// another order (parts, then members) and agree to rounding, so a test that
+// falls on its threshold may end a run one test earlier or later.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

@@ -1191,9 +1191,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(SN > 2 ? 2 : 
 // parts hold as halo, whose p (and correction) each part then updates itself,
 // with the operations of the owner.  Each is one round trip through memory
 // (about 2 us), which with the barriers around it is what bounds an iteration.
-// Microseconds per iteration and column, streamed -> here: one RVE of 4900 free
-// nodes 22 -> 7.2, of 10 300 42 -> 9.3, of 16 000 76 -> 10; 28 RVEs at once 46 ->
-// 37, 110 -> 42 and 184 -> 65.  The tangents of 256 RVEs of 100 to 3000 seeds took
+// Microseconds per iteration, all nine columns at once, streamed -> here: one RVE
+// of 4900 free nodes 22 -> 6.5, of 10 300 42 -> 8.2, of 16 000 76 -> 8.7; 28 RVEs
+// 46 -> 34, 110 -> 38 and 184 -> 59.  The tangents of 256 RVEs of 100 to 3000 seeds took
 // 50 ms with the streamed kernel and take 27.
 //
 // The arithmetic and its rounding are those of cg_stream_task but for the order
