@@ -2223,9 +2223,11 @@ static int launch_spread_groups(rve_batch* b, const SolveArgs& a, int32_t* queue
     sa.spin_limit = (int32_t)std::min<int64_t>(b->team_spin_limit, INT32_MAX);
     HIP_TRY(launch_team_slots(list0, n0, list1, n1, b->spread_k_dev, b->spread_rve, b->spread_first, s));
     HIP_TRY(launch_zero32(reinterpret_cast<int32_t*>(sa.xchg), 2 * (int64_t)sa.n_areas * sa.area_words, s));
-    HIP_TRY(launch_set_status(b->spread_rve, sa.n_tasks, a.status, kStUnfinished, s));
     const bool warm = a.init == RVE_INIT_WARM;
-    if (warm) HIP_TRY(launch_keep_state(sa, b->spread_kept, false, s));
+    if (warm)
+        HIP_TRY(launch_keep_state(sa, b->spread_kept, false, s));
+    else
+        HIP_TRY(launch_set_status(b->spread_rve, sa.n_tasks, a.status, kStUnfinished, s));
     HIP_TRY(launch_spread(sa, s));
     if (warm) HIP_TRY(launch_keep_state(sa, b->spread_kept, true, s));
     IncArgs it = b->inc_tab;

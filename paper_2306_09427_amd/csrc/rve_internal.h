@@ -389,8 +389,8 @@ hipError_t tangent_spread_info(int* blocks_per_cu, size_t* private_bytes);
 size_t tangent_spread_slot_bytes();
 constexpr int kStUnfinished = -1;    // status of an RVE a team has not finished
 hipError_t launch_spread(const SpreadArgs& a, hipStream_t s);
-// Keep the start of a warm solve (kept: 3 doubles per entry of `own`), and put
-// it back for the RVEs left unfinished.
+// Mark the RVEs of a warm solve unfinished and keep their start (kept: 3 doubles
+// per entry of `own`); or put it back for those left unfinished.
 hipError_t launch_keep_state(const SpreadArgs& a, double* kept, bool restore, hipStream_t s);
 hipError_t spread_info(int* blocks_per_cu, size_t* private_bytes);
 hipError_t launch_set_status(const int32_t* list, int n, int32_t* status, int32_t value, hipStream_t s);

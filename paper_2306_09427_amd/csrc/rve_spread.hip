@@ -570,16 +570,18 @@ __global__ void set_status(const int32_t* list, int n, int32_t* status, int32_t 
 }
 
 // The free nodes' fluctuation of the listed RVEs into `kept` (in the order of
-// their parts' nodes), or back where the status is kStUnfinished.
+// their parts' nodes) and their status to kStUnfinished; or (restore) back where
+// the status still is.
 __global__ __launch_bounds__(256) void keep_state(const int32_t* list, const SpreadPart* parts, const int64_t* part_first,
-                                                  const int64_t* free_off, double* h, double* kept,
-                                                  const int32_t* unfinished)
+                                                  const int64_t* free_off, double* h, double* kept, int32_t* status,
+                                                  bool restore)
 {
     const int r = list[blockIdx.x];
-    if (unfinished && unfinished[r] != kStUnfinished) return;
+    if (restore && status[r] != kStUnfinished) return;
+    if (!restore && blockIdx.y == 0 && threadIdx.x == 0) status[r] = kStUnfinished;
     const int64_t a0 = 3 * free_off[r], n = 3 * free_off[r + 1] - a0, k0 = 3 * parts[part_first[r]].own0;
     for (int64_t q = blockIdx.y * 256 + threadIdx.x; q < n; q += 256 * gridDim.y) {
-        if (unfinished)
+        if (restore)
             h[a0 + q] = kept[k0 + q];
         else
             kept[k0 + q] = h[a0 + q];
@@ -592,7 +594,7 @@ hipError_t launch_keep_state(const SpreadArgs& a, double* kept, bool restore, hi
 {
     if (a.n_tasks <= 0) return hipSuccess;
     hipLaunchKernelGGL(keep_state, dim3((unsigned)a.n_tasks, 8), dim3(256), 0, s, a.task_rve, a.parts, a.part_first,
-                       a.s.net.free_off, a.s.h_state, kept, restore ? a.s.status : nullptr);
+                       a.s.net.free_off, a.s.h_state, kept, a.s.status, restore);
     return hipGetLastError();
 }
 
